@@ -30,6 +30,11 @@
 namespace rs {
 namespace {
 
+// Lane column of the n-th quad of a row pair (its partner is CQ further): of every 2 CQ
+// columns the first CQ.
+template <int CQ>
+__device__ constexpr int quad_column(int n) { return n / CQ * (2 * CQ) + n % CQ; }
+
 // One lens's terms for this lane's RX x RY rays: dx per column, dy and dy^2 per
 // row, then per ray r^2 = fma(dx, dx, dy^2), the reciprocal and two FMAs into the
 // FP32 sums. The reciprocal issues at a fraction of the FMA rate, so rays share it
@@ -54,59 +59,74 @@ __device__ __forceinline__ void lens_terms(float LX, float LY, float M, const fl
     }
 #pragma unroll
     for (int c = 0; c < RX; ++c) dx[c] = rxl[c] - LX;
+    if (QUAD) {
+        constexpr int NQ = RX * RY / 4;   // quad q: rows 2 (q / (RX / 2)) and the next, column quad_column(q)
+        float ra[NQ], rb[NQ], rc[NQ], rd[NQ], pab[NQ], pcd[NQ], R[NQ];
 #pragma unroll
-    for (int r = 0; r < RY; r += 2)
-#pragma unroll
-        for (int c = 0; c < RX; ++c) {
-            if (QUAD) {
-                if ((c / CQ) % 2) continue;
-                const int e = c + CQ;
-                const float ra = __builtin_fmaf(dx[c], dx[c], dy2[r]);
-                const float rb = __builtin_fmaf(dx[c], dx[c], dy2[r + 1]);
-                const float rc = __builtin_fmaf(dx[e], dx[e], dy2[r]);
-                const float rd = __builtin_fmaf(dx[e], dx[e], dy2[r + 1]);
-                const float pab = ra * rb, pcd = rc * rd;
-                const float R = __builtin_amdgcn_rcpf(pab * pcd);
-                const float qab = R * pcd, qcd = R * pab;
-                float ia = rb * qab, ib = ra * qab, ic = rd * qcd, id = rc * qcd;
-                if (!UNIT) {
-                    ia = M * ia;
-                    ib = M * ib;
-                    ic = M * ic;
-                    id = M * id;
-                }
-                sx[r][c] = __builtin_fmaf(dx[c], ia, sx[r][c]);
-                sy[r][c] = __builtin_fmaf(dy[r], ia, sy[r][c]);
-                sx[r + 1][c] = __builtin_fmaf(dx[c], ib, sx[r + 1][c]);
-                sy[r + 1][c] = __builtin_fmaf(dy[r + 1], ib, sy[r + 1][c]);
-                sx[r][e] = __builtin_fmaf(dx[e], ic, sx[r][e]);
-                sy[r][e] = __builtin_fmaf(dy[r], ic, sy[r][e]);
-                sx[r + 1][e] = __builtin_fmaf(dx[e], id, sx[r + 1][e]);
-                sy[r + 1][e] = __builtin_fmaf(dy[r + 1], id, sy[r + 1][e]);
-            } else {
-                const float ra = __builtin_fmaf(dx[c], dx[c], dy2[r]);
-                const float rb = __builtin_fmaf(dx[c], dx[c], dy2[r + 1]);
-                const float rab = __builtin_amdgcn_rcpf(ra * rb);
-                float ia = rb * rab, ib = ra * rab;
-                if (!UNIT) {
-                    ia = M * ia;
-                    ib = M * ib;
-                }
-                sx[r][c] = __builtin_fmaf(dx[c], ia, sx[r][c]);
-                sy[r][c] = __builtin_fmaf(dy[r], ia, sy[r][c]);
-                sx[r + 1][c] = __builtin_fmaf(dx[c], ib, sx[r + 1][c]);
-                sy[r + 1][c] = __builtin_fmaf(dy[r + 1], ib, sy[r + 1][c]);
-            }
+        for (int q = 0; q < NQ; ++q) {
+            const int r = 2 * (q / (RX / 2)), c = quad_column<CQ>(q % (RX / 2)), e = c + CQ;
+            ra[q] = __builtin_fmaf(dx[c], dx[c], dy2[r]);
+            rb[q] = __builtin_fmaf(dx[c], dx[c], dy2[r + 1]);
+            rc[q] = __builtin_fmaf(dx[e], dx[e], dy2[r]);
+            rd[q] = __builtin_fmaf(dx[e], dx[e], dy2[r + 1]);
+            pab[q] = ra[q] * rb[q];
+            pcd[q] = rc[q] * rd[q];
+            R[q] = pab[q] * pcd[q];
         }
+        rcp_all(R);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int r = 2 * (q / (RX / 2)), c = quad_column<CQ>(q % (RX / 2)), e = c + CQ;
+            const float qab = R[q] * pcd[q], qcd = R[q] * pab[q];
+            float ia = rb[q] * qab, ib = ra[q] * qab, ic = rd[q] * qcd, id = rc[q] * qcd;
+            if (!UNIT) {
+                ia = M * ia;
+                ib = M * ib;
+                ic = M * ic;
+                id = M * id;
+            }
+            sx[r][c] = __builtin_fmaf(dx[c], ia, sx[r][c]);
+            sy[r][c] = __builtin_fmaf(dy[r], ia, sy[r][c]);
+            sx[r + 1][c] = __builtin_fmaf(dx[c], ib, sx[r + 1][c]);
+            sy[r + 1][c] = __builtin_fmaf(dy[r + 1], ib, sy[r + 1][c]);
+            sx[r][e] = __builtin_fmaf(dx[e], ic, sx[r][e]);
+            sy[r][e] = __builtin_fmaf(dy[r], ic, sy[r][e]);
+            sx[r + 1][e] = __builtin_fmaf(dx[e], id, sx[r + 1][e]);
+            sy[r + 1][e] = __builtin_fmaf(dy[r + 1], id, sy[r + 1][e]);
+        }
+    } else {
+        constexpr int NP = RX * RY / 2;   // pair q: rows 2 (q / RX) and the next, column q % RX
+        float ra[NP], rb[NP], R[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int r = 2 * (q / RX), c = q % RX;
+            ra[q] = __builtin_fmaf(dx[c], dx[c], dy2[r]);
+            rb[q] = __builtin_fmaf(dx[c], dx[c], dy2[r + 1]);
+            R[q] = ra[q] * rb[q];
+        }
+        rcp_all(R);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int r = 2 * (q / RX), c = q % RX;
+            float ia = rb[q] * R[q], ib = ra[q] * R[q];
+            if (!UNIT) {
+                ia = M * ia;
+                ib = M * ib;
+            }
+            sx[r][c] = __builtin_fmaf(dx[c], ia, sx[r][c]);
+            sy[r][c] = __builtin_fmaf(dy[r], ia, sy[r][c]);
+            sx[r + 1][c] = __builtin_fmaf(dx[c], ib, sx[r + 1][c]);
+            sy[r + 1][c] = __builtin_fmaf(dy[r + 1], ib, sy[r + 1][c]);
+        }
+    }
 }
 
-// FP32 sums over the N lenses of tile entries g .. g+N-1 for this lane's rays
-// (lens_terms), folded into the FP64 accumulators. Every LDS read is a 16-byte
-// broadcast: two lenses of unit mass, or one lens with its mass. The four-ray
-// loop is unrolled by 8 reads, not fully (a full unroll makes the compiler spill);
-// the two-ray loop fully.
-template <int N, int RX, int RY, bool UNIT, bool QUAD, int CQ>
-__device__ __forceinline__ void group_sums(const float4 *tile, int g, const float (&rxl)[RX], const float (&ryl)[RY],
+// FP32 sums over the n lenses of tile entries g .. g+n-1 (n = GROUP or GROUP / 2) for
+// this lane's rays (lens_terms), folded into the FP64 accumulators. Every LDS read is a
+// 16-byte broadcast: two lenses of unit mass, or one lens with its mass. The loops are
+// unrolled by 8 reads (four-ray form; a full unroll makes the compiler spill) or 4.
+template <int RX, int RY, bool UNIT, bool QUAD, int CQ>
+__device__ __forceinline__ void group_sums(const float4 *tile, int g, int n, const float (&rxl)[RX], const float (&ryl)[RY],
                                            double (&Ax)[RY][RX], double (&Ay)[RY][RX]) {
     static_assert(RY % 2 == 0, "rows are paired for the shared reciprocal");
     static_assert(RX == 4 * CQ, "column partners are CQ lane columns apart");
@@ -118,37 +138,17 @@ __device__ __forceinline__ void group_sums(const float4 *tile, int g, const floa
             sx[r][c] = 0.0f;
             sy[r][c] = 0.0f;
         }
-    if (UNIT) {
-        if (QUAD) {
-#pragma unroll 8
-            for (int kk = 0; kk < N; kk += 2) {
-                const float4 q = tile[(g + kk) >> 1];
-                lens_terms<RX, RY, true, true, CQ>(q.x, q.y, 1.0f, rxl, ryl, sx, sy);
-                lens_terms<RX, RY, true, true, CQ>(q.z, q.w, 1.0f, rxl, ryl, sx, sy);
-            }
-        } else {
+    constexpr int LENSES = UNIT ? 2 : 1;      // per read
+    constexpr int READS = QUAD ? 8 : 4;       // per round
+    const float4 *const end = tile + (g + n) / LENSES;
+#pragma unroll 1
+    for (const float4 *p = tile + g / LENSES; p < end; p += READS)
 #pragma unroll
-            for (int kk = 0; kk < N; kk += 2) {
-                const float4 q = tile[(g + kk) >> 1];
-                lens_terms<RX, RY, true, false, CQ>(q.x, q.y, 1.0f, rxl, ryl, sx, sy);
-                lens_terms<RX, RY, true, false, CQ>(q.z, q.w, 1.0f, rxl, ryl, sx, sy);
-            }
+        for (int k = 0; k < READS; ++k) {
+            const float4 q = p[k];
+            lens_terms<RX, RY, UNIT, QUAD, CQ>(q.x, q.y, q.z, rxl, ryl, sx, sy);   // (UNIT: the mass is not used)
+            if (UNIT) lens_terms<RX, RY, UNIT, QUAD, CQ>(q.z, q.w, 1.0f, rxl, ryl, sx, sy);
         }
-    } else {
-        if (QUAD) {
-#pragma unroll 8
-            for (int kk = 0; kk < N; ++kk) {
-                const float4 q = tile[g + kk];
-                lens_terms<RX, RY, false, true, CQ>(q.x, q.y, q.z, rxl, ryl, sx, sy);
-            }
-        } else {
-#pragma unroll
-            for (int kk = 0; kk < N; ++kk) {
-                const float4 q = tile[g + kk];
-                lens_terms<RX, RY, false, false, CQ>(q.x, q.y, q.z, rxl, ryl, sx, sy);
-            }
-        }
-    }
 #pragma unroll
     for (int r = 0; r < RY; ++r)
 #pragma unroll
@@ -169,7 +169,6 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
     static_assert(RX * STRIDE_X == PATCH_X && RY * STRIDE_Y == PATCH_Y, "shape must tile the patch");
     static_assert(BLOCK_THREADS / 64 <= 16, "reduction buffer");
     float4 *tile = sm.tile;
-    int &near_count = sm.near_count;
     double *red_bx = sm.red_bx;
     double *red_by = sm.red_by;
 
@@ -215,7 +214,7 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
         }
 
     if (tid == 0) {
-        near_count = 0;
+        sm.near_count = 0;
         sm.far_tile = -1;
     }
     double bx = 0.0, by = 0.0;  // this thread's share of the block error bound (units of u)
@@ -235,15 +234,15 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
         // Whole groups of real lenses with four-ray reciprocals where the tile's lenses
         // and the patch allow them; then the rest (groups holding padding lenses, at
         // offset PAD_OFFSET, or every group of a tile out of range) with two-ray ones. The
-        // last tile may end with half a group, summed by code of its own, so that the
-        // loops' schedules are those of whole groups.
+        // last tile may end with half a group.
         const int tile_idx = (int)(t0 / LENS_TILE);
         const int full_q = (quad_patch && sm.far_tile != tile_idx) ? cnt / GROUP * GROUP : 0;
-        const int full = cnt_pad / GROUP * GROUP;
         int g = 0;
-        for (; g < full_q; g += GROUP) group_sums<GROUP, RX, RY, UNIT, true, CQ>(tile, g, rxl, ryl, Ax, Ay);
-        for (; g < full; g += GROUP) group_sums<GROUP, RX, RY, UNIT, false, CQ>(tile, g, rxl, ryl, Ax, Ay);
-        if (full < cnt_pad) group_sums<GROUP / 2, RX, RY, UNIT, false, CQ>(tile, full, rxl, ryl, Ax, Ay);
+#pragma unroll 1
+        for (; g < full_q; g += GROUP) group_sums<RX, RY, UNIT, true, CQ>(tile, g, GROUP, rxl, ryl, Ax, Ay);
+#pragma unroll 1
+        for (; g < cnt_pad; g += GROUP)
+            group_sums<RX, RY, UNIT, false, CQ>(tile, g, cnt_pad - g < GROUP ? cnt_pad - g : GROUP, rxl, ryl, Ax, Ay);
     }
 
     // Block-wide error bound (mixed mode).
@@ -267,33 +266,54 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
             Bx += red_bx[w];
             By += red_by[w];
         }
-        n_near = near_count;
+        n_near = sm.near_count;
         // (a patch under 1e-6 across could underflow the paired products of r^2)
         all_flagged = n_near > NEAR_MAX || h < 1.0e-6;
         if (all_flagged) n_near = 0;
     }
 
-    // Epilogue: macro terms, pixel, classification, binning.
+    // Epilogue: macro terms, pixel, classification, binning, one ray of each lane at a
+    // time. The deflections go through the tile's LDS (each wave's own part, half of its
+    // rays at a time), so that the loop is not unrolled over registers: unrolled, it was
+    // most of the kernel's code, and a small map spent more time fetching it than on its
+    // sums.
     const float h_f = (float)h;
     const float tiny_r2 = 1.0e-6f * h_f * h_f;
     unsigned long long n_in = 0, n_out = 0, n_sing = 0;
     const int64_t W = a.i1 - a.i0;
+    constexpr int HELD = RX * RY / 2;   // rays per lane held at a time
+    static_assert(sizeof(double2) * HELD * BLOCK_THREADS <= sizeof(sm.tile), "half of the rays fit the tile");
+    double2 *const held = reinterpret_cast<double2 *>(sm.tile) + wave * (HELD * 64) + lane;
+    __syncthreads();   // every wave is done with the tile
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-    for (int r = 0; r < RY; ++r)
-#pragma unroll
-        for (int c = 0; c < RX; ++c) {
+        for (int k = 0; k < HELD; ++k) {
+            const int r0 = k / RX, r1 = RY / 2 + k / RX, c = k % RX;
+            held[64 * k] = half ? make_double2(Ax[r1][c], Ay[r1][c]) : make_double2(Ax[r0][c], Ay[r0][c]);
+        }
+        wave_lds_fence();
+#pragma unroll 1
+        for (int k = 0; k < HELD; ++k) {
+            const int r = half * (RY / 2) + k / RX, c = k % RX;
+            const double2 A = held[64 * k];
             const int64_t i = i_lane + c * STRIDE_X, j = j_pair + 2 * (r >> 1) * STRIDE_Y + (r & 1);
             const bool valid = (i < a.i1) && (j < a.jc1);
             const double x1 = ray_coord(a.sx0, i, a.spx);
             const double x2 = ray_coord(a.sy0, j, a.spy);
-            const double y1 = a.c1 * x1 - Ax[r][c];
-            const double y2 = a.c2 * x2 - Ay[r][c];
+            const double y1 = a.c1 * x1 - A.x;
+            const double y2 = a.c2 * x2 - A.y;
             const double u = (y1 - a.tx0) * a.inv_pixw;
             const double v = (y2 - a.ty0) * a.inv_pixh;
-            const int cp = ((c / CQ) % 2) ? c - CQ : c + CQ;   // the column partner of the four-ray reciprocal
-            int code = classify_ray<MODE>(a, x1, x2, Ax[r][c], Ay[r][c], u, v, rxl[c], ryl[r], rxl[c], ryl[r ^ 1],
-                                          rxl[cp], quad_patch, Bx, By, n_near, all_flagged, sm.near_list, k_term,
-                                          h_f, tiny_r2);
+            // the ray's FP32 offsets, and its reciprocal partners': the other row of its
+            // pair, and the column 16 apart
+            const int cp = ((c / CQ) % 2) ? -16 : 16;
+            const int64_t jp = j + ((r & 1) ? -1 : 1);
+            const float rx = (float)(x1 - ox), ry = (float)(x2 - oy);
+            const float ryp = (float)(ray_coord(a.sy0, jp, a.spy) - oy);
+            const float rxq = (float)(ray_coord(a.sx0, i + cp, a.spx) - ox);
+            int code = classify_ray<MODE>(a, x1, x2, A.x, A.y, u, v, rx, ry, rx, ryp, rxq, quad_patch, Bx, By, n_near,
+                                          all_flagged, sm.near_list, h_f, tiny_r2);
             if (!valid) code = INT32_MIN;
 
             n_in += __builtin_popcountll(__ballot(code >= 0));
@@ -310,6 +330,8 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
                 if (fl) sink.append(a, fl, lane, code == FLAGGED, i, j);
             }
         }
+        wave_lds_fence();
+    }
     if (lane == 0) {
         if (n_in) atomicAdd(a.counters + C_IN, n_in);
         if (n_out) atomicAdd(a.counters + C_OUT, n_out);
