@@ -600,6 +600,19 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const Shoot
     }
 }
 
+// A wave's rays to re-check (lanes fl) appended to the launch's queue, which holds every
+// ray of the launch. The far-field mode leaves a handful of rays per map.
+__device__ __forceinline__ void queue_append(const ShootArgs &a, uint64_t fl, int lane, bool mine, int64_t i, int64_t j) {
+    const int first = __builtin_ctzll(fl);
+    uint32_t base = 0;
+    if (lane == first) base = atomicAdd(a.qcount, (uint32_t)__builtin_popcountll(fl));
+    base = __builtin_amdgcn_readlane(base, first);
+    if (mine) {
+        const uint32_t below = (uint32_t)__builtin_popcountll(fl & ((1ull << lane) - 1ull));
+        a.queue[base + below] = (uint32_t)((j - a.jc0) * (a.i1 - a.i0) + (i - a.i0));
+    }
+}
+
 struct FarSmem {
     PixelTable table;            // the patch's counts per pixel (map mode)
     double near_x[NEAR_EXP], near_y[NEAR_EXP], near_m[NEAR_EXP];
@@ -746,10 +759,10 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
                 if (PIX) {
                     if (valid && code != FLAGGED) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
                 } else {
-                    table_add(sm.table, a.map, code);
+                    if (code >= 0) table_add(sm.table, a.map, code, 1u);
                 }
                 const uint64_t fl = __ballot(code == FLAGGED);
-                if (fl) SingleSink{}.append(a, fl, lane, code == FLAGGED, i, j);
+                if (fl) queue_append(a, fl, lane, code == FLAGGED, i, j);
             }
         }
         if (tid == 0) sm.next = (int)next;

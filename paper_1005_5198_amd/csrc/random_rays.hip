@@ -168,7 +168,7 @@ __device__ __forceinline__ void shoot_free_chunk(const ShootArgs &a, uint32_t ba
         Ay[q] = 0.0;
     }
 
-    if (tid == 0) sm.near_count = 0;
+    smem_begin(sm, tid);
     double bx = 0.0, by = 0.0;
     const double k_term = UNIT ? K_TERM_UNIT : K_TERM_MASS;
     float4 *tile = sm.tile;
@@ -214,7 +214,7 @@ __device__ __forceinline__ void shoot_free_chunk(const ShootArgs &a, uint32_t ba
 
     const float h_f = (float)h;
     const float tiny_r2 = 1.0e-6f * h_f * h_f;
-    unsigned long long n_in = 0, n_out = 0, n_sing = 0;
+    uint32_t n_in = 0, n_out = 0, n_sing = 0;
     const int64_t W = a.i1 - a.i0;
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
@@ -240,18 +240,14 @@ __device__ __forceinline__ void shoot_free_chunk(const ShootArgs &a, uint32_t ba
         if (PIX) {
             if (valid && code != FLAGGED) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
         } else {
-            aggregated_add(a.map, code);
+            wave_table_add(sm.table, a.map, code);
         }
         if (MODE == 1) {
             const uint64_t fl = __ballot(code == FLAGGED);
-            if (fl) SingleSink{}.append(a, fl, lane, code == FLAGGED, i, j);
+            if (fl) SingleSink{}.append(a, sm, fl, lane, code == FLAGGED, i, j);
         }
     }
-    if (lane == 0) {
-        if (n_in) atomicAdd(a.counters + C_IN, n_in);
-        if (n_out) atomicAdd(a.counters + C_OUT, n_out);
-        if (n_sing) atomicAdd(a.counters + C_SING, n_sing);
-    }
+    smem_end<BLOCK_THREADS, MODE, PIX>(a, sm, SingleSink{}, tid, n_in, n_out, n_sing);
 }
 
 constexpr int FREE_RR = 8;
@@ -262,6 +258,7 @@ constexpr int FREE_CAP = 64 * FREE_WAVES * FREE_RR;
 template <bool UNIT, int MODE, bool PIX>
 __global__ __launch_bounds__(64 * FREE_WAVES) void shoot_free_kernel(const ShootArgs a) {
     __shared__ ShootSmem sm;
+    if (!PIX) table_clear<64 * FREE_WAVES>(sm.table, threadIdx.x);
     const int64_t bin = blockIdx.x;
     const uint32_t beg = a.bin_offset[bin], end = a.bin_offset[bin + 1];
     const int64_t bxi = bin % a.nbx_r, byi = bin / a.nbx_r;

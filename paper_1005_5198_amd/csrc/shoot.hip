@@ -23,8 +23,10 @@
 //    the FP32 error of every ray in the patch (lenses close to the patch are
 //    bounded per ray instead). A ray whose bound reaches a pixel edge goes to a
 //    queue that the FP64 re-check stages decide exactly as the definition does.
-//  * Binning uses wave-aggregated atomics: lanes that hit the same pixel add
-//    their count with one atomic.
+//  * Binning: a block counts its rays per pixel in an LDS table and then adds each
+//    distinct pixel's count to the map with one atomic (one wave's rays fall on up to 64
+//    pixels, so aggregating within a wave alone took up to 64 rounds per ray of a lane:
+//    half of the time of the 1024^2-ray, 462-lens map).
 #include "shoot_common.h"
 
 namespace rs {
@@ -213,10 +215,7 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
             Ay[r][c] = 0.0;
         }
 
-    if (tid == 0) {
-        sm.near_count = 0;
-        sm.far_tile = -1;
-    }
+    smem_begin(sm, tid);
     double bx = 0.0, by = 0.0;  // this thread's share of the block error bound (units of u)
     const double k_term = UNIT ? K_TERM_QUAD : K_TERM_MASS_QUAD;
     // Four-ray reciprocals need the patch's half-diagonal in range (see QUAD_RANGE).
@@ -279,7 +278,7 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
     // sums.
     const float h_f = (float)h;
     const float tiny_r2 = 1.0e-6f * h_f * h_f;
-    unsigned long long n_in = 0, n_out = 0, n_sing = 0;
+    uint32_t n_in = 0, n_out = 0, n_sing = 0;
     const int64_t W = a.i1 - a.i0;
     constexpr int HELD = RX * RY / 2;   // rays per lane held at a time
     static_assert(sizeof(double2) * HELD * BLOCK_THREADS <= sizeof(sm.tile), "half of the rays fit the tile");
@@ -323,26 +322,23 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
             if (PIX) {
                 if (valid && code != FLAGGED) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
             } else {
-                aggregated_add(a.map, code);
+                wave_table_add(sm.table, a.map, code);
             }
             if (MODE == 1) {
                 const uint64_t fl = __ballot(code == FLAGGED);
-                if (fl) sink.append(a, fl, lane, code == FLAGGED, i, j);
+                if (fl) sink.append(a, sm, fl, lane, code == FLAGGED, i, j);
             }
         }
         wave_lds_fence();
     }
-    if (lane == 0) {
-        if (n_in) atomicAdd(a.counters + C_IN, n_in);
-        if (n_out) atomicAdd(a.counters + C_OUT, n_out);
-        if (n_sing) atomicAdd(a.counters + C_SING, n_sing);
-    }
+    smem_end<BLOCK_THREADS, MODE, PIX>(a, sm, sink, tid, n_in, n_out, n_sing);
 }
 
 // Single map: one block per patch of this launch's rows.
 template <int RX, int RY, int WX, int WY, bool UNIT, int MODE, bool PIX>
 __global__ __launch_bounds__(64 * WX * WY, (RX * RY <= 8) ? 4 : 1) void shoot_kernel(const ShootArgs a) {
     __shared__ ShootSmem sm;
+    if (!PIX) table_clear<64 * WX * WY>(sm.table, threadIdx.x);   // (barriers follow before its first use)
     shoot_patch<RX, RY, WX, WY, UNIT, MODE, PIX>(a, (int64_t)blockIdx.x, sm, SingleSink{});
 }
 
@@ -352,6 +348,7 @@ template <int RX, int RY, int WX, int WY, bool UNIT, int MODE>
 __global__ __launch_bounds__(64 * WX * WY, (RX * RY <= 8) ? 4 : 1) void shoot_batch_kernel(const BatchArgs b) {
     __shared__ ShootSmem sm;
     __shared__ long long s_tile;
+    table_clear<64 * WX * WY>(sm.table, threadIdx.x);
     for (;;) {
         __syncthreads();  // s_tile of the previous round has been read by every thread
         if (threadIdx.x == 0) s_tile = (long long)atomicAdd(b.tile_counter, 1ull);

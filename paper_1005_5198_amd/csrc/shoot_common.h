@@ -80,18 +80,6 @@ __device__ __forceinline__ void rcp_all(float (&R)[N]) {
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
-// Add one count per lane to map[p] for every lane with p >= 0, one atomic per distinct pixel.
-__device__ __forceinline__ void aggregated_add(uint32_t *map, int p) {
-    uint64_t pending = __ballot(p >= 0);
-    while (pending) {
-        const int leader = __builtin_ctzll(pending);
-        const int lp = __builtin_amdgcn_readlane(p, leader);
-        const uint64_t same = __ballot(p == lp) & pending;
-        if (lane_id() == leader) atomicAdd(map + lp, (uint32_t)__builtin_popcountll(same));
-        pending &= ~same;
-    }
-}
-
 // A block's counts per pixel in LDS (open addressing on the pixel index): rays add
 // with LDS atomics, and the block then adds each distinct pixel's count to the map
 // with one global atomic. A ray whose pixel finds no free slot within PT_PROBES
@@ -112,20 +100,37 @@ __device__ __forceinline__ void table_clear(PixelTable &t, int tid) {
     }
 }
 
-// Count one ray in pixel p (p < 0: nothing to count).
-__device__ __forceinline__ void table_add(PixelTable &t, uint32_t *map, int p) {
-    if (p < 0) return;
+// Count n rays in pixel p >= 0.
+__device__ __forceinline__ void table_add(PixelTable &t, uint32_t *map, int p, uint32_t n) {
     const uint32_t k = (uint32_t)p + 1u;
     uint32_t s = (k * 2654435761u) >> 21;   // multiplicative hash onto 2^11 slots
     for (int probe = 0; probe < PT_PROBES; ++probe) {
         const uint32_t old = atomicCAS(&t.key[s], 0u, k);
         if (old == 0u || old == k) {
-            atomicAdd(&t.cnt[s], 1u);
+            atomicAdd(&t.cnt[s], n);
             return;
         }
         s = (s + 1u) & (PT_SLOTS - 1);
     }
-    global_add(map + p, 1u);
+    global_add(map + p, n);
+}
+
+// Count each lane's ray in its pixel p (p < 0: nothing to count). Lanes of one pixel
+// are added together while that takes AGG_MIN lanes or more off the wave; the others add
+// one by one.
+constexpr int AGG_MIN = 8;
+__device__ __forceinline__ void wave_table_add(PixelTable &t, uint32_t *map, int p) {
+    uint64_t pending = __ballot(p >= 0);
+    while (pending) {
+        const int leader = __builtin_ctzll(pending);
+        const int lp = __builtin_amdgcn_readlane(p, leader);
+        const uint64_t same = __ballot(p == lp) & pending;
+        const int n = __builtin_popcountll(same);
+        if (n < AGG_MIN) break;
+        if (lane_id() == leader) table_add(t, map, lp, (uint32_t)n);
+        pending &= ~same;
+    }
+    if ((pending >> lane_id()) & 1ull) table_add(t, map, p, 1u);
 }
 static_assert(PT_SLOTS == 1 << 11, "the hash keeps 11 bits");
 
@@ -153,26 +158,45 @@ __device__ __forceinline__ void table_flush_clear(PixelTable &t, uint32_t *map, 
     }
 }
 
+constexpr int FLAG_LIST = 512;   // rays to re-check that a block holds before it appends them to the queue
+
 struct ShootSmem {
     float4 tile[LENS_TILE];        // UNIT: two (x,y) pairs per float4; else (x,y,m,0)
     NearLens near_list[NEAR_MAX];
     int near_count;
     int far_tile;                  // last tile (index) with a lens beyond QUAD_RANGE of the patch centre
     double red_bx[16], red_by[16];
+    PixelTable table;              // the patch's counts per pixel (map output)
+    uint32_t count[3];             // its rays in the map, out and singular
+    uint32_t n_flagged;            // its rays to re-check (the first FLAG_LIST of them in flagged)
+    uint32_t flagged[FLAG_LIST];
 };
 
 // Queue sink of a single-map launch: uint32 chunk-relative ray indices; the
-// queue holds every ray of the launch, so it cannot overflow.
+// queue holds every ray of the launch, so it cannot overflow. A block collects its rays
+// in LDS and takes its part of the queue once, at its end: one atomic on the queue's
+// length per block instead of one per wave and ray of a lane.
 struct SingleSink {
-    __device__ void append(const ShootArgs &a, uint64_t fl, int lane, bool mine, int64_t i, int64_t j) const {
+    __device__ void append(const ShootArgs &a, ShootSmem &sm, uint64_t fl, int lane, bool mine, int64_t i, int64_t j) const {
         const int first = __builtin_ctzll(fl);
         uint32_t base = 0;
-        if (lane == first) base = atomicAdd(a.qcount, (uint32_t)__builtin_popcountll(fl));
-        base = __builtin_amdgcn_readlane(base, first);
+        if (lane == first) base = atomicAdd(&sm.n_flagged, (uint32_t)__builtin_popcountll(fl));
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, first);
         if (mine) {
-            const uint32_t below = (uint32_t)__builtin_popcountll(fl & ((1ull << lane) - 1ull));
-            a.queue[base + below] = (uint32_t)((j - a.jc0) * (a.i1 - a.i0) + (i - a.i0));
+            const uint32_t at = base + (uint32_t)__builtin_popcountll(fl & ((1ull << lane) - 1ull));
+            const uint32_t ray = (uint32_t)((j - a.jc0) * (a.i1 - a.i0) + (i - a.i0));
+            if (at < (uint32_t)FLAG_LIST) sm.flagged[at] = ray;
+            else a.queue[atomicAdd(a.qcount, 1u)] = ray;   // the list is full
         }
+    }
+    // By one wave, after every append (and a barrier).
+    __device__ void flush(const ShootArgs &a, const ShootSmem &sm, int lane) const {
+        const uint32_t n = sm.n_flagged < (uint32_t)FLAG_LIST ? sm.n_flagged : (uint32_t)FLAG_LIST;
+        if (n == 0) return;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(a.qcount, n);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        for (uint32_t k = lane; k < n; k += 64) a.queue[base + k] = sm.flagged[k];
     }
 };
 
@@ -181,14 +205,45 @@ struct SingleSink {
 struct BatchSink {
     unsigned long long *counters;
     uint32_t *flag_bits;
-    __device__ void append(const ShootArgs &a, uint64_t fl, int lane, bool mine, int64_t i, int64_t j) const {
-        if (lane == __builtin_ctzll(fl)) atomicAdd(counters + C_RECHECK, (unsigned long long)__builtin_popcountll(fl));
+    __device__ void append(const ShootArgs &a, ShootSmem &sm, uint64_t fl, int lane, bool mine, int64_t i, int64_t j) const {
+        if (lane == __builtin_ctzll(fl)) atomicAdd(&sm.n_flagged, (uint32_t)__builtin_popcountll(fl));
         if (mine) {
             const uint32_t ray = (uint32_t)((j - a.j0) * (a.i1 - a.i0) + (i - a.i0));
             atomicOr(flag_bits + (ray >> 5), 1u << (ray & 31u));
         }
     }
+    __device__ void flush(const ShootArgs &a, const ShootSmem &sm, int lane) const {
+        if (lane == 0 && sm.n_flagged) global_add(counters + C_RECHECK, (unsigned long long)sm.n_flagged);
+    }
 };
+
+// A block's bookkeeping for one patch (or bin chunk): cleared before its first barrier,
+// added to after it.
+__device__ __forceinline__ void smem_begin(ShootSmem &sm, int tid) {
+    if (tid == 0) {
+        sm.near_count = 0;
+        sm.far_tile = -1;
+        sm.n_flagged = 0u;
+    }
+    if (tid < 3) sm.count[tid] = 0u;
+}
+
+// The patch's results leave the block: its pixels' counts (the table is empty after it),
+// its counters and the rays to re-check.
+template <int THREADS, int MODE, bool PIX, class Sink>
+__device__ __forceinline__ void smem_end(const ShootArgs &a, ShootSmem &sm, const Sink &sink, int tid, uint32_t n_in,
+                                         uint32_t n_out, uint32_t n_sing) {
+    static_assert(C_IN == 0 && C_OUT == 1 && C_SING == 2, "order of sm.count");
+    if ((tid & 63) == 0) {
+        if (n_in) atomicAdd(&sm.count[C_IN], n_in);
+        if (n_out) atomicAdd(&sm.count[C_OUT], n_out);
+        if (n_sing) atomicAdd(&sm.count[C_SING], n_sing);
+    }
+    __syncthreads();
+    if (MODE == 1 && tid < 64) sink.flush(a, sm, tid);
+    if (!PIX) table_flush_clear<THREADS>(sm.table, a.map, tid);
+    if (tid < 3 && sm.count[tid]) global_add(a.counters + tid, (unsigned long long)sm.count[tid]);
+}
 
 // Stage lenses t0 .. t0+cnt of the lens array into the LDS tile as FP32 offsets
 // from the block origin (ox, oy), padded to whole half groups with lenses at
@@ -275,28 +330,32 @@ __device__ __forceinline__ int classify_ray(const ShootArgs &a, double x1, doubl
     } else {
         // Per-ray bound from the lenses next to the block.
         float cx = 0.0f, cy = 0.0f;
+        bool bad = false;
+#pragma unroll 2
         for (int q = 0; q < n_near; ++q) {
             const NearLens nl = near_list[q];
             const float dxn = rx - nl.x, dyn = ry - nl.y;
             const float r2n = dxn * dxn + dyn * dyn;
             const float dxp = rxp - nl.x, dyp = ryp - nl.y;
             const float r2p = dxp * dxp + dyp * dyp;
-            const float wgt = nl.wgt;
-            bool quad_ok = true;
+            bad |= !(r2n > tiny_r2) || !(r2p > tiny_r2);
             if (quad) {
                 const float dxq = rxq - nl.x;
-                const double r2q = (double)(dxq * dxq + dyn * dyn), r2qp = (double)(dxq * dxq + dyp * dyp);
-                const double pa = (double)r2n * (double)r2p, pc = r2q * r2qp;
-                quad_ok = pa > QUAD_P_MIN && pc > QUAD_P_MIN && pa * pc > QUAD_P_MIN;
+                const float r2q = dxq * dxq + dyn * dyn, r2qp = dxq * dxq + dyp * dyp;
+                // (four factors above 2^-25 have products above 2^-100)
+                if (!(fminf(fminf(r2n, r2p), fminf(r2q, r2qp)) > 0x1p-25f)) {
+                    const double pa = (double)r2n * (double)r2p, pc = (double)r2q * (double)r2qp;
+                    bad |= !(pa > QUAD_P_MIN && pc > QUAD_P_MIN && pa * pc > QUAD_P_MIN);
+                }
             }
-            if (!(r2n > tiny_r2) || !(r2p > tiny_r2) || !quad_ok) {
-                cx = __builtin_inff();
-                cy = __builtin_inff();
-            } else {
-                const float im = nl.m / (0.999f * r2n);
-                cx += im * (wgt * (1.001f * fabsf(dxn) + 1e-6f * h_f) + (float)K_H * h_f);
-                cy += im * (wgt * (1.001f * fabsf(dyn) + 1e-6f * h_f) + (float)K_H * h_f);
-            }
+            // (v_rcp_f32 is within 1 ulp; the factor also covers r2n's rounding)
+            const float im = nl.m * __builtin_amdgcn_rcpf(0.9985f * r2n);
+            cx += im * (nl.wgt * (1.001f * fabsf(dxn) + 1e-6f * h_f) + (float)K_H * h_f);
+            cy += im * (nl.wgt * (1.001f * fabsf(dyn) + 1e-6f * h_f) + (float)K_H * h_f);
+        }
+        if (bad) {
+            cx = __builtin_inff();
+            cy = __builtin_inff();
         }
         const double ea = 1e-15 + 8.9e-16 * (fabs(a.c1 * x1) + fabs(Axv) + fabs(a.tx0));
         const double eb = 1e-15 + 8.9e-16 * (fabs(a.c2 * x2) + fabs(Ayv) + fabs(a.ty0));
