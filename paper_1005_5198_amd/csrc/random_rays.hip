@@ -85,57 +85,59 @@ __global__ __launch_bounds__(256) void rand_scatter_kernel(const ShootArgs a) {
     }
 }
 
-// FP32 sums over the N lenses of tile entries g .. g+N-1 for RR rays with no
+// FP32 sums over the n lenses of tile entries g .. g+n-1 for RR rays with no
 // shared rows or columns (per ray dx, dy, dy^2, r^2, reciprocal, two FMAs),
-// folded into the FP64 accumulators. Unit masses: the two lenses of one LDS
-// read share one v_rcp_f32 per ray, of the product of the ray's two r^2 (a
-// ray's arithmetic must not depend on its slot, which the scatter's atomics set).
-template <int N, int RR, bool UNIT>
-__device__ __forceinline__ void free_group_sums(const float4 *tile, int g, const float (&rx)[RR],
+// folded into the FP64 accumulators. Two lenses share one v_rcp_f32 per ray, of
+// the product of the ray's two r^2 (a ray's arithmetic must not depend on its
+// slot, which the scatter's atomics set).
+template <int RR, bool UNIT>
+__device__ __forceinline__ void free_group_sums(const float4 *tile, int g, int n, const float (&rx)[RR],
                                                 const float (&ry)[RR], double (&Ax)[RR], double (&Ay)[RR]) {
+    constexpr int READS = 4;   // pairs of lenses per round (GROUP / 2 is a multiple of two rounds' lenses)
+    static_assert((GROUP / 2) % (2 * READS) == 0, "whole rounds");
     float sx[RR], sy[RR];
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
         sx[q] = 0.0f;
         sy[q] = 0.0f;
     }
-    if (UNIT) {
+#pragma unroll 1
+    for (int kk = 0; kk < n; kk += 2 * READS)
 #pragma unroll
-        for (int kk = 0; kk < N; kk += 2) {
-            const float4 l2 = tile[(g + kk) >> 1];   // lenses g+kk (x, y) and g+kk+1 (z, w)
+        for (int k = 0; k < READS; ++k) {
+            // lenses a and b: of one read (unit masses) or two
+            const float4 la = UNIT ? tile[((g + kk) >> 1) + k] : tile[g + kk + 2 * k];
+            const float4 lb = UNIT ? make_float4(la.z, la.w, 1.0f, 0.0f) : tile[g + kk + 2 * k + 1];
 #pragma unroll
-            for (int q = 0; q < RR; ++q) {
-                const float dxa = rx[q] - l2.x, dya = ry[q] - l2.y;
-                const float dxb = rx[q] - l2.z, dyb = ry[q] - l2.w;
-                const float ra = __builtin_fmaf(dxa, dxa, dya * dya);
-                const float rb = __builtin_fmaf(dxb, dxb, dyb * dyb);
-                const float rab = __builtin_amdgcn_rcpf(ra * rb);
-                const float ia = rb * rab, ib = ra * rab;
-                sx[q] = __builtin_fmaf(dxa, ia, sx[q]);
-                sy[q] = __builtin_fmaf(dya, ia, sy[q]);
-                sx[q] = __builtin_fmaf(dxb, ib, sx[q]);
-                sy[q] = __builtin_fmaf(dyb, ib, sy[q]);
+            for (int q0 = 0; q0 < RR; q0 += 4) {   // four rays' reciprocals at a time
+                float dxa[4], dya[4], dxb[4], dyb[4], ra[4], rb[4], R[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int q = q0 + e;
+                    dxa[e] = rx[q] - la.x;
+                    dya[e] = ry[q] - la.y;
+                    dxb[e] = rx[q] - lb.x;
+                    dyb[e] = ry[q] - lb.y;
+                    ra[e] = __builtin_fmaf(dxa[e], dxa[e], dya[e] * dya[e]);
+                    rb[e] = __builtin_fmaf(dxb[e], dxb[e], dyb[e] * dyb[e]);
+                    R[e] = ra[e] * rb[e];
+                }
+                rcp_all(R);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int q = q0 + e;
+                    float ia = rb[e] * R[e], ib = ra[e] * R[e];
+                    if (!UNIT) {
+                        ia = la.z * ia;
+                        ib = lb.z * ib;
+                    }
+                    sx[q] = __builtin_fmaf(dxa[e], ia, sx[q]);
+                    sy[q] = __builtin_fmaf(dya[e], ia, sy[q]);
+                    sx[q] = __builtin_fmaf(dxb[e], ib, sx[q]);
+                    sy[q] = __builtin_fmaf(dyb[e], ib, sy[q]);
+                }
             }
         }
-    } else {
-#pragma unroll
-        for (int kk = 0; kk < N; kk += 2) {
-            const float4 la = tile[g + kk], lb = tile[g + kk + 1];
-#pragma unroll
-            for (int q = 0; q < RR; ++q) {
-                const float dxa = rx[q] - la.x, dya = ry[q] - la.y;
-                const float dxb = rx[q] - lb.x, dyb = ry[q] - lb.y;
-                const float ra = __builtin_fmaf(dxa, dxa, dya * dya);
-                const float rb = __builtin_fmaf(dxb, dxb, dyb * dyb);
-                const float rab = __builtin_amdgcn_rcpf(ra * rb);
-                const float ia = la.z * (rb * rab), ib = lb.z * (ra * rab);
-                sx[q] = __builtin_fmaf(dxa, ia, sx[q]);
-                sy[q] = __builtin_fmaf(dya, ia, sy[q]);
-                sx[q] = __builtin_fmaf(dxb, ib, sx[q]);
-                sy[q] = __builtin_fmaf(dyb, ib, sy[q]);
-            }
-        }
-    }
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
         Ax[q] += (double)sx[q];
@@ -180,10 +182,10 @@ __device__ __forceinline__ void shoot_free_chunk(const ShootArgs &a, uint32_t ba
         stage_tile<UNIT, MODE, BLOCK_THREADS>(a, t0, cnt, cnt_pad, ox, oy, hx, hy, h, near_r2, k_term, sm, tid, bx,
                                               by);
         __syncthreads();
-        // Whole groups in the loop; the last tile may end with half a group, summed after it.
-        const int full = cnt_pad / GROUP * GROUP;
-        for (int g = 0; g < full; g += GROUP) free_group_sums<GROUP, RR, UNIT>(tile, g, rx, ry, Ax, Ay);
-        if (full < cnt_pad) free_group_sums<GROUP / 2, RR, UNIT>(tile, full, rx, ry, Ax, Ay);
+        // the last tile may end with half a group
+#pragma unroll 1
+        for (int g = 0; g < cnt_pad; g += GROUP)
+            free_group_sums<RR, UNIT>(tile, g, cnt_pad - g < GROUP ? cnt_pad - g : GROUP, rx, ry, Ax, Ay);
     }
 
     double Bx = 0.0, By = 0.0;
@@ -212,40 +214,56 @@ __device__ __forceinline__ void shoot_free_chunk(const ShootArgs &a, uint32_t ba
         if (all_flagged) n_near = 0;
     }
 
+    // One ray of each lane at a time, the deflections through the tile's LDS (each wave's
+    // own part, half of its rays at a time), so that the loop is not unrolled over registers.
     const float h_f = (float)h;
     const float tiny_r2 = 1.0e-6f * h_f * h_f;
     uint32_t n_in = 0, n_out = 0, n_sing = 0;
     const int64_t W = a.i1 - a.i0;
+    constexpr int HELD = RR / 2;
+    static_assert(sizeof(double2) * HELD * BLOCK_THREADS <= sizeof(sm.tile), "half of the rays fit the tile");
+    double2 *const held = reinterpret_cast<double2 *>(sm.tile) + wave * (HELD * 64) + lane;
+    __syncthreads();   // every wave is done with the tile
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-    for (int q = 0; q < RR; ++q) {
-        const uint32_t slot = base + (uint32_t)(q * BLOCK_THREADS + tid);
-        const bool valid = slot < end;
-        const int64_t rel = valid ? (int64_t)a.ray_rel[slot] : 0;
-        const int64_t i = a.i0 + rel % W, j = a.jc0 + rel / W;
-        const double x1 = valid ? a.ray_x[slot] : ox;
-        const double x2 = valid ? a.ray_y[slot] : oy;
-        const double y1 = a.c1 * x1 - Ax[q];
-        const double y2 = a.c2 * x2 - Ay[q];
-        const double u = (y1 - a.tx0) * a.inv_pixw;
-        const double v = (y2 - a.ty0) * a.inv_pixh;
-        // reciprocals are shared between two lenses of one ray, not between rays
-        int code = classify_ray<MODE>(a, x1, x2, Ax[q], Ay[q], u, v, rx[q], ry[q], rx[q], ry[q], rx[q], false, Bx, By,
-                                      n_near, all_flagged, sm.near_list, h_f, tiny_r2);
-        if (!valid) code = INT32_MIN;
+        for (int k = 0; k < HELD; ++k)
+            held[64 * k] = half ? make_double2(Ax[HELD + k], Ay[HELD + k]) : make_double2(Ax[k], Ay[k]);
+        wave_lds_fence();
+#pragma unroll 1
+        for (int k = 0; k < HELD; ++k) {
+            const double2 A = held[64 * k];
+            const uint32_t slot = base + (uint32_t)((half * HELD + k) * BLOCK_THREADS + tid);
+            const bool valid = slot < end;
+            const int64_t rel = valid ? (int64_t)a.ray_rel[slot] : 0;
+            const int64_t i = a.i0 + rel % W, j = a.jc0 + rel / W;
+            const double x1 = valid ? a.ray_x[slot] : ox;
+            const double x2 = valid ? a.ray_y[slot] : oy;
+            const float fx = valid ? (float)(x1 - ox) : 0.0f, fy = valid ? (float)(x2 - oy) : 0.0f;
+            const double y1 = a.c1 * x1 - A.x;
+            const double y2 = a.c2 * x2 - A.y;
+            const double u = (y1 - a.tx0) * a.inv_pixw;
+            const double v = (y2 - a.ty0) * a.inv_pixh;
+            // reciprocals are shared between two lenses of one ray, not between rays
+            int code = classify_ray<MODE>(a, x1, x2, A.x, A.y, u, v, fx, fy, fx, fy, fx, false, Bx, By, n_near,
+                                          all_flagged, sm.near_list, h_f, tiny_r2);
+            if (!valid) code = INT32_MIN;
 
-        n_in += __builtin_popcountll(__ballot(code >= 0));
-        n_out += __builtin_popcountll(__ballot(code == OUT));
-        n_sing += __builtin_popcountll(__ballot(code == SINGULAR));
+            n_in += __builtin_popcountll(__ballot(code >= 0));
+            n_out += __builtin_popcountll(__ballot(code == OUT));
+            n_sing += __builtin_popcountll(__ballot(code == SINGULAR));
 
-        if (PIX) {
-            if (valid && code != FLAGGED) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
-        } else {
-            wave_table_add(sm.table, a.map, code);
+            if (PIX) {
+                if (valid && code != FLAGGED) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
+            } else {
+                wave_table_add(sm.table, a.map, code);
+            }
+            if (MODE == 1) {
+                const uint64_t fl = __ballot(code == FLAGGED);
+                if (fl) SingleSink{}.append(a, sm, fl, lane, code == FLAGGED, i, j);
+            }
         }
-        if (MODE == 1) {
-            const uint64_t fl = __ballot(code == FLAGGED);
-            if (fl) SingleSink{}.append(a, sm, fl, lane, code == FLAGGED, i, j);
-        }
+        wave_lds_fence();
     }
     smem_end<BLOCK_THREADS, MODE, PIX>(a, sm, SingleSink{}, tid, n_in, n_out, n_sing);
 }
@@ -256,7 +274,7 @@ constexpr int FREE_CAP = 64 * FREE_WAVES * FREE_RR;
 
 // One block per bin; a bin with more rays than one chunk holds takes several passes.
 template <bool UNIT, int MODE, bool PIX>
-__global__ __launch_bounds__(64 * FREE_WAVES) void shoot_free_kernel(const ShootArgs a) {
+__global__ __launch_bounds__(64 * FREE_WAVES, 4) void shoot_free_kernel(const ShootArgs a) {
     __shared__ ShootSmem sm;
     if (!PIX) table_clear<64 * FREE_WAVES>(sm.table, threadIdx.x);
     const int64_t bin = blockIdx.x;

@@ -48,9 +48,11 @@ __device__ constexpr int quad_column(int n) { return n / CQ * (2 * CQ) + n % CQ;
 //  * otherwise rows 2k and 2k+1 of a column share one, of the product of their
 //    r^2 (1/a = b/(ab), 1/b = a/(ab)), three multiplies per two rays.
 // With masses each reciprocal is multiplied by the lens's mass last, so a unit
-// mass gives the unit path's result. The partners do not depend on the thread
-// shape, so neither does a ray's arithmetic.
-template <int RX, int RY, bool UNIT, bool QUAD, int CQ>
+// mass gives the unit path's result; in mixed mode (SHARE_M, whose map is the
+// definition's whatever the rounding within its bound) the mass multiplies the two
+// factors that the four reciprocals share, two multiplies less per four rays. The partners
+// do not depend on the thread shape, so neither does a ray's arithmetic.
+template <int RX, int RY, bool UNIT, bool SHARE_M, bool QUAD, int CQ>
 __device__ __forceinline__ void lens_terms(float LX, float LY, float M, const float (&rxl)[RX],
                                            const float (&ryl)[RY], float (&sx)[RY][RX], float (&sy)[RY][RX]) {
     float dy[RY], dy2[RY], dx[RX];
@@ -79,9 +81,13 @@ __device__ __forceinline__ void lens_terms(float LX, float LY, float M, const fl
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const int r = 2 * (q / (RX / 2)), c = quad_column<CQ>(q % (RX / 2)), e = c + CQ;
-            const float qab = R[q] * pcd[q], qcd = R[q] * pab[q];
+            float qab = R[q] * pcd[q], qcd = R[q] * pab[q];
+            if (!UNIT && SHARE_M) {
+                qab = M * qab;
+                qcd = M * qcd;
+            }
             float ia = rb[q] * qab, ib = ra[q] * qab, ic = rd[q] * qcd, id = rc[q] * qcd;
-            if (!UNIT) {
+            if (!UNIT && !SHARE_M) {
                 ia = M * ia;
                 ib = M * ib;
                 ic = M * ic;
@@ -127,7 +133,7 @@ __device__ __forceinline__ void lens_terms(float LX, float LY, float M, const fl
 // this lane's rays (lens_terms), folded into the FP64 accumulators. Every LDS read is a
 // 16-byte broadcast: two lenses of unit mass, or one lens with its mass. The loops are
 // unrolled by 8 reads (four-ray form; a full unroll makes the compiler spill) or 4.
-template <int RX, int RY, bool UNIT, bool QUAD, int CQ>
+template <int RX, int RY, bool UNIT, bool SHARE_M, bool QUAD, int CQ>
 __device__ __forceinline__ void group_sums(const float4 *tile, int g, int n, const float (&rxl)[RX], const float (&ryl)[RY],
                                            double (&Ax)[RY][RX], double (&Ay)[RY][RX]) {
     static_assert(RY % 2 == 0, "rows are paired for the shared reciprocal");
@@ -148,8 +154,8 @@ __device__ __forceinline__ void group_sums(const float4 *tile, int g, int n, con
 #pragma unroll
         for (int k = 0; k < READS; ++k) {
             const float4 q = p[k];
-            lens_terms<RX, RY, UNIT, QUAD, CQ>(q.x, q.y, q.z, rxl, ryl, sx, sy);   // (UNIT: the mass is not used)
-            if (UNIT) lens_terms<RX, RY, UNIT, QUAD, CQ>(q.z, q.w, 1.0f, rxl, ryl, sx, sy);
+            lens_terms<RX, RY, UNIT, SHARE_M, QUAD, CQ>(q.x, q.y, q.z, rxl, ryl, sx, sy);   // (UNIT: the mass is not used)
+            if (UNIT) lens_terms<RX, RY, UNIT, SHARE_M, QUAD, CQ>(q.z, q.w, 1.0f, rxl, ryl, sx, sy);
         }
 #pragma unroll
     for (int r = 0; r < RY; ++r)
@@ -238,10 +244,10 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
         const int full_q = (quad_patch && sm.far_tile != tile_idx) ? cnt / GROUP * GROUP : 0;
         int g = 0;
 #pragma unroll 1
-        for (; g < full_q; g += GROUP) group_sums<RX, RY, UNIT, true, CQ>(tile, g, GROUP, rxl, ryl, Ax, Ay);
+        for (; g < full_q; g += GROUP) group_sums<RX, RY, UNIT, MODE == 1, true, CQ>(tile, g, GROUP, rxl, ryl, Ax, Ay);
 #pragma unroll 1
         for (; g < cnt_pad; g += GROUP)
-            group_sums<RX, RY, UNIT, false, CQ>(tile, g, cnt_pad - g < GROUP ? cnt_pad - g : GROUP, rxl, ryl, Ax, Ay);
+            group_sums<RX, RY, UNIT, MODE == 1, false, CQ>(tile, g, cnt_pad - g < GROUP ? cnt_pad - g : GROUP, rxl, ryl, Ax, Ay);
     }
 
     // Block-wide error bound (mixed mode).
