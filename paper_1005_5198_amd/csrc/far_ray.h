@@ -5,6 +5,8 @@
 // and the evaluation of one ray from its super-patch record and lens list.
 #pragma once
 
+#include <type_traits>
+
 #include "shoot_common.h"
 
 namespace rs {
@@ -95,16 +97,23 @@ __device__ inline ShootArgs batch_far_args(const BatchMap &m) {
 // Re-check stage F for one ray at (x1, x2) inside super-patch sp: the
 // super-patch's series (Horner in -w = zS - z, the series the patch kernel
 // re-centres) plus its listed lenses summed directly in FP64, under the patch
-// kernel's bound with no patch level. Returns the definition's pixel or OUT,
+// kernel's bound with no patch level (which holds for any order of the direct sum). Returns the definition's pixel or OUT,
 // or FLAGGED when the bound reaches a pixel edge, the ray sits on a listed
 // lens, or the list overflowed.
-template <bool UNIT>
+// WAVE: one ray for the whole wave (every argument the same in every lane, and so the
+// result), the record by scalar loads and the listed lenses split over the lanes;
+// otherwise one ray per lane. The listed lenses' indices and positions are loaded several
+// at a time, so that their latencies overlap. (Grouping the lanes by super-patch to read
+// the lists by scalar loads was no faster where a wave's rays share one, and twice as slow
+// where random rays do not.)
+template <bool UNIT, bool WAVE>
 __device__ inline int far_eval(const ShootArgs &a, int64_t sp, double x1, double x2) {
     constexpr double U64 = 1.1102230246251565e-16;  // 2^-53
-    const int32_t *list = a.ff_near + sp * (int64_t)(1 + a.ff_cap);
-    const int32_t listed = list[0];
+    const int32_t *const list = a.ff_near + sp * (int64_t)(1 + a.ff_cap);
+    const int32_t listed = ((const global_i32 *)list)[0];
     if (listed > a.ff_cap) return FLAGGED;
-    const double *rec = a.ff_super + sp * (int64_t)FAR_REC;
+    using rec_double = typename std::conditional<WAVE, const_double, global_double>::type;
+    const rec_double *const rec = (const rec_double *)(a.ff_super + sp * (int64_t)FAR_REC);
     double cx, cy, H;
     super_geometry(a, sp, cx, cy, H);
     const double nw1 = cx - x1, nw2 = cy - x2;   // -w
@@ -116,20 +125,47 @@ __device__ inline int far_eval(const ShootArgs &a, int64_t sp, double x1, double
         S1 = q1;
         S2 = q2;
     }
-    double a1 = S1, a2 = -S2;
+    double a1 = WAVE ? 0.0 : S1, a2 = WAVE ? 0.0 : -S2;
     double snear = 0.0;
-    bool tiny = false;
-    for (int l = 0; l < listed; ++l) {
-        const int64_t k = list[1 + l];
-        const double e1 = x1 - ((global_double *)a.lens_xy)[2 * k];
-        const double e2 = x2 - ((global_double *)a.lens_xy)[2 * k + 1];
+    int tiny = 0;
+    auto add = [&](double X, double Y, double m) {
+        const double e1 = x1 - X;
+        const double e2 = x2 - Y;
         const double r2 = __builtin_fma(e1, e1, e2 * e2);
         tiny |= !(r2 > 1e-200);
-        const double m = (UNIT || a.lens_m == nullptr) ? 1.0 : ((global_double *)a.lens_m)[k];
         const double f = m * rcp64(r2);
         a1 = __builtin_fma(f, e1, a1);
         a2 = __builtin_fma(f, e2, a2);
         snear = __builtin_fma(fabs(e1) + fabs(e2), fabs(f), snear);
+    };
+    constexpr int U = 4;   // lenses in flight per lane
+    const int step = WAVE ? 64 : 1;
+    for (int l0 = WAVE ? lane_id() : 0; l0 < listed; l0 += U * step) {
+        int64_t k[U];
+        double X[U], Y[U], m[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)   // past the end: the last one, not added
+            k[u] = ((const global_i32 *)list)[1 + (l0 + u * step < listed ? l0 + u * step : listed - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            X[u] = ((global_double *)a.lens_xy)[2 * k[u]];
+            Y[u] = ((global_double *)a.lens_xy)[2 * k[u] + 1];
+            m[u] = (UNIT || a.lens_m == nullptr) ? 1.0 : ((global_double *)a.lens_m)[k[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (l0 + u * step < listed) add(X[u], Y[u], m[u]);
+    }
+    if (WAVE) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            a1 += __shfl_xor(a1, off);
+            a2 += __shfl_xor(a2, off);
+            snear += __shfl_xor(snear, off);
+            tiny |= __shfl_xor(tiny, off);
+        }
+        a1 += S1;
+        a2 -= S2;
     }
     const double SFAR = rec[2 * FAR_P], TRUNC = rec[2 * FAR_P + 1], SDEF = rec[2 * FAR_P + 2];
     const double NFAR = rec[2 * FAR_P + 3];
@@ -137,11 +173,19 @@ __device__ inline int far_eval(const ShootArgs &a, int64_t sp, double x1, double
     return far_decide(a, x1, x2, a1, a2, far_err, SFAR, SDEF, snear, listed, !tiny);
 }
 
+// A wave-uniform 64-bit value in scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // Stage F for ray (i, j): on the grid its super-patch follows from its indices;
 // a random ray's from its position (the cell of the whole rectangle's
 // super-patch grid that holds it, clamped: a ray within rounding of a cell
 // edge is still inside the neighbouring box's one-spacing slack).
-template <bool UNIT>
+// One ray per lane, or with WAVE one ray (i, j the same in every lane) for the whole wave.
+template <bool UNIT, bool WAVE>
 __device__ inline int far_recheck_ray(const ShootArgs &a, int64_t i, int64_t j) {
     double x1, x2;
     int64_t sp;
@@ -155,9 +199,10 @@ __device__ inline int far_recheck_ray(const ShootArgs &a, int64_t i, int64_t j) 
     } else {
         x1 = ray_coord(a.sx0, i, a.spx);
         x2 = ray_coord(a.sy0, j, a.spy);
-        sp = ((j - a.ff_j0) / (PATCH_Y * FF_SP_Y)) * a.ff_sbx + (i - a.ff_i0) / (PATCH_X * FF_SP_X);
+        const uint32_t row = (uint32_t)(j - a.ff_j0) / (PATCH_Y * FF_SP_Y), col = (uint32_t)(i - a.ff_i0) / (PATCH_X * FF_SP_X);
+        sp = (int64_t)row * a.ff_sbx + col;
     }
-    return far_eval<UNIT>(a, sp, x1, x2);
+    return far_eval<UNIT, WAVE>(a, WAVE ? uniform64(sp) : sp, x1, x2);
 }
 
 }  // namespace

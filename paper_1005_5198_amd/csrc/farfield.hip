@@ -776,49 +776,83 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
     }
 }
 
-// Re-check stage of the mixed mode on the regular grid, one thread per queued
-// ray (far_recheck_ray). A ray it places is binned and its entry marked
-// RESOLVED; the others are counted in *qlive and left for the FP64 stage over
-// every lens. Queue entries of one deflection wave are adjacent and share a
-// super-patch, so a wave walks one list.
-template <bool UNIT>
-__global__ __launch_bounds__(256) void recheck_far_kernel(const ShootArgs a, uint32_t *qlive) {
+// At most this many queued rays take stage F one wave per ray (a short queue leaves
+// most of the chip idle otherwise: the 1219 rays of the 1024^2-ray, 462-lens map, whose
+// super-patches list almost every lens, took 84 us one thread per ray).
+constexpr uint32_t FAR_WAVE_MAX = 32768;
+
+// Re-check stage F of the mixed mode (far_recheck_ray), one thread or one wave per
+// queued ray. A ray it places is binned. STAGE_A: the others take stage A at once, one
+// wave per ray, and are marked UNRESOLVED when that cannot place them either;
+// otherwise a ray it places is marked RESOLVED, and the others are counted in *qlive and
+// left for the stages over every lens. Queue entries of one deflection block are
+// adjacent and share a super-patch, so a wave walks one list.
+template <bool UNIT, bool STAGE_A>
+__global__ __launch_bounds__(256, 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
+    __shared__ uint32_t sums[3];   // rays in the map, out, left
     const uint32_t n = *a.qcount;
-    const int64_t W = a.i1 - a.i0;
-    unsigned long long n_in = 0, n_out = 0;
-    uint32_t left = 0;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += stride) {
-        const uint32_t q = a.queue[idx];
-        const int64_t i = a.i0 + (int64_t)(q % (uint64_t)W);
-        const int64_t j = a.jc0 + (int64_t)(q / (uint64_t)W);
-        const int code = far_recheck_ray<UNIT>(a, i, j);
-        if (code == FLAGGED) {
-            ++left;
-        } else {
-            a.queue[idx] = q | RESOLVED;
+    if (n == 0) return;
+    if (threadIdx.x < 3) sums[threadIdx.x] = 0u;
+    __syncthreads();
+    const uint32_t W = (uint32_t)(a.i1 - a.i0);   // at most 2^22
+    const int lane = lane_id();
+    const uint32_t wave_id = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
+    uint32_t n_in = 0, n_out = 0, left = 0;   // this lane's
+    const bool wave_form = n <= FAR_WAVE_MAX;
+    if (STAGE_A && wave_id == 0 && lane == 0) atomicAdd(a.counters + C_RECHECK, (unsigned long long)n);
+    // wave form: entry wave_id, wave_id + n_waves, ...; thread form: 64 entries at a time
+    for (uint64_t e0 = wave_form ? wave_id : 64ull * wave_id; e0 < n; e0 += wave_form ? n_waves : 64ull * n_waves) {
+        const uint64_t idx = wave_form ? e0 : e0 + (uint32_t)lane;
+        const bool mine = wave_form ? lane == 0 : idx < n;   // this lane records the entry's result
+        const uint32_t q = a.queue[idx < n ? idx : n - 1];
+        const int64_t i = a.i0 + (int64_t)(q % W);
+        const int64_t j = a.jc0 + (int64_t)(q / W);
+        int code = wave_form ? far_recheck_ray<UNIT, true>(a, i, j) : far_recheck_ray<UNIT, false>(a, i, j);
+        uint64_t todo = __ballot(mine && code == FLAGGED);
+        if (mine && code == FLAGGED) ++left;
+        if (STAGE_A) {
+            while (todo) {
+                const int src = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
+                int c = 0;
+                const bool decided = fast_ray_wave<UNIT>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c);
+                if (lane == src) {
+                    if (decided) {
+                        code = c;
+                    } else {
+                        a.queue[idx] = q | UNRESOLVED;
+                        atomicAdd(r.qunres, 1u);
+                    }
+                }
+            }
+        }
+        if (mine && code != FLAGGED) {
+            if (!STAGE_A) a.queue[idx] = q | RESOLVED;
             if (code >= 0) ++n_in;
             else ++n_out;
-            if (a.pix_out) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
-            else if (code >= 0) atomicAdd(a.map + code, 1u);
+            if (a.pix_out) a.pix_out[(j - a.j0) * (int64_t)W + (i - a.i0)] = code;
+            else if (code >= 0) global_add(a.map + code, 1u);
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        n_in += __shfl_xor(n_in, off);
-        n_out += __shfl_xor(n_out, off);
-        left += __shfl_xor(left, off);
-    }
-    if (__lane_id() == 0) {
-        if (n_in) atomicAdd(a.counters + C_IN, n_in);
-        if (n_out) atomicAdd(a.counters + C_OUT, n_out);
-        if (left) atomicAdd(qlive, left);
+    // one atomic per block and counter: atomics on one address take about 12 ns each
+    if (n_in) atomicAdd(&sums[0], n_in);
+    if (n_out) atomicAdd(&sums[1], n_out);
+    if (left) atomicAdd(&sums[2], left);
+    __syncthreads();
+    if (threadIdx.x < 2 && sums[threadIdx.x])
+        global_add(a.counters + (threadIdx.x ? C_OUT : C_IN), (unsigned long long)sums[threadIdx.x]);
+    if (threadIdx.x == 2 && sums[2]) {
+        if (STAGE_A) global_add(a.counters + C_DIRECT, (unsigned long long)sums[2]);
+        else atomicAdd(qlive, sums[2]);
     }
 }
 
 }  // namespace
 
-hipError_t launch_recheck_far(const ShootArgs &a, uint32_t *qlive, int64_t max_rays, hipStream_t stream) {
+hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t *qlive, bool stage_a, int64_t max_rays,
+                              hipStream_t stream) {
     if (max_rays <= 0) return hipSuccess;
     const bool unit = a.lens_m == nullptr;
     if (!a.random) {   // grid: this launch's records (random rays: the map's, built once)
@@ -832,9 +866,15 @@ hipError_t launch_recheck_far(const ShootArgs &a, uint32_t *qlive, int64_t max_r
         if (e != hipSuccess) return e;
     }
     int64_t blocks = (max_rays + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    if (unit) hipLaunchKernelGGL((recheck_far_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, stream, a, qlive);
-    else hipLaunchKernelGGL((recheck_far_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, stream, a, qlive);
+    if (blocks > 1024) blocks = 1024;
+    const dim3 grid((unsigned)blocks), block(256);
+    if (unit) {
+        if (stage_a) hipLaunchKernelGGL((recheck_far_kernel<true, true>), grid, block, 0, stream, a, r, qlive);
+        else hipLaunchKernelGGL((recheck_far_kernel<true, false>), grid, block, 0, stream, a, r, qlive);
+    } else {
+        if (stage_a) hipLaunchKernelGGL((recheck_far_kernel<false, true>), grid, block, 0, stream, a, r, qlive);
+        else hipLaunchKernelGGL((recheck_far_kernel<false, false>), grid, block, 0, stream, a, r, qlive);
+    }
     return hipGetLastError();
 }
 

@@ -320,7 +320,7 @@ __device__ inline bool batch_stage_f(const BatchArgs &b, QueueEntry e, bool vali
             const int64_t W = a.i1 - a.i0;
             const int64_t i = a.i0 + (int64_t)(e.ray % (uint64_t)W);
             const int64_t j = a.j0 + (int64_t)(e.ray / (uint64_t)W);
-            code = (ALL_UNIT || a.lens_m == nullptr) ? far_recheck_ray<true>(a, i, j) : far_recheck_ray<false>(a, i, j);
+            code = (ALL_UNIT || a.lens_m == nullptr) ? far_recheck_ray<true, false>(a, i, j) : far_recheck_ray<false, false>(a, i, j);
             if (code >= 0) atomicAdd(a.map + code, 1u);
             placed = code != FLAGGED;
         }
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256) void recheck_scan_batch_kernel(const BatchArgs
 
 }  // namespace
 
-hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_only, hipStream_t stream) {
+hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_only, bool stage_a_done, hipStream_t stream) {
     int64_t blocks = (max_rays + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     if (blocks < 1) blocks = 1;
@@ -466,6 +466,10 @@ hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_onl
     if (exact_only) {
         if (unit) hipLaunchKernelGGL(recheck_exact_kernel<true>, grid, block, 0, stream, a);
         else hipLaunchKernelGGL(recheck_exact_kernel<false>, grid, block, 0, stream, a);
+    } else if (stage_a_done) {
+        const dim3 few((unsigned)(blocks < 512 ? blocks : 512));   // it mostly finds nothing to do
+        if (unit) hipLaunchKernelGGL(recheck_exact_wave_kernel<true>, few, block, 0, stream, a);
+        else hipLaunchKernelGGL(recheck_exact_wave_kernel<false>, few, block, 0, stream, a);
     } else {
         RecheckArgs b = a;
         if (a.defer) {

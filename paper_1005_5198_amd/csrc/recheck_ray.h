@@ -48,6 +48,8 @@ constexpr int CODE_SINGULAR = -2;
 // loads that wait on every memory counter each iteration.
 typedef __attribute__((address_space(1))) const double global_double;
 typedef __attribute__((address_space(1))) const int32_t global_i32;
+// Data that no kernel in flight writes, read at wave-uniform addresses: scalar loads.
+typedef __attribute__((address_space(4))) const double const_double;
 
 // Relaxed device-scope atomic adds through global (not flat) addressing, so a
 // later wait on LDS results does not also wait for these to complete.

@@ -321,11 +321,12 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
             if (pl.defer) r.qleft = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + 3 * pl.n_chunks + c;
             if (pl.far_recheck) {
                 uint32_t *qlive = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + pl.n_chunks + c;
-                e = launch_recheck_far(a, qlive, (a.jc1 - a.jc0) * pl.W, stream);
-                if (e != hipSuccess) return hip_fail(e, "far-field re-check kernel");
                 r.qlive = qlive;
+                e = launch_recheck_far(a, r, qlive, !pl.defer, (a.jc1 - a.jc0) * pl.W, stream);
+                if (e != hipSuccess) return hip_fail(e, "far-field re-check kernel");
             }
-            e = launch_recheck(r, (a.jc1 - a.jc0) * pl.W, (p->flags & RS_EXACT_RECHECK) != 0, stream);
+            e = launch_recheck(r, (a.jc1 - a.jc0) * pl.W, (p->flags & RS_EXACT_RECHECK) != 0,
+                               pl.far_recheck && !pl.defer, stream);
             if (e != hipSuccess) return hip_fail(e, "re-check kernel");
         }
     }

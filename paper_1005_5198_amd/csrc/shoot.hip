@@ -137,7 +137,7 @@ template <int RX, int RY, bool UNIT, bool SHARE_M, bool QUAD, int CQ>
 __device__ __forceinline__ void group_sums(const float4 *tile, int g, int n, const float (&rxl)[RX], const float (&ryl)[RY],
                                            double (&Ax)[RY][RX], double (&Ay)[RY][RX]) {
     static_assert(RY % 2 == 0, "rows are paired for the shared reciprocal");
-    static_assert(RX == 4 * CQ, "column partners are CQ lane columns apart");
+    static_assert(RX % (2 * CQ) == 0, "column partners are CQ lane columns apart");
     float sx[RY][RX], sy[RY][RX];
 #pragma unroll
     for (int r = 0; r < RY; ++r)
@@ -172,9 +172,11 @@ __device__ __forceinline__ void group_sums(const float4 *tile, int g, int n, con
 template <int RX, int RY, int WX, int WY, bool UNIT, int MODE, bool PIX, class Sink>
 __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, ShootSmem &sm, const Sink &sink) {
     constexpr int BLOCK_THREADS = 64 * WX * WY;
-    constexpr int STRIDE_X = LANES_X * WX;
+    // A lane's columns are STRIDE_X apart; with two of them, 16 apart (partners of the
+    // four-ray reciprocal), the block's waves beside and between them.
+    constexpr int STRIDE_X = RX > 2 ? LANES_X * WX : 16;
     constexpr int STRIDE_Y = LANES_Y * WY;
-    static_assert(RX * STRIDE_X == PATCH_X && RY * STRIDE_Y == PATCH_Y, "shape must tile the patch");
+    static_assert(RX * LANES_X * WX == PATCH_X && RY * STRIDE_Y == PATCH_Y, "shape must tile the patch");
     static_assert(BLOCK_THREADS / 64 <= 16, "reduction buffer");
     float4 *tile = sm.tile;
     double *red_bx = sm.red_bx;
@@ -202,7 +204,7 @@ __device__ __forceinline__ void shoot_patch(const ShootArgs &a, int64_t patch, S
 
     // This lane's rays: column i = i_lane + c * STRIDE_X and the rows below, held
     // as FP32 offsets from the patch origin.
-    const int64_t i_lane = ib + wx * LANES_X + lx;
+    const int64_t i_lane = ib + (RX > 2 ? wx : (wx >> 1) * 4 + (wx & 1)) * LANES_X + lx;
     // Rows come in adjacent pairs (2k, 2k+1) per lane, the pairs STRIDE_Y apart:
     // ray r of the lane is on row j_pair + 2 (r / 2) STRIDE_Y + (r % 2).
     const int64_t j_pair = jb + 2 * (wy * LANES_Y + ly);
@@ -489,6 +491,13 @@ hipError_t launch_batch_fill(const BatchArgs &b, void *workspace, int32_t n_maps
     return hipGetLastError();
 }
 
+// At most this many patches (two per CU; in FP32 mode one) are deflected by blocks of
+// twice the waves with half the rays per lane: the default shape would leave SIMDs with
+// one or two waves. 1848 lenses, patches of 64 x 32 rays, default against wide: 256
+// patches 244 against 148 us (mixed) and 210 against 137 us (FP32); 512 patches 270
+// against 267 us and 235 against 249 us.
+constexpr int64_t WIDE_MAX_BLOCKS = 512;
+
 hipError_t launch_shoot(const ShootArgs &a, int mode, int shape, hipStream_t stream) {
     const int64_t nby = (a.jc1 - a.jc0 + PATCH_Y - 1) / PATCH_Y;
     const int64_t blocks = a.nbx * nby;
@@ -498,7 +507,10 @@ hipError_t launch_shoot(const ShootArgs &a, int mode, int shape, hipStream_t str
         case 1: launch_shape<4, 4, 2, 1>(a, mode, grid, stream); break;
         case 2: launch_shape<8, 2, 1, 2>(a, mode, grid, stream); break;
         case 3: launch_shape<8, 4, 1, 1>(a, mode, grid, stream); break;
-        default: launch_shape<4, 2, 2, 2>(a, mode, grid, stream); break;
+        default:
+            if (blocks <= (mode == 0 ? WIDE_MAX_BLOCKS / 2 : WIDE_MAX_BLOCKS)) launch_shape<2, 2, 4, 2>(a, mode, grid, stream);
+            else launch_shape<4, 2, 2, 2>(a, mode, grid, stream);
+            break;
     }
     return hipGetLastError();
 }

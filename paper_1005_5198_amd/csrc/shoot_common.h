@@ -67,13 +67,14 @@ __device__ __forceinline__ double ray_coord(double origin, int64_t idx, double s
 // (The s_setprio after the last reciprocal is also the wait state that its result needs.)
 template <int N>
 __device__ __forceinline__ void rcp_all(float (&R)[N]) {
-    static_assert(N % 2 == 0, "reciprocals come in twos");
+    static_assert(N % 2 == 0 || N == 1, "reciprocals come in twos");
+    if (N == 1) asm volatile("s_setprio 1\n\tv_rcp_f32 %0, %0\n\ts_setprio 0" : "+v"(R[0]));
 #pragma unroll
     for (int i = 0; i + 2 < N; i += 4)
         asm volatile("s_setprio 1\n\tv_rcp_f32 %0, %0\n\tv_rcp_f32 %1, %1\n\tv_rcp_f32 %2, %2\n\tv_rcp_f32 %3, %3\n\t"
                      "s_setprio 0"
                      : "+v"(R[i]), "+v"(R[i + 1]), "+v"(R[i + 2]), "+v"(R[i + 3]));
-    if (N % 4)
+    if (N % 4 == 2)
         asm volatile("s_setprio 1\n\tv_rcp_f32 %0, %0\n\tv_rcp_f32 %1, %1\n\ts_setprio 0"
                      : "+v"(R[N - 2]), "+v"(R[N - 1]));
 }
