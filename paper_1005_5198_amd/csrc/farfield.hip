@@ -621,7 +621,9 @@ struct FarSmem {
     int next;                    // the patch after this one
 };
 
-// Level 2, part 2: the rays. Persistent blocks take patches from a counter. A
+// Level 2, part 2: the rays. Persistent blocks take patches from a counter, `take` of
+// them at a time (an atomic on one address takes 12 ns, 0.43 of the 1.61 ms of the
+// 36000-patch map when each patch took one). A
 // patch's near lenses come from its record, or, when the record could not hold
 // them all, from the candidates with the record kernel's test (beyond NEAR_EXP
 // of them the patch is re-checked whole). Each thread then takes 8 rays: the
@@ -629,7 +631,7 @@ struct FarSmem {
 // bound, and the count in the block's pixel table, which is added to the map
 // (one global atomic per distinct pixel) and cleared after every patch.
 template <bool UNIT, bool PIX>
-__global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArgs a, int64_t patches) {
+__global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArgs a, int64_t patches, int take) {
     __shared__ FarSmem sm;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -637,15 +639,18 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
     if (tid == 0) {
         sm.near_count[0] = 0;
         sm.near_count[1] = 0;
-        sm.next = (int)atomicAdd(a.ff_work, 1u);
+        sm.next = (int)atomicAdd(a.ff_work, (uint32_t)take);
     }
     __syncthreads();
     int64_t patch = sm.next;
+    int left = take;             // patches of this block's share from this one on
     unsigned long long n_in = 0, n_out = 0;
     const int64_t W = a.i1 - a.i0;
     for (int par = 0; patch < patches; par ^= 1) {
         uint32_t next = 0;
-        if (tid == 0) next = atomicAdd(a.ff_work, 1u);   // used after the rays: its latency is hidden
+        // (used after the rays: the atomic's latency is hidden)
+        if (tid == 0) next = left > 1 ? (uint32_t)patch + 1u : atomicAdd(a.ff_work, (uint32_t)take);
+        left = left > 1 ? left - 1 : take;
         const PatchFrame f = patch_frame(a, patch);
         const int64_t ib = f.ib, jb = f.jb;
         const double ox = f.ox, oy = f.oy;
@@ -680,7 +685,10 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
         __syncthreads();
         const double SFAR = sm.rec[2 * FAR_P], far_err = sm.rec[2 * FAR_P + 1], SDEF = sm.rec[2 * FAR_P + 2];
         const int n_near_all = sm.near_count[par];
-        if (tid == 0) sm.near_count[par ^ 1] = 0;   // every thread read it one patch ago
+        if (tid == 0) {
+            sm.near_count[par ^ 1] = 0;   // every thread read it one patch ago
+            sm.table.used[par ^ 1] = 0u;  // and emptied the table
+        }
         const bool all_flagged = n_near_all > NEAR_EXP;
         const int n_near = all_flagged ? 0 : n_near_all;
 
@@ -759,7 +767,7 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
                 if (PIX) {
                     if (valid && code != FLAGGED) a.pix_out[(j - a.j0) * W + (i - a.i0)] = code;
                 } else {
-                    if (code >= 0) table_add(sm.table, a.map, code, 1u);
+                    if (code >= 0) table_add(sm.table, a.map, code, 1u, par);
                 }
                 const uint64_t fl = __ballot(code == FLAGGED);
                 if (fl) queue_append(a, fl, lane, code == FLAGGED, i, j);
@@ -767,7 +775,7 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
         }
         if (tid == 0) sm.next = (int)next;
         __syncthreads();   // every ray of the patch is in the table
-        if (!PIX) table_flush_clear<FAR_THREADS>(sm.table, a.map, tid);
+        if (!PIX) table_flush_clear<FAR_THREADS>(sm.table, a.map, tid, par);
         patch = sm.next;
     }
     if (lane == 0) {
@@ -930,7 +938,9 @@ hipError_t launch_farfield(const ShootArgs &a, hipStream_t stream) {
     auto launch_rays = [&](auto kernel) {
         int64_t blocks = persistent_blocks(kernel, FAR_THREADS, 0);
         if (blocks > patches) blocks = patches;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), block, 0, stream, a, patches);
+        // few enough at a time for the blocks to end together
+        const int take = patches >= 64 * blocks ? 4 : (patches >= 16 * blocks ? 2 : 1);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), block, 0, stream, a, patches, take);
     };
     if (unit) {
         if (pix) launch_rays(farfield_kernel<true, true>);
