@@ -16,6 +16,10 @@ constexpr int FAR_P = 16;                 // expansion order
 constexpr double FAR_RATIO = 4.0;         // lenses beyond FAR_RATIO half-diagonals are expanded
 constexpr int FAR_EXTRA = 4;              // SFAR, TRUNC, SDEF, NFAR
 constexpr int FAR_REC = 2 * FAR_P + FAR_EXTRA;
+// Roundings of one directly summed lens's term, in units of 2^-53 of |e1| + |e2| over r^2
+// (the differences, r^2, the reciprocal, shared by four rays in the ray kernel: four
+// products more, the mass), rounded up.
+constexpr double NEAR_ROUNDINGS = 16.0;
 static_assert(FAR_REC == FF_REC_DOUBLES, "super-patch record size");
 
 __device__ __forceinline__ double rcp64(double r2) {
@@ -66,7 +70,7 @@ __device__ __forceinline__ int far_decide(const ShootArgs &a, double x1, double 
     const double y2 = a.c2 * x2 - a2;
     const double u = (y1 - a.tx0) * a.inv_pixw;
     const double v = (y2 - a.ty0) * a.inv_pixh;
-    const double near_err = ((double)n_near + 10.0) * U64 * 1.001 * snear + (double)n_near * U64 * 1.34 * SFAR;
+    const double near_err = ((double)n_near + NEAR_ROUNDINGS) * U64 * 1.001 * snear + (double)n_near * U64 * 1.34 * SFAR;
     const double def_sum = kN * (snear + SDEF);
     const double eu = far_err + near_err + def_sum + 16.0 * U64 * (fabs(a.c1 * x1) + fabs(a1) + fabs(a.tx0));
     const double ev = far_err + near_err + def_sum + 16.0 * U64 * (fabs(a.c2 * x2) + fabs(a2) + fabs(a.ty0));

@@ -613,6 +613,49 @@ __device__ __forceinline__ void queue_append(const ShootArgs &a, uint64_t fl, in
     }
 }
 
+// A patch's part of the pixel decision, the terms of far_decide that do not depend on the
+// ray: the bound in pixels is e + s snear + g |c x| + g |a| on each axis.
+struct PatchBound {
+    double eu, ev, su, sv, gu, gv;
+};
+
+__device__ __forceinline__ PatchBound patch_bound(const ShootArgs &a, double far_err, double SFAR, double SDEF, int n_near,
+                                                  bool all_flagged) {
+    constexpr double U64 = 1.1102230246251565e-16;  // 2^-53
+    const double kN = ((double)a.n_lens + 10.0) * U64 * 1.001;
+    const double e = all_flagged ? __builtin_inf() : far_err + (double)n_near * U64 * 1.34 * SFAR + kN * SDEF;
+    const double s = ((double)n_near + NEAR_ROUNDINGS) * U64 * 1.001 + kN;
+    const double wu = 1.0011 * a.inv_pixw, wv = 1.0011 * a.inv_pixh;   // (0.0001 for the terms' own rounding)
+    PatchBound b;
+    b.gu = 16.0 * U64 * wu;
+    b.gv = 16.0 * U64 * wv;
+    b.eu = e * wu + b.gu * fabs(a.tx0);
+    b.ev = e * wv + b.gv * fabs(a.ty0);
+    b.su = s * wu;
+    b.sv = s * wv;
+    return b;
+}
+
+// The pixel decision of far_decide with the patch's and the column's or row's terms taken
+// out: (cu, cv) = ((c1 x1 - tx0) / pixel, (c2 x2 - ty0) / pixel), (eu, ev) the bound's terms
+// but those in a1, a2 and snear. Anything not finite compares false: FLAGGED.
+__device__ __forceinline__ int patch_decide(const ShootArgs &a, const PatchBound &b, double cu, double cv, double eu,
+                                            double ev, double a1, double a2, double snear) {
+    const double u = __builtin_fma(-a1, a.inv_pixw, cu);
+    const double v = __builtin_fma(-a2, a.inv_pixh, cv);
+    const double Mu = __builtin_fma(b.su, snear, __builtin_fma(b.gu, fabs(a1), eu));
+    const double Mv = __builtin_fma(b.sv, snear, __builtin_fma(b.gv, fabs(a2), ev));
+    const double fu = floor(u), fv = floor(v);
+    const double ru = u - fu, rv = v - fv;   // exact
+    const int iu = (int)fu, iv = (int)fv;    // (out of int's range: its end, outside the map)
+    if ((uint32_t)iu < (uint32_t)a.npx && (uint32_t)iv < (uint32_t)a.npy && ru > Mu && ru + Mu < 1.0 && rv > Mv &&
+        rv + Mv < 1.0)
+        return iv * (int)a.npx + iu;
+    const bool out_u = (u < -Mu) || (u - (double)a.npx > Mu);
+    const bool out_v = (v < -Mv) || (v - (double)a.npy > Mv);
+    return (out_u || out_v) && isfinite(Mu) && isfinite(Mv) && isfinite(u) && isfinite(v) ? OUT : FLAGGED;
+}
+
 struct FarSmem {
     PixelTable table;            // the patch's counts per pixel (map mode)
     double near_x[NEAR_EXP], near_y[NEAR_EXP], near_m[NEAR_EXP];
@@ -704,6 +747,18 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
         for (int c = 0; c < 2; ++c) X1[c] = ray_coord(a.sx0, col(c), a.spx);
 #pragma unroll
         for (int rr = 0; rr < FAR_ROWS / 2; ++rr) X2[rr] = ray_coord(a.sy0, row(rr), a.spy);
+        const PatchBound bound = patch_bound(a, far_err, SFAR, SDEF, n_near, all_flagged);
+        double cu[2], eu[2], cv[FAR_ROWS / 2], ev[FAR_ROWS / 2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            cu[c] = (a.c1 * X1[c] - a.tx0) * a.inv_pixw;
+            eu[c] = __builtin_fma(bound.gu, fabs(a.c1 * X1[c]), bound.eu);
+        }
+#pragma unroll
+        for (int rr = 0; rr < FAR_ROWS / 2; ++rr) {
+            cv[rr] = (a.c2 * X2[rr] - a.ty0) * a.inv_pixh;
+            ev[rr] = __builtin_fma(bound.gv, fabs(a.c2 * X2[rr]), bound.ev);
+        }
         // The thread's rays in two passes of RPASS: per pass, (1) the expansion of each
         // ray (independent Horner chains), (2) the near lenses, each read from LDS once
         // per pass and added onto each ray's far part in list order, (3) the pixel
@@ -738,19 +793,37 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
             double SN[RPASS];
 #pragma unroll
             for (int k = 0; k < RPASS; ++k) SN[k] = 0.0;
-            uint32_t tiny = 0u;
+            bool tiny = false;
             for (int q = 0; q < n_near; ++q) {
-                const double X = sm.near_x[q], Y = sm.near_y[q], M = sm.near_m[q];
+                const double X = sm.near_x[q], Y = sm.near_y[q];
+                double e1[2], e2[2], r2[RPASS], f[RPASS];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    e1[c] = X1[c] - X;
+                    e2[c] = X2[2 * pass + c] - Y;
+                }
+                // ray k: column k % 2, row k / 2; one reciprocal for the four (v_rcp_f64 takes
+                // four times an FMA's issue, and its two Newton steps four FMAs)
+#pragma unroll
+                for (int k = 0; k < RPASS; ++k) r2[k] = __builtin_fma(e1[k & 1], e1[k & 1], e2[k >> 1] * e2[k >> 1]);
+                const double pab = r2[0] * r2[1], pcd = r2[2] * r2[3], P = pab * pcd;
+                tiny |= !(P > 1e-290);
+                const double R = rcp64(P);
+                double qab = R * pcd, qcd = R * pab;
+                if (!UNIT) {
+                    const double M = sm.near_m[q];
+                    qab = M * qab;
+                    qcd = M * qcd;
+                }
+                f[0] = r2[1] * qab;
+                f[1] = r2[0] * qab;
+                f[2] = r2[3] * qcd;
+                f[3] = r2[2] * qcd;
 #pragma unroll
                 for (int k = 0; k < RPASS; ++k) {
-                    const int r = pass * RPASS + k;
-                    const double e1 = X1[r & 1] - X, e2 = X2[r >> 1] - Y;
-                    const double r2 = __builtin_fma(e1, e1, e2 * e2);
-                    if (!(r2 > 1e-200)) tiny |= 1u << k;
-                    const double f = M * rcp64(r2);
-                    A1[k] = __builtin_fma(f, e1, A1[k]);
-                    A2[k] = __builtin_fma(f, e2, A2[k]);
-                    SN[k] = __builtin_fma(fabs(e1) + fabs(e2), fabs(f), SN[k]);
+                    A1[k] = __builtin_fma(f[k], e1[k & 1], A1[k]);
+                    A2[k] = __builtin_fma(f[k], e2[k >> 1], A2[k]);
+                    SN[k] = __builtin_fma(fabs(e1[k & 1]) + fabs(e2[k >> 1]), UNIT ? f[k] : fabs(f[k]), SN[k]);
                 }
             }
 #pragma unroll
@@ -758,8 +831,8 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
                 const int r = pass * RPASS + k;
                 const int64_t i = col(r & 1), j = row(r >> 1);
                 const bool valid = (i < a.i1) && (j < a.jc1);
-                int code = far_decide(a, X1[r & 1], X2[r >> 1], A1[k], A2[k], far_err, SFAR, SDEF, SN[k], n_near,
-                                      !((tiny >> k) & 1u) && !all_flagged);
+                int code = patch_decide(a, bound, cu[r & 1], cv[r >> 1], eu[r & 1], ev[r >> 1], A1[k], A2[k], SN[k]);
+                if (tiny) code = FLAGGED;
                 if (!valid) code = INT32_MIN;
 
                 n_in += __builtin_popcountll(__ballot(code >= 0));
