@@ -41,6 +41,60 @@ struct BinomTable {
 };
 __constant__ constexpr BinomTable BINOM_TABLE{};
 #define BINOM BINOM_TABLE.v
+// Steps of a reduction over the wave's lanes that leaves each lane with part of the
+// values: of its N values a lane keeps the first (N + 1) / 2 if its bit BIT is 0, the
+// others if it is 1, and adds its partner's partial sums of them. at and end follow
+// which values of the whole list a lane holds.
+template <int BIT, int N>
+__device__ __forceinline__ void scatter_range(int lane, int &at, int &end) {
+    constexpr int H = (N + 1) / 2;
+    if (lane & BIT) at += H;
+    else if (end > at + H) end = at + H;
+}
+
+// BIT 32 or 16: v_permlane32_swap / v_permlane16_swap exchange the upper lanes (odd
+// rows) of one register with the lower lanes (even rows) of another.
+template <int BIT, int N, int M>
+__device__ __forceinline__ void scatter_swap(double (&v)[M], int lane, int &at, int &end) {
+    static_assert(N % 2 == 0, "halves");
+    constexpr int H = N / 2;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        const uint64_t a = (uint64_t)__double_as_longlong(v[k]), b = (uint64_t)__double_as_longlong(v[k + H]);
+        uint64_t x, y;
+        if constexpr (BIT == 32) {
+            const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+            x = ((uint64_t)hi[0] << 32) | lo[0];
+            y = ((uint64_t)hi[1] << 32) | lo[1];
+        } else {
+            const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+            const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+            x = ((uint64_t)hi[0] << 32) | lo[0];
+            y = ((uint64_t)hi[1] << 32) | lo[1];
+        }
+        v[k] = __longlong_as_double((long long)x) + __longlong_as_double((long long)y);
+    }
+    scatter_range<BIT, N>(lane, at, end);
+}
+
+// Smaller BIT: the partner (the lane that differs in BIT, and maybe in lower bits) by DPP.
+template <int BIT, int N, int CTRL, int M>
+__device__ __forceinline__ void scatter_dpp(double (&v)[M], int lane, int &at, int &end) {
+    constexpr int H = (N + 1) / 2;
+    const bool up = (lane & BIT) != 0;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        const double lo = v[k], hi = k + H < N ? v[k + H] : 0.0;
+        const double keep = up ? hi : lo, send = up ? lo : hi;
+        const uint64_t w = (uint64_t)__double_as_longlong(send);
+        const uint32_t w0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)w, CTRL, 0xf, 0xf, false);
+        const uint32_t w1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(w >> 32), CTRL, 0xf, 0xf, false);
+        v[k] = keep + __longlong_as_double((long long)(((uint64_t)w1 << 32) | w0));
+    }
+    scatter_range<BIT, N>(lane, at, end);
+}
+
 // One lens's contribution to an expansion about (ox, oy) with half-diagonal h
 // (the lens is at least FAR_RATIO h away): the powers m t^(n+1) and the bound
 // terms m/|d|, m/|d| rho^P / (1 - rho) and sqrt(2) m / (|d| - h).
@@ -83,37 +137,35 @@ struct FarAcc {
         sdef += 1.4142135623730951 * s * g;
         nfar += 1.0;
     }
-    // Sum over the wave's lanes (butterfly): every lane ends with the totals.
-    __device__ void butterfly() {
+    // The wave's totals into tot[FAR_REC] (shared): a reduction that scatters as it goes
+    // (each step halves the number of values a lane holds), 38 exchanges of a double in all
+    // and none of them through LDS. (A butterfly of the 36 values takes 216, through LDS:
+    // a third of the patch record kernel's time.)
+    __device__ __forceinline__ void wave_totals(double *tot) {
+        double v[FAR_REC];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-            for (int n = 0; n < FAR_P; ++n) {
-                c1[n] += __shfl_xor(c1[n], off);
-                c2[n] += __shfl_xor(c2[n], off);
-            }
-            sfar += __shfl_xor(sfar, off);
-            trunc += __shfl_xor(trunc, off);
-            sdef += __shfl_xor(sdef, off);
-            nfar += __shfl_xor(nfar, off);
+        for (int n = 0; n < FAR_P; ++n) {
+            v[n] = c1[n];
+            v[FAR_P + n] = c2[n];
         }
+        v[2 * FAR_P] = sfar;
+        v[2 * FAR_P + 1] = trunc;
+        v[2 * FAR_P + 2] = sdef;
+        v[2 * FAR_P + 3] = nfar;
+        const int lane = threadIdx.x & 63;
+        int at = 0, end = FAR_REC;   // this lane's values are at .. end - 1 of the 36
+        scatter_swap<32, 36>(v, lane, at, end);
+        scatter_swap<16, 18>(v, lane, at, end);
+        scatter_dpp<8, 9, 0x128>(v, lane, at, end);   // row_ror:8
+        scatter_dpp<4, 5, 0x141>(v, lane, at, end);   // row_half_mirror: the lane's three low bits flipped
+        scatter_dpp<2, 3, 0x4e>(v, lane, at, end);    // quad_perm [2,3,0,1]
+        scatter_dpp<1, 2, 0xb1>(v, lane, at, end);    // quad_perm [1,0,3,2]
+        if (at < end) tot[at] = v[0];
     }
-    // Block sum into out[FAR_REC] (shared); lanes by butterfly, then waves in index order.
+    // Block sum into out[FAR_REC] (shared); lanes first, then waves in index order.
     template <int THREADS = FAR_THREADS>
     __device__ void reduce(double (*part)[FAR_REC], double *out) {
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        butterfly();
-        if (lane == 0) {
-#pragma unroll
-            for (int n = 0; n < FAR_P; ++n) {
-                part[wave][n] = c1[n];
-                part[wave][FAR_P + n] = c2[n];
-            }
-            part[wave][2 * FAR_P] = sfar;
-            part[wave][2 * FAR_P + 1] = trunc;
-            part[wave][2 * FAR_P + 2] = sdef;
-            part[wave][2 * FAR_P + 3] = nfar;
-        }
+        wave_totals(part[threadIdx.x >> 6]);
         __syncthreads();
         if (threadIdx.x < FAR_REC) {
             double v = 0.0;
@@ -526,6 +578,8 @@ __device__ __forceinline__ bool candidate(const ShootArgs &a, const Candidates &
 template <bool UNIT>
 __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const ShootArgs a, int64_t patches) {
     constexpr double U64 = 1.1102230246251565e-16;  // 2^-53
+    __shared__ double totals[FAR_THREADS / 64][FAR_REC];
+    double *const own = totals[threadIdx.x >> 6];   // the expansion of the patch's own lenses
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.ff_work = 0u;
     const int lane = threadIdx.x & 63;
     const int64_t patch = (int64_t)blockIdx.x * (FAR_THREADS / 64) + (threadIdx.x >> 6);
@@ -561,18 +615,11 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const Shoot
         }
         n_near += __builtin_popcountll(nb);
     }
-    acc.butterfly();   // every lane now holds the wave's sums
+    acc.wave_totals(own);
+    wave_lds_fence();
     const global_double *sc = (const global_double *)(a.ff_super + f.sp * (int64_t)FAR_REC);
     if (lane < FAR_P) {
         const int mm = lane;
-        double p1 = 0.0, p2 = 0.0;
-#pragma unroll
-        for (int n = 0; n < FAR_P; ++n) {
-            if (n == mm) {
-                p1 = acc.c1[n];
-                p2 = acc.c2[n];
-            }
-        }
         const double e1 = c.cx - f.ox, e2 = c.cy - f.oy;
         double s1 = 0.0, s2 = 0.0;
         double g1 = 1.0, g2 = 0.0;   // e^(n-m)
@@ -585,15 +632,16 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const Shoot
             g1 = q1;
             g2 = q2;
         }
-        rec[mm] = s1 + p1;
-        rec[FAR_P + mm] = s2 + p2;
+        rec[mm] = s1 + own[mm];
+        rec[FAR_P + mm] = s2 + own[FAR_P + mm];
     } else if (lane == FAR_P) {
         const double SFAR_S = sc[2 * FAR_P], TRUNC_S = sc[2 * FAR_P + 1], SDEF_S = sc[2 * FAR_P + 2];
         const double NFAR_S = sc[2 * FAR_P + 3];
-        rec[2 * FAR_P] = SFAR_S + acc.sfar;
-        rec[2 * FAR_P + 1] = TRUNC_S + acc.trunc + (NFAR_S + 24.0 * FAR_P + 64.0) * U64 * 1.34 * SFAR_S +
-                             (acc.nfar + 16.0 * FAR_P + 64.0) * U64 * 1.34 * acc.sfar;
-        rec[2 * FAR_P + 2] = SDEF_S + acc.sdef;
+        const double sfar = own[2 * FAR_P], nfar = own[2 * FAR_P + 3];
+        rec[2 * FAR_P] = SFAR_S + sfar;
+        rec[2 * FAR_P + 1] = TRUNC_S + own[2 * FAR_P + 1] + (NFAR_S + 24.0 * FAR_P + 64.0) * U64 * 1.34 * SFAR_S +
+                             (nfar + 16.0 * FAR_P + 64.0) * U64 * 1.34 * sfar;
+        rec[2 * FAR_P + 2] = SDEF_S + own[2 * FAR_P + 2];
         rec[2 * FAR_P + 3] = (double)n_near;
     } else if (lane <= FAR_P + FF_PATCH_HEAD - (2 * FAR_P + 4)) {
         rec[2 * FAR_P + 4 + (lane - FAR_P - 1)] = 0.0;   // the spare doubles
