@@ -41,6 +41,18 @@ struct BinomTable {
 };
 __constant__ constexpr BinomTable BINOM_TABLE{};
 #define BINOM BINOM_TABLE.v
+// n! and 1 / n! for n < FAR_P (n! below 2^41, exact in FP64).
+struct FactorialTable {
+    double f[FAR_P], inv[FAR_P];
+    constexpr FactorialTable() : f(), inv() {
+        f[0] = inv[0] = 1.0;
+        for (int n = 1; n < FAR_P; ++n) {
+            f[n] = f[n - 1] * n;
+            inv[n] = 1.0 / f[n];
+        }
+    }
+};
+__constant__ constexpr FactorialTable FACTORIAL{};
 // Steps of a reduction over the wave's lanes that leaves each lane with part of the
 // values: of its N values a lane keeps the first (N + 1) / 2 if its bit BIT is 0, the
 // others if it is 1, and adds its partner's partial sums of them. at and end follow
@@ -632,8 +644,9 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const Shoot
             g1 = q1;
             g2 = q2;
         }
-        rec[mm] = s1 + own[mm];
-        rec[FAR_P + mm] = s2 + own[FAR_P + mm];
+        // (n! T_n, real and imaginary part: the ray kernel's form of the series)
+        rec[2 * mm] = FACTORIAL.f[mm] * (s1 + own[mm]);
+        rec[2 * mm + 1] = FACTORIAL.f[mm] * (s2 + own[FAR_P + mm]);
     } else if (lane == FAR_P) {
         const double SFAR_S = sc[2 * FAR_P], TRUNC_S = sc[2 * FAR_P + 1], SDEF_S = sc[2 * FAR_P + 2];
         const double NFAR_S = sc[2 * FAR_P + 3];
@@ -646,6 +659,49 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const Shoot
     } else if (lane <= FAR_P + FF_PATCH_HEAD - (2 * FAR_P + 4)) {
         rec[2 * FAR_P + 4 + (lane - FAR_P - 1)] = 0.0;   // the spare doubles
     }
+}
+
+// A patch's part of the pixel decision: the terms of far_decide that do not depend on the
+// ray, in pixels. The bound on an axis is e + s snear (|x| on the patch and the size of the
+// deflection, at most 1.35 SFAR + snear, are bounded for the whole patch), and the position
+// is x c + o - a w.
+struct PatchBound {
+    double eu, ev, su, sv;
+};
+
+__device__ __forceinline__ PatchBound patch_bound(const ShootArgs &a, const PatchFrame &f, double far_err, double SFAR,
+                                                  double SDEF, int n_near, bool all_flagged) {
+    constexpr double U64 = 1.1102230246251565e-16;  // 2^-53
+    const double kN = ((double)a.n_lens + 10.0) * U64 * 1.001;
+    const double e = all_flagged ? __builtin_inf()
+                                 : far_err + ((double)n_near * 1.34 + 16.0 * 1.35) * U64 * SFAR + kN * SDEF;
+    const double s = ((double)n_near + NEAR_ROUNDINGS) * U64 * 1.001 + kN + 16.0 * U64;
+    const double wu = 1.0011 * a.inv_pixw, wv = 1.0011 * a.inv_pixh;   // (0.0001 for the terms' own rounding)
+    PatchBound b;
+    b.eu = wu * (e + 16.0 * U64 * (fabs(a.c1) * (fabs(f.ox) + f.h) + fabs(a.tx0)));
+    b.ev = wv * (e + 16.0 * U64 * (fabs(a.c2) * (fabs(f.oy) + f.h) + fabs(a.ty0)));
+    b.su = wu * s;
+    b.sv = wv * s;
+    return b;
+}
+
+// The pixel decision of far_decide for the ray at (u, v) pixels; a position or bound that
+// is not finite compares false: FLAGGED (a position that overflowed within its bound is
+// out of the map in the definition too).
+__device__ __forceinline__ int patch_decide(const ShootArgs &a, const PatchBound &b, double u, double v, double snear) {
+    const double Mu = __builtin_fma(b.su, snear, b.eu);
+    const double Mv = __builtin_fma(b.sv, snear, b.ev);
+    const double fu = floor(u), fv = floor(v);
+    const double ru = u - fu, rv = v - fv;   // exact
+    const int iu = (int)fu, iv = (int)fv;    // (out of int's range: its end, outside the map)
+    const bool in = (uint32_t)iu < (uint32_t)a.npx && (uint32_t)iv < (uint32_t)a.npy && ru > Mu && ru + Mu < 1.0 &&
+                    rv > Mv && rv + Mv < 1.0;
+    int code = (int)((uint32_t)iv * (uint32_t)a.npx + (uint32_t)iu);
+    if (__ballot(!in)) {
+        const bool out = u < -Mu || u - (double)a.npx > Mu || v < -Mv || v - (double)a.npy > Mv;
+        code = in ? code : (out ? OUT : FLAGGED);
+    }
+    return code;
 }
 
 // A wave's rays to re-check (lanes fl) appended to the launch's queue, which holds every
@@ -661,225 +717,214 @@ __device__ __forceinline__ void queue_append(const ShootArgs &a, uint64_t fl, in
     }
 }
 
-// A patch's part of the pixel decision, the terms of far_decide that do not depend on the
-// ray: the bound in pixels is e + s snear + g |c x| + g |a| on each axis.
-struct PatchBound {
-    double eu, ev, su, sv, gu, gv;
-};
-
-__device__ __forceinline__ PatchBound patch_bound(const ShootArgs &a, double far_err, double SFAR, double SDEF, int n_near,
-                                                  bool all_flagged) {
-    constexpr double U64 = 1.1102230246251565e-16;  // 2^-53
-    const double kN = ((double)a.n_lens + 10.0) * U64 * 1.001;
-    const double e = all_flagged ? __builtin_inf() : far_err + (double)n_near * U64 * 1.34 * SFAR + kN * SDEF;
-    const double s = ((double)n_near + NEAR_ROUNDINGS) * U64 * 1.001 + kN;
-    const double wu = 1.0011 * a.inv_pixw, wv = 1.0011 * a.inv_pixh;   // (0.0001 for the terms' own rounding)
-    PatchBound b;
-    b.gu = 16.0 * U64 * wu;
-    b.gv = 16.0 * U64 * wv;
-    b.eu = e * wu + b.gu * fabs(a.tx0);
-    b.ev = e * wv + b.gv * fabs(a.ty0);
-    b.su = s * wu;
-    b.sv = s * wv;
-    return b;
-}
-
-// The pixel decision of far_decide with the patch's and the column's or row's terms taken
-// out: (cu, cv) = ((c1 x1 - tx0) / pixel, (c2 x2 - ty0) / pixel), (eu, ev) the bound's terms
-// but those in a1, a2 and snear. Anything not finite compares false: FLAGGED.
-__device__ __forceinline__ int patch_decide(const ShootArgs &a, const PatchBound &b, double cu, double cv, double eu,
-                                            double ev, double a1, double a2, double snear) {
-    const double u = __builtin_fma(-a1, a.inv_pixw, cu);
-    const double v = __builtin_fma(-a2, a.inv_pixh, cv);
-    const double Mu = __builtin_fma(b.su, snear, __builtin_fma(b.gu, fabs(a1), eu));
-    const double Mv = __builtin_fma(b.sv, snear, __builtin_fma(b.gv, fabs(a2), ev));
-    const double fu = floor(u), fv = floor(v);
-    const double ru = u - fu, rv = v - fv;   // exact
-    const int iu = (int)fu, iv = (int)fv;    // (out of int's range: its end, outside the map)
-    if ((uint32_t)iu < (uint32_t)a.npx && (uint32_t)iv < (uint32_t)a.npy && ru > Mu && ru + Mu < 1.0 && rv > Mv &&
-        rv + Mv < 1.0)
-        return iv * (int)a.npx + iu;
-    const bool out_u = (u < -Mu) || (u - (double)a.npx > Mu);
-    const bool out_v = (v < -Mv) || (v - (double)a.npy > Mv);
-    return (out_u || out_v) && isfinite(Mu) && isfinite(Mv) && isfinite(u) && isfinite(v) ? OUT : FLAGGED;
-}
-
+constexpr int ROW_STRIDE = FAR_P + 1;   // (rows of a wave start on different LDS banks)
 struct FarSmem {
-    PixelTable table;            // the patch's counts per pixel (map mode)
-    double near_x[NEAR_EXP], near_y[NEAR_EXP], near_m[NEAR_EXP];
-    double rec[FF_PATCH_HEAD];
-    int near_count[2];           // by patch parity: one is filled while the other is cleared
-    int next;                    // the patch after this one
+    PixelTable table;                    // the patch's counts per pixel (map mode)
+    // this patch's record and the next one's: the series, followed by zeros, and the rest
+    double2 series[2][2 * FAR_P - 1];
+    double rest[2][FF_PATCH_DOUBLES - 2 * FAR_P];
+    double2 row[FAR_THREADS / 64][8][ROW_STRIDE];   // per wave: its 8 rows' series in the column offset
+    double near_x[NEAR_EXP], near_y[NEAR_EXP], near_m[NEAR_EXP];   // near lenses a record could not hold
+    int near_count;
+    int next;                            // the patch after the next one
 };
+static_assert(FAR_THREADS / 64 * 8 == PATCH_Y && FF_PATCH_DOUBLES <= FAR_THREADS, "a wave takes eight rows");
 
 // Level 2, part 2: the rays. Persistent blocks take patches from a counter, `take` of
 // them at a time (an atomic on one address takes 12 ns, 0.43 of the 1.61 ms of the
-// 36000-patch map when each patch took one). A
-// patch's near lenses come from its record, or, when the record could not hold
-// them all, from the candidates with the record kernel's test (beyond NEAR_EXP
-// of them the patch is re-checked whole). Each thread then takes 8 rays: the
-// series (Horner in v), the near lenses directly, the pixel decision against the
-// bound, and the count in the block's pixel table, which is added to the map
-// (one global atomic per distinct pixel) and cleared after every patch.
+// 36000-patch map when each patch took one). The next patch's record is loaded while
+// this one's rays are evaluated. A patch's near lenses come from its record, or, when the
+// record could not hold them all, from the candidates with the record kernel's test
+// (beyond NEAR_EXP of them the patch is re-checked whole).
+//
+// A lane takes 8 rays of one row (a wave eight rows, 8 x 8 rays at a time). The series
+// in w' = z0 - z = p + i q, p the column's offset and q the row's, is re-centred on the
+// row once for its 64 rays,
+//   sum_n T_n (p + i q)^n = sum_m p^m / m! sum_k (n! T_n) (i q)^k / k!,  n = m + k,
+// two values of m by each of the row's 8 lanes, so that a ray costs 30 FMAs (a real
+// variable) instead of 60. Then the near lenses directly, four rays sharing a reciprocal,
+// the pixel decision against the bound, and the count in the block's pixel table, which is
+// added to the map and cleared after every patch. Rounding of the evaluation: every
+// product of |p| and |q| sums to at most sum |T_n| (|p| + |q|)^n <= 1.55 sum m/|d|, with
+// at most 95 roundings (1 for n!, 3 k for q^k / k!, 16 additions, 2 for 1 / m!, 2 m + 1 in
+// p): within the record's terms, which allow 448 (super-patch and above) and 320 units of
+// 1.34 sum m/|d| where the coefficients take at most 245 and 143.
 template <bool UNIT, bool PIX>
 __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArgs a, int64_t patches, int take) {
     __shared__ FarSmem sm;
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    const int lane = tid & 63, wave = tid >> 6;
     if (!PIX) table_clear<FAR_THREADS>(sm.table, tid);
+    // thread 0's share of the counter: patches share .. share + left - 1 are this block's
+    uint32_t share = 0;
+    int left = 0;
+    auto fetch = [&]() {
+        if (left == 0) {
+            share = atomicAdd(a.ff_work, (uint32_t)take);
+            left = take;
+        }
+        --left;
+        return (int)share++;
+    };
     if (tid == 0) {
-        sm.near_count[0] = 0;
-        sm.near_count[1] = 0;
-        sm.next = (int)atomicAdd(a.ff_work, (uint32_t)take);
+        sm.near_count = fetch();
+        sm.next = fetch();
     }
     __syncthreads();
-    int64_t patch = sm.next;
-    int left = take;             // patches of this block's share from this one on
-    unsigned long long n_in = 0, n_out = 0;
+    int64_t patch = sm.near_count, next = sm.next;
+    __syncthreads();
+    if (tid == 0) sm.near_count = 0;
+    auto hold = [&](int par, double v) {   // a record's double tid into its place
+        if (tid < 2 * FAR_P) reinterpret_cast<double *>(sm.series[par])[tid] = v;
+        else if (tid < FF_PATCH_DOUBLES) sm.rest[par][tid - 2 * FAR_P] = v;
+    };
+    if (tid < 2 * (FAR_P - 1))
+        for (int par = 0; par < 2; ++par) reinterpret_cast<double *>(sm.series[par])[2 * FAR_P + tid] = 0.0;
+    if (patch < patches && tid < FF_PATCH_DOUBLES)
+        hold(0, ((const global_double *)a.ff_patch)[patch * FF_PATCH_DOUBLES + tid]);
+    const int m0 = lane & 7, m1 = 15 - m0;   // the coefficients this lane makes for its row
+    const double inv0 = FACTORIAL.inv[m0], inv1 = FACTORIAL.inv[m1];
+    double2 *const my_row = sm.row[wave][lane >> 3];
+    const double oc1 = a.c1 * a.inv_pixw, oc2 = a.c2 * a.inv_pixh;   // position: x c + o - a w
+    const double ou = -a.tx0 * a.inv_pixw, ov = -a.ty0 * a.inv_pixh;
+    uint32_t n_in = 0, n_out = 0;   // (of a block's patches: below 2^32)
     const int64_t W = a.i1 - a.i0;
+    __syncthreads();
     for (int par = 0; patch < patches; par ^= 1) {
-        uint32_t next = 0;
-        // (used after the rays: the atomic's latency is hidden)
-        if (tid == 0) next = left > 1 ? (uint32_t)patch + 1u : atomicAdd(a.ff_work, (uint32_t)take);
-        left = left > 1 ? left - 1 : take;
+        double ahead = 0.0;   // the next patch's record, one double per thread
+        if (next < patches && tid < FF_PATCH_DOUBLES)
+            ahead = ((const global_double *)a.ff_patch)[next * FF_PATCH_DOUBLES + tid];
+        int after = 0;
+        if (tid == 0) after = fetch();   // used after the rays: the atomic's latency is hidden
         const PatchFrame f = patch_frame(a, patch);
-        const int64_t ib = f.ib, jb = f.jb;
-        const double ox = f.ox, oy = f.oy;
-        const global_double *R = (const global_double *)(a.ff_patch + patch * (int64_t)FF_PATCH_DOUBLES);
-        if (tid < FF_PATCH_HEAD) sm.rec[tid] = R[tid];
-        const int stored = (int)R[2 * FAR_P + 3];
-        if (stored <= FF_PATCH_NEAR) {
-            if (tid < stored) {
-                sm.near_x[tid] = R[FF_PATCH_HEAD + tid];
-                sm.near_y[tid] = R[FF_PATCH_HEAD + FF_PATCH_NEAR + tid];
-                sm.near_m[tid] = R[FF_PATCH_HEAD + 2 * FF_PATCH_NEAR + tid];
-            }
-            if (tid == 0) sm.near_count[par] = stored;
-        } else {
+        const double *const rest = sm.rest[par];
+        const int stored = (int)rest[3];
+        const double *near_x = rest + FF_PATCH_HEAD - 2 * FAR_P, *near_y = near_x + FF_PATCH_NEAR, *near_m = near_y + FF_PATCH_NEAR;
+        int n_near = stored;
+        if (stored > FF_PATCH_NEAR) {
             const Candidates c = candidates(a, f.sp);
             for (int64_t q = tid; q < c.n; q += FAR_THREADS) {
                 int64_t k;
                 double X, Y;
                 if (!candidate(a, c, q, k, X, Y)) continue;
-                const double d1 = ox - X, d2 = oy - Y;
+                const double d1 = f.ox - X, d2 = f.oy - Y;
                 const double r2 = d1 * d1 + d2 * d2;
                 if (r2 >= f.near_r2) continue;   // in the patch's expansion
                 const double m = (UNIT || a.lens_m == nullptr) ? 1.0 : ((global_double *)a.lens_m)[k];
-                const int j = atomicAdd(&sm.near_count[par], 1);
+                const int j = atomicAdd(&sm.near_count, 1);
                 if (j < NEAR_EXP) {
                     sm.near_x[j] = X;
                     sm.near_y[j] = Y;
                     sm.near_m[j] = m;
                 }
             }
+            __syncthreads();
+            n_near = sm.near_count;
+            __syncthreads();
+            if (tid == 0) sm.near_count = 0;   // (the next patch's first use follows two barriers)
+            near_x = sm.near_x;
+            near_y = sm.near_y;
+            near_m = sm.near_m;
         }
-        __syncthreads();
-        const double SFAR = sm.rec[2 * FAR_P], far_err = sm.rec[2 * FAR_P + 1], SDEF = sm.rec[2 * FAR_P + 2];
-        const int n_near_all = sm.near_count[par];
-        if (tid == 0) {
-            sm.near_count[par ^ 1] = 0;   // every thread read it one patch ago
-            sm.table.used[par ^ 1] = 0u;  // and emptied the table
-        }
-        const bool all_flagged = n_near_all > NEAR_EXP;
-        const int n_near = all_flagged ? 0 : n_near_all;
+        const bool all_flagged = n_near > NEAR_EXP;
+        if (all_flagged) n_near = 0;
+        const PatchBound bound =
+            patch_bound(a, f, rest[1], rest[0], rest[2], n_near, all_flagged);
 
-        // A wave takes 8 x 8-ray blocks of the patch (block wave + 4 r, r < 8), so the
-        // rays of one wave land on few pixels. Ray r of this thread has column
-        // ib + 8 ((wave + 4 r) % 8) + lane % 8 (two values, r even or odd) and row
-        // jb + 8 (r / 2) + lane / 8 (four values).
-        const int wave = tid >> 6;
-        auto col = [&](int c) { return ib + 8 * ((wave + 4 * c) % (PATCH_X / 8)) + (lane & 7); };
-        auto row = [&](int rr) { return jb + 8 * rr + (lane >> 3); };
-        double X1[2], X2[FAR_ROWS / 2];
+        // This lane's row, and two coefficients of its series.
+        const int64_t j = f.jb + 8 * wave + (lane >> 3);
+        const double x2 = ray_coord(a.sy0, j, a.spy);
+        const double q = f.oy - x2;
+        {
+            const double2 *const T0 = sm.series[par] + m0, *const T1 = sm.series[par] + m1;   // n! T_n, n = m + k
+            double2 r0 = make_double2(0.0, 0.0), r1 = r0;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) X1[c] = ray_coord(a.sx0, col(c), a.spx);
-#pragma unroll
-        for (int rr = 0; rr < FAR_ROWS / 2; ++rr) X2[rr] = ray_coord(a.sy0, row(rr), a.spy);
-        const PatchBound bound = patch_bound(a, far_err, SFAR, SDEF, n_near, all_flagged);
-        double cu[2], eu[2], cv[FAR_ROWS / 2], ev[FAR_ROWS / 2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            cu[c] = (a.c1 * X1[c] - a.tx0) * a.inv_pixw;
-            eu[c] = __builtin_fma(bound.gu, fabs(a.c1 * X1[c]), bound.eu);
-        }
-#pragma unroll
-        for (int rr = 0; rr < FAR_ROWS / 2; ++rr) {
-            cv[rr] = (a.c2 * X2[rr] - a.ty0) * a.inv_pixh;
-            ev[rr] = __builtin_fma(bound.gv, fabs(a.c2 * X2[rr]), bound.ev);
-        }
-        // The thread's rays in two passes of RPASS: per pass, (1) the expansion of each
-        // ray (independent Horner chains), (2) the near lenses, each read from LDS once
-        // per pass and added onto each ray's far part in list order, (3) the pixel
-        // decision and binning into the block's pixel table.
-        constexpr int RPASS = FAR_ROWS / 2;
-#pragma unroll
-        for (int pass = 0; pass < FAR_ROWS / RPASS; ++pass) {
-            double A1[RPASS], A2[RPASS];
-            {
-                double T1[FAR_P], T2[FAR_P];
-#pragma unroll
-                for (int n = 0; n < FAR_P; ++n) {
-                    T1[n] = sm.rec[n];
-                    T2[n] = sm.rec[FAR_P + n];
-                }
-#pragma unroll
-                for (int k = 0; k < RPASS; ++k) {
-                    const int r = pass * RPASS + k;
-                    const double nw1 = ox - X1[r & 1], nw2 = oy - X2[r >> 1];   // -w
-                    double S1 = T1[FAR_P - 1], S2 = T2[FAR_P - 1];
-#pragma unroll
-                    for (int n = FAR_P - 2; n >= 0; --n) {
-                        const double q1 = __builtin_fma(S1, nw1, __builtin_fma(-S2, nw2, T1[n]));
-                        const double q2 = __builtin_fma(S1, nw2, __builtin_fma(S2, nw1, T2[n]));
-                        S1 = q1;
-                        S2 = q2;
-                    }
-                    A1[k] = S1;
-                    A2[k] = -S2;
+            for (int k = FAR_P - 1; k >= 0; --k) {
+                const double s = q * (1.0 / (k + 1));
+                const double2 t = T0[k];
+                r0 = make_double2(__builtin_fma(-s, r0.y, t.x), __builtin_fma(s, r0.x, t.y));
+                if (k < FAR_P / 2) {   // (m1 is at least 8)
+                    const double2 t1 = T1[k];
+                    r1 = make_double2(__builtin_fma(-s, r1.y, t1.x), __builtin_fma(s, r1.x, t1.y));
                 }
             }
-            double SN[RPASS];
+            my_row[m0] = make_double2(r0.x * inv0, r0.y * inv0);
+            my_row[m1] = make_double2(r1.x * inv1, r1.y * inv1);
+            wave_lds_fence();
+        }
+        const double vrow = __builtin_fma(x2, oc2, ov);
+        // The row's rays in two passes of RPASS columns.
+        constexpr int RPASS = FAR_ROWS / 2;
+        const double i_base = (double)(f.ib + (lane & 7)) + 0.5;
+#pragma unroll 1
+        for (int pass = 0; pass < FAR_ROWS / RPASS; ++pass) {
+            double X1[RPASS], A1[RPASS], A2[RPASS], SN[RPASS];
+            {
+                double p[RPASS];
 #pragma unroll
-            for (int k = 0; k < RPASS; ++k) SN[k] = 0.0;
-            bool tiny = false;
-            for (int q = 0; q < n_near; ++q) {
-                const double X = sm.near_x[q], Y = sm.near_y[q];
-                double e1[2], e2[2], r2[RPASS], f[RPASS];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    e1[c] = X1[c] - X;
-                    e2[c] = X2[2 * pass + c] - Y;
+                for (int k = 0; k < RPASS; ++k) {
+                    X1[k] = a.sx0 + (i_base + (double)(8 * (pass * RPASS + k))) * a.spx;   // ray_coord's operations
+                    p[k] = f.ox - X1[k];
+                    SN[k] = 0.0;
                 }
-                // ray k: column k % 2, row k / 2; one reciprocal for the four (v_rcp_f64 takes
-                // four times an FMA's issue, and its two Newton steps four FMAs)
+                const double2 t = my_row[FAR_P - 1];
 #pragma unroll
-                for (int k = 0; k < RPASS; ++k) r2[k] = __builtin_fma(e1[k & 1], e1[k & 1], e2[k >> 1] * e2[k >> 1]);
+                for (int k = 0; k < RPASS; ++k) {
+                    A1[k] = t.x;
+                    A2[k] = -t.y;
+                }
+#pragma unroll
+                for (int m = FAR_P - 2; m >= 0; --m) {
+                    const double2 c = my_row[m];
+#pragma unroll
+                    for (int k = 0; k < RPASS; ++k) {
+                        A1[k] = __builtin_fma(A1[k], p[k], c.x);
+                        A2[k] = __builtin_fma(A2[k], p[k], -c.y);
+                    }
+                }
+            }
+            bool tiny = false;
+            for (int l = 0; l < n_near; ++l) {
+                const double e2 = x2 - near_y[l], e2sq = e2 * e2;
+                double e1[RPASS], r2[RPASS], g[RPASS];
+#pragma unroll
+                for (int k = 0; k < RPASS; ++k) {
+                    e1[k] = X1[k] - near_x[l];
+                    r2[k] = __builtin_fma(e1[k], e1[k], e2sq);
+                }
+                // one reciprocal for the four (v_rcp_f64 takes four times an FMA's issue, and
+                // its two Newton steps four FMAs)
                 const double pab = r2[0] * r2[1], pcd = r2[2] * r2[3], P = pab * pcd;
                 tiny |= !(P > 1e-290);
                 const double R = rcp64(P);
                 double qab = R * pcd, qcd = R * pab;
                 if (!UNIT) {
-                    const double M = sm.near_m[q];
+                    const double M = near_m[l];
                     qab = M * qab;
                     qcd = M * qcd;
                 }
-                f[0] = r2[1] * qab;
-                f[1] = r2[0] * qab;
-                f[2] = r2[3] * qcd;
-                f[3] = r2[2] * qcd;
+                g[0] = r2[1] * qab;
+                g[1] = r2[0] * qab;
+                g[2] = r2[3] * qcd;
+                g[3] = r2[2] * qcd;
 #pragma unroll
                 for (int k = 0; k < RPASS; ++k) {
-                    A1[k] = __builtin_fma(f[k], e1[k & 1], A1[k]);
-                    A2[k] = __builtin_fma(f[k], e2[k >> 1], A2[k]);
-                    SN[k] = __builtin_fma(fabs(e1[k & 1]) + fabs(e2[k >> 1]), UNIT ? f[k] : fabs(f[k]), SN[k]);
+                    A1[k] = __builtin_fma(g[k], e1[k], A1[k]);
+                    A2[k] = __builtin_fma(g[k], e2, A2[k]);
+                    SN[k] = __builtin_fma(fabs(e1[k]) + fabs(e2), UNIT ? g[k] : fabs(g[k]), SN[k]);
                 }
+            }
+            if (pass == 0) {
+                __syncthreads();   // the previous patch has left the pixel table
+                if (tid == 0) sm.table.used[par ^ 1] = 0u;
             }
 #pragma unroll
             for (int k = 0; k < RPASS; ++k) {
-                const int r = pass * RPASS + k;
-                const int64_t i = col(r & 1), j = row(r >> 1);
+                const int64_t i = f.ib + (lane & 7) + 8 * (pass * RPASS + k);
                 const bool valid = (i < a.i1) && (j < a.jc1);
-                int code = patch_decide(a, bound, cu[r & 1], cv[r >> 1], eu[r & 1], ev[r >> 1], A1[k], A2[k], SN[k]);
+                const double u = __builtin_fma(-A1[k], a.inv_pixw, __builtin_fma(X1[k], oc1, ou));
+                const double v = __builtin_fma(-A2[k], a.inv_pixh, vrow);
+                int code = patch_decide(a, bound, u, v, SN[k]);
                 if (tiny) code = FLAGGED;
                 if (!valid) code = INT32_MIN;
 
@@ -894,14 +939,16 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
                 if (fl) queue_append(a, fl, lane, code == FLAGGED, i, j);
             }
         }
-        if (tid == 0) sm.next = (int)next;
+        hold(par ^ 1, ahead);
+        if (tid == 0) sm.next = after;
         __syncthreads();   // every ray of the patch is in the table
         if (!PIX) table_flush_clear<FAR_THREADS>(sm.table, a.map, tid, par);
-        patch = sm.next;
+        patch = next;
+        next = sm.next;
     }
     if (lane == 0) {
-        if (n_in) global_add(a.counters + C_IN, n_in);
-        if (n_out) global_add(a.counters + C_OUT, n_out);
+        if (n_in) global_add(a.counters + C_IN, (unsigned long long)n_in);
+        if (n_out) global_add(a.counters + C_OUT, (unsigned long long)n_out);
     }
 }
 

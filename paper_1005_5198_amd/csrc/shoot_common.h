@@ -90,11 +90,11 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 // directly. Counts are integers, so the map does not depend on the order of the additions.
 constexpr int PT_LINE = 16;
 constexpr int PT_SLOTS = 256;
-constexpr int PT_PROBES = 4;
+constexpr int PT_PROBES = 2;
 struct PixelTable {
     uint32_t cnt[PT_SLOTS * PT_LINE];
     uint32_t key[PT_SLOTS];     // line + 1; 0 = empty
-    uint32_t list[PT_SLOTS];    // used slots, in order of their first use
+    uint8_t list[PT_SLOTS];     // used slots, in order of their first use
     uint32_t used[2];           // their number (of two counts, so that one can be reset while the other is in use)
 };
 
@@ -114,7 +114,7 @@ __device__ __forceinline__ void table_add(PixelTable &t, uint32_t *map, int p, u
         if (old == 0u) {
             old = atomicCAS(&t.key[s], 0u, k);
             if (old == 0u) {
-                t.list[atomicAdd(&t.used[par], 1u)] = s;   // at most once per slot
+                t.list[atomicAdd(&t.used[par], 1u)] = (uint8_t)s;   // at most once per slot
                 old = k;
             }
         }
