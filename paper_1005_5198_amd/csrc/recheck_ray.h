@@ -106,94 +106,154 @@ __device__ inline int exact_ray_thread(const RecheckArgs &a, int64_t i, int64_t 
     return CODE_OUT;
 }
 
-// The same definition evaluated by a whole wave for one ray (i, j wave-uniform):
-// lanes form the per-lens terms (m/r2)*d1, (m/r2)*d2 of 64 lenses at a time and
-// stage them in LDS; every lane then adds them in lens order (the same sum in
-// every lane, so no lane-to-scalar moves sit on the dependent chain). Callers
-// are blocks of at most 256 threads.
 __device__ __forceinline__ void wave_lds_fence() {
     // LDS accesses of one wave complete in order; keep the compiler from moving them across.
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
 
+// Inclusive sums over the wave's lanes, in lane order, by DPP (row_shr within rows of 16
+// lanes, then the rows' last lanes broadcast to the rows after them).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double shift_dpp(double v) {   // (0 where there is no source lane)
+    const uint64_t w = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)w, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(w >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double add_dpp(double v) {
+    return v + shift_dpp<CTRL, ROWS>(v);
+}
+__device__ __forceinline__ double wave_scan(double v) {
+    v = add_dpp<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8
+    v = add_dpp<0x112, 0xf>(v);
+    v = add_dpp<0x114, 0xf>(v);
+    v = add_dpp<0x118, 0xf>(v);
+    v = add_dpp<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    return add_dpp<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const uint64_t w = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(w >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// s <- fl(...fl(fl(s + t_0) + t_1)...) over the terms of the wave, lane l holding terms
+// l J .. l J + J - 1 of the sequence: each addition's rounding exactly as one after the
+// other, many at a time.
+//
+// While every partial sum stays strictly inside one binade (2^e < |s| < 2^(e+1), unit in
+// the last place g = 2^(e-52)), s is a multiple of g and an addition gives s + r, r = t
+// rounded to a multiple of g: the roundings do not depend on s, and the r add up without
+// rounding, in any order. r = fl(t + C) - C with C = 1.5 2^e, which stays in the binade for
+// |t| < 2^(e-1). Where that does not hold - a partial sum leaves the binade, a larger t, a
+// tie (t halfway between two multiples of g, whose rounding depends on s) - the first
+// lane concerned is found from the exact partial sums; the lanes before it are added at
+// once, its J terms one by one, and the rest starts over from the new s (the second time
+// after two lanes one by one, then after four, ...: such places lie close together).
+
+// One round, over the lanes from `from` on: the partial sum before each lane (exact up to
+// the first lane concerned), the sum of every lane's terms, and the lanes concerned.
+struct OrderedRound {
+    double before, total;
+    uint64_t where;
+};
+template <int J>
+__device__ __forceinline__ OrderedRound ordered_round(double s, const double (&t)[J], int from) {
+    const uint64_t bits = (uint64_t)__double_as_longlong(s);
+    const uint64_t ex = bits & 0x7ff0000000000000ull, sign = bits & 0x8000000000000000ull;
+    // (g has to be a normal number, 2^(e+1) finite; zero and denormals are not)
+    bool bad = ex < (60ull << 52) || ex >= (2040ull << 52);
+    const double p = __longlong_as_double((long long)ex);   // 2^e
+    const double half_g = __longlong_as_double((long long)(ex - (53ull << 52)));
+    const double C = __longlong_as_double((long long)((uint64_t)__double_as_longlong(1.5 * p) | sign));
+    const bool mine = __lane_id() >= from;
+    double sum = 0.0, lo = 0.0, hi = 0.0;   // this lane's partial sums
+#pragma unroll
+    for (int u = 0; u < J; ++u) {
+        const double r = (t[u] + C) - C;
+        bad |= !(fabs(t[u]) < 0.5 * p) || fabs(t[u] - r) == half_g;   // (t - r is exact)
+        sum += r;
+        lo = fmin(lo, sum);
+        hi = fmax(hi, sum);
+    }
+    const double upto = wave_scan(mine ? sum : 0.0);
+    OrderedRound o;
+    o.before = s + shift_dpp<0x138>(upto);   // wave_shr:1
+    o.total = read_lane(upto, 63);
+    const double a0 = o.before + lo, a1 = o.before + hi;
+    const double least = sign ? -a1 : a0, most = sign ? -a0 : a1;   // of |partial sum|
+    bad |= !(least > p && most < 2.0 * p);
+    o.where = __ballot(bad && mine);
+    return o;
+}
+
+template <int J>
+__device__ __forceinline__ double add_in_order(double s, const double (&t)[J], OrderedRound o) {
+    for (int run = 1; o.where; run *= 2) {   // (the same in every lane)
+        int next = __builtin_ctzll(o.where);
+        s = read_lane(o.before, next);   // (exact: every lane before it is good)
+        const int end = next + run < 64 ? next + run : 64;
+#pragma unroll 1
+        for (; next < end; ++next) {   // every lane adds its own terms; lane next's sum counts
+#pragma unroll
+            for (int u = 0; u < J; ++u) s += t[u];
+            s = read_lane(s, next);
+        }
+        if (next == 64) return s;
+        o = ordered_round(s, t, next);
+    }
+    return s + o.total;
+}
+
+// The same definition evaluated by a whole wave for one ray (i, j wave-uniform): lanes
+// form the per-lens terms (m/r2)*d1, (m/r2)*d2 of EXACT_J consecutive lenses each, and the
+// sums add them in lens order (add_in_order). The 10^6-lens far-field map's last rays:
+// 4.7 ms (the slowest ray, whose sum stays near zero; 2.2 ms without its starts over)
+// against 9.8 ms for the chain of dependent additions alone.
+constexpr int EXACT_J = 8;
 template <bool UNIT>
 __device__ inline int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j) {
-    __shared__ double2 terms[4][2][64];   // [wave][buffer][lens of the chunk]: (m/r2 d1, m/r2 d2)
     const int lane = __lane_id();
-    const int w = (threadIdx.x >> 6) & 3;
     double x1, x2;
     ray_xy(a, i, j, x1, x2);
-    double a1 = 0.0, a2 = 0.0;
+    double a1 = 0.0, a2 = 0.0;   // the same in every lane
     bool zero = false;
-    if (a.n_lens > 0) {
-        // Loads and terms have no branches (indices past the last lens read the last
-        // lens, and their terms are replaced by zero, which adds nothing: the running
-        // sums start at +0 and never become -0), so the compiler can count the loads
-        // in flight and wait for the oldest only.
-        const int64_t last = a.n_lens - 1;
-        auto load = [&](int64_t k, double &X, double &Y, double &M) {
-            const int64_t kc = k < a.n_lens ? k : last;
-            X = lens_x(a, kc);
-            Y = lens_y(a, kc);
-            M = UNIT ? 1.0 : lens_mass(a, kc);
-        };
-        auto term = [&](int64_t k, double X, double Y, double M) {
-            const double d1 = x1 - X;
-            const double d2 = x2 - Y;
+    // Loads have no branches (indices past the last lens read the last lens, and their
+    // terms are replaced by zero, which adds nothing: the running sums start at +0 and
+    // never become -0), and the next lenses are loaded while these are summed.
+    const int64_t last = a.n_lens - 1;
+    double X[EXACT_J], Y[EXACT_J], M[EXACT_J];
+    auto load = [&](int64_t k0) {
+#pragma unroll
+        for (int u = 0; u < EXACT_J; ++u) {
+            const int64_t k = k0 + u < a.n_lens ? k0 + u : last;
+            X[u] = lens_x(a, k);
+            Y[u] = lens_y(a, k);
+            M[u] = UNIT ? 1.0 : lens_mass(a, k);
+        }
+    };
+    if (a.n_lens > 0) load((int64_t)lane * EXACT_J);
+    for (int64_t k0 = 0; k0 < a.n_lens; k0 += 64 * EXACT_J) {
+        const int64_t mine = k0 + (int64_t)lane * EXACT_J;
+        double t1[EXACT_J], t2[EXACT_J];
+#pragma unroll
+        for (int u = 0; u < EXACT_J; ++u) {
+            const double d1 = x1 - X[u];
+            const double d2 = x2 - Y[u];
             const double r2 = d1 * d1 + d2 * d2;
-            const bool real = k < a.n_lens;
+            const bool real = mine + u < a.n_lens;
             zero |= real && (r2 == 0.0);
-            const double m = UNIT ? 1.0 : M;
-            const double f = m / r2;
-            return make_double2(real ? f * d1 : 0.0, real ? f * d2 : 0.0);
-        };
-        const int64_t n_chunks = (a.n_lens + 63) / 64;
-        {
-            double X, Y, M;
-            load(lane, X, Y, M);
-            terms[w][0][lane] = term(lane, X, Y, M);
+            const double f = (UNIT ? 1.0 : M[u]) / r2;
+            t1[u] = real ? f * d1 : 0.0;
+            t2[u] = real ? f * d2 : 0.0;
         }
-        // Lens positions are loaded P chunks ahead of their terms (slot s of the ring
-        // holds chunk c + 1 while chunk c is summed, c = s mod P), and a chunk's terms
-        // are formed while the previous chunk is summed, so neither the memory latency
-        // nor the division sits on the dependent chain of additions.
-        constexpr int P = 4;
-        double SX[P], SY[P], SM[P];
-#pragma unroll
-        for (int s = 0; s < P; ++s) load(64 * (s + 1) + lane, SX[s], SY[s], SM[s]);
-        wave_lds_fence();
-        // Whole rounds of P chunks: the chunks past the last one hold zero terms.
-        for (int64_t c0 = 0; c0 < n_chunks; c0 += P) {
-#pragma unroll
-            for (int s = 0; s < P; ++s) {
-                const int64_t c = c0 + s;
-                const double2 tn = term(64 * (c + 1) + lane, SX[s], SY[s], SM[s]);
-                load(64 * (c + 1 + P) + lane, SX[s], SY[s], SM[s]);
-                const double2 *T = terms[w][c & 1];
-                // in lens order, eight terms read ahead of their additions (LDS latency
-                // is several times one addition's)
-                constexpr int B = 8;
-                double2 cur[B];
-#pragma unroll
-                for (int l = 0; l < B; ++l) cur[l] = T[l];
-#pragma unroll
-                for (int g = 0; g < 64 / B; ++g) {
-                    double2 nxt[B];
-#pragma unroll
-                    for (int l = 0; l < B; ++l) nxt[l] = T[(B * (g + 1) + l) & 63];
-#pragma unroll
-                    for (int l = 0; l < B; ++l) {
-                        a1 += cur[l].x;
-                        a2 += cur[l].y;
-                    }
-#pragma unroll
-                    for (int l = 0; l < B; ++l) cur[l] = nxt[l];
-                }
-                terms[w][(c + 1) & 1][lane] = tn;
-                wave_lds_fence();   // every lane has read chunk c, and chunk c + 1 is written
-            }
-        }
+        load(mine + 64 * EXACT_J);
+        const OrderedRound o1 = ordered_round(a1, t1, 0), o2 = ordered_round(a2, t2, 0);
+        a1 = add_in_order(a1, t1, o1);
+        a2 = add_in_order(a2, t2, o2);
     }
     if (__ballot(zero)) return CODE_SINGULAR;
     const double y1 = ((1.0 - a.gamma) - a.sigma_c) * x1 - a1;
