@@ -14,7 +14,13 @@ namespace {
 
 constexpr int FAR_P = 16;                 // expansion order
 constexpr double FAR_RATIO = 4.0;         // lenses beyond FAR_RATIO half-diagonals are expanded
-constexpr int FAR_EXTRA = 4;              // SFAR, TRUNC, SDEF, NFAR
+constexpr int FAR_EXTRA = 4;              // SFAR, TRUNC, SDEF, CHAIN
+// A record: FAR_P real and FAR_P imaginary coefficients, then over the expanded lenses
+//   SFAR   sum of |m|/|d|, d the distance from the centre;
+//   TRUNC  bound of the terms past the last power, sum of |m|/|d| rho^P / (1 - rho), rho = H/|d|;
+//   SDEF   sum of |m| / (|d| - H), which bounds sum |m| |d1| / r^2 and sum |m| |d2| / r^2, the
+//          magnitudes the definition adds up, for every ray of the cell;
+//   CHAIN  the additions a term went through in these sums (their rounding).
 constexpr int FAR_REC = 2 * FAR_P + FAR_EXTRA;
 // Roundings of one directly summed lens's term, in units of 2^-53 of |e1| + |e2| over r^2
 // (the differences, r^2, the reciprocal, shared by four rays in the ray kernel: four
@@ -172,8 +178,8 @@ __device__ inline int far_eval(const ShootArgs &a, int64_t sp, double x1, double
         a2 -= S2;
     }
     const double SFAR = rec[2 * FAR_P], TRUNC = rec[2 * FAR_P + 1], SDEF = rec[2 * FAR_P + 2];
-    const double NFAR = rec[2 * FAR_P + 3];
-    const double far_err = TRUNC + (NFAR + 24.0 * FAR_P + 64.0) * U64 * 1.34 * SFAR;
+    const double CHAIN = rec[2 * FAR_P + 3];
+    const double far_err = TRUNC + (CHAIN + 24.0 * FAR_P + 64.0) * U64 * 1.34 * SFAR;
     return far_decide(a, x1, x2, a1, a2, far_err, SFAR, SDEF, snear, listed, !tiny);
 }
 

@@ -109,17 +109,17 @@ __device__ __forceinline__ void scatter_dpp(double (&v)[M], int lane, int &at, i
 
 // One lens's contribution to an expansion about (ox, oy) with half-diagonal h
 // (the lens is at least FAR_RATIO h away): the powers m t^(n+1) and the bound
-// terms m/|d|, m/|d| rho^P / (1 - rho) and sqrt(2) m / (|d| - h).
+// terms m/|d|, m/|d| rho^P / (1 - rho) and m / (|d| - h).
 struct FarAcc {
     double c1[FAR_P], c2[FAR_P];
-    double sfar, trunc, sdef, nfar;
+    double sfar, trunc, sdef;
     __device__ void zero() {
 #pragma unroll
         for (int n = 0; n < FAR_P; ++n) {
             c1[n] = 0.0;
             c2[n] = 0.0;
         }
-        sfar = trunc = sdef = nfar = 0.0;
+        sfar = trunc = sdef = 0.0;
     }
     __device__ __forceinline__ void add(double d1, double d2, double r2, double m, double h) {
         const double inv = rcp64(r2);
@@ -143,11 +143,10 @@ struct FarAcc {
         const double s = fabs(m) * inv_ad;
         const double rho = h * inv_ad;
         const double rho2 = rho * rho, rho4 = rho2 * rho2, rho8 = rho4 * rho4, rho16 = rho8 * rho8;
-        const double g = rcp64(1.0 - rho);
+        const double sg = s * rcp64(1.0 - rho);
         sfar += s;
-        trunc += s * rho16 * g;
-        sdef += 1.4142135623730951 * s * g;
-        nfar += 1.0;
+        trunc = __builtin_fma(sg, rho16, trunc);
+        sdef += sg;
     }
     // The wave's totals into tot[FAR_REC] (shared): a reduction that scatters as it goes
     // (each step halves the number of values a lane holds), 38 exchanges of a double in all
@@ -163,7 +162,7 @@ struct FarAcc {
         v[2 * FAR_P] = sfar;
         v[2 * FAR_P + 1] = trunc;
         v[2 * FAR_P + 2] = sdef;
-        v[2 * FAR_P + 3] = nfar;
+        v[2 * FAR_P + 3] = 0.0;   // (CHAIN is the builder's)
         const int lane = threadIdx.x & 63;
         int at = 0, end = FAR_REC;   // this lane's values are at .. end - 1 of the 36
         scatter_swap<32, 36>(v, lane, at, end);
@@ -242,9 +241,13 @@ __device__ __forceinline__ void build_level(const ShootArgs &a, double cx, doubl
         acc.add(d1, d2, r2, m, H);
     }
     acc.template reduce<THREADS>(sm.part, sm.out);
+    // The most additions any term of this level's sums went through: its thread's own, the
+    // lanes', the waves'. (With the number of lenses in its place, 10^6 at the top, this
+    // rounding was half of the bound.)
+    const double chain = (double)((n_cand + THREADS - 1) / THREADS + 6 + THREADS / 64);
     const int t = threadIdx.x;
     if (parent == nullptr) {
-        if (t < FAR_REC) rec[t] = sm.out[t];
+        if (t < FAR_REC) rec[t] = t == FAR_REC - 1 ? chain : sm.out[t];
     } else {
         const global_double *Pp = (const global_double *)parent;
         auto P = [&](int n) {
@@ -268,7 +271,8 @@ __device__ __forceinline__ void build_level(const ShootArgs &a, double cx, doubl
             rec[t] = s1 + sm.out[t];
             rec[FAR_P + t] = s2 + sm.out[FAR_P + t];
         } else if (t < FAR_P + FAR_EXTRA) {
-            rec[2 * FAR_P + (t - FAR_P)] = P(2 * FAR_P + (t - FAR_P)) + sm.out[2 * FAR_P + (t - FAR_P)];
+            const int k = FAR_P + t;   // the bound terms (the parts' chains add up to more than the longest and the joining)
+            rec[k] = P(k) + (k == FAR_REC - 1 ? chain : sm.out[k]);
         }
     }
     if (t == 0) list[0] = sm.count;
@@ -649,11 +653,11 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_patch_kernel(const Shoot
         rec[2 * mm + 1] = FACTORIAL.f[mm] * (s2 + own[FAR_P + mm]);
     } else if (lane == FAR_P) {
         const double SFAR_S = sc[2 * FAR_P], TRUNC_S = sc[2 * FAR_P + 1], SDEF_S = sc[2 * FAR_P + 2];
-        const double NFAR_S = sc[2 * FAR_P + 3];
-        const double sfar = own[2 * FAR_P], nfar = own[2 * FAR_P + 3];
+        const double CHAIN_S = sc[2 * FAR_P + 3], chain = (double)((c.n + 63) / 64 + 6);
+        const double sfar = own[2 * FAR_P];
         rec[2 * FAR_P] = SFAR_S + sfar;
-        rec[2 * FAR_P + 1] = TRUNC_S + own[2 * FAR_P + 1] + (NFAR_S + 24.0 * FAR_P + 64.0) * U64 * 1.34 * SFAR_S +
-                             (nfar + 16.0 * FAR_P + 64.0) * U64 * 1.34 * sfar;
+        rec[2 * FAR_P + 1] = TRUNC_S + own[2 * FAR_P + 1] + (CHAIN_S + 24.0 * FAR_P + 64.0) * U64 * 1.34 * SFAR_S +
+                             (chain + 16.0 * FAR_P + 64.0) * U64 * 1.34 * sfar;
         rec[2 * FAR_P + 2] = SDEF_S + own[2 * FAR_P + 2];
         rec[2 * FAR_P + 3] = (double)n_near;
     } else if (lane <= FAR_P + FF_PATCH_HEAD - (2 * FAR_P + 4)) {

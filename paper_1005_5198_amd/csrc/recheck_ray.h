@@ -322,13 +322,14 @@ __device__ inline double sequential_bound(int64_t n_lens, double S, double Q) {
 // This stage summing lenses in blocks of B in lens order (one wave per ray, the lanes' sums
 // combined at every block's end): Q = sum over block starts of |partial sum|. For lens k of a
 // block, |s_k| <= |s at the block's start| + the block's sum of |terms|, so sum_k |s_k| <=
-// B Q + B S plus each block start's error (its sum depth e: e 2^-53 S, plus 16 2^-53 S for the
-// two term evaluations); this stage's own sum is within (e + 8) 2^-53 S.
+// B Q + B S plus each block start's error (its sum depth e: e 2^-53 S, plus 21 2^-53 S for the
+// two term evaluations); this stage's own sum is within (e + 13) 2^-53 S (a term: 4 roundings
+// in r^2, 6 of the shared reciprocal, the mass, d).
 __device__ inline double block_bound(int64_t n_lens, double S, double Q, double B, double e) {
     const double U64 = 1.1102230246251565e-16;  // 2^-53
     const double N = (double)n_lens;
-    const double partial = 1.001 * ((e + 32.0 + 1.05 * B) * U64 * S + 1.05 * B * U64 * Q +
-                                    1.05 * (N + B) * (e + 32.0) * U64 * U64 * S);
+    const double partial = 1.001 * ((e + 40.0 + 1.05 * B) * U64 * S + 1.05 * B * U64 * Q +
+                                    1.05 * (N + B) * (e + 40.0) * U64 * U64 * S);
     return fmin(any_order_bound(n_lens, S), partial);
 }
 
@@ -372,20 +373,35 @@ __device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j,
     double a1 = 0.0, a2 = 0.0, S = 0.0, Q1 = 0.0, Q2 = 0.0;
     int tiny = 0;
     // Lane l takes lenses l, l + 64, ...; U of them per step, whose positions were
-    // loaded during the previous step, so the memory latency is not waited for.
-    // Loads past the last lens read the last lens and their terms are dropped, so
-    // the loop has no branches and the compiler can count the loads in flight.
+    // loaded during the previous step, so the memory latency is not waited for. In the
+    // last, partial step loads past the last lens read the last lens and their terms are
+    // dropped, so the loop has no branches per lane and the compiler can count the loads
+    // in flight. A step's four lenses share one reciprocal (v_rcp_f64 issues like four
+    // FMAs, and its Newton steps are four more; sharing takes nine products).
     constexpr int U = 4, L = 4;
     constexpr double B = 64.0 * U * L;
     double LX[U], LY[U], LM[U];
+    const int lane = __lane_id();
     const int64_t last = a.n_lens - 1;
-    auto load = [&](int64_t k0) {
+    const int64_t full = a.n_lens / (64 * U);                   // steps without a remainder
+    const int64_t steps = (a.n_lens + 64 * U - 1) / (64 * U);   // (both the same for every lane)
+    auto load = [&](int64_t it) {
+        const int64_t k0 = 64 * U * it + lane;
+        if (it < full) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t k = k0 + 64 * u < a.n_lens ? k0 + 64 * u : last;
-            LX[u] = lens_x(a, k);
-            LY[u] = lens_y(a, k);
-            LM[u] = UNIT ? 1.0 : lens_mass(a, k);
+            for (int u = 0; u < U; ++u) {
+                LX[u] = lens_x(a, k0 + 64 * u);
+                LY[u] = lens_y(a, k0 + 64 * u);
+                LM[u] = UNIT ? 1.0 : lens_mass(a, k0 + 64 * u);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = k0 + 64 * u < a.n_lens ? k0 + 64 * u : last;
+                LX[u] = lens_x(a, k);
+                LY[u] = lens_y(a, k);
+                LM[u] = UNIT ? 1.0 : lens_mass(a, k);
+            }
         }
     };
     auto wave_sum = [](double v) {
@@ -393,35 +409,41 @@ __device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j,
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
         return v;
     };
-    const int64_t steps = (a.n_lens + 64 * U - 1) / (64 * U);   // the same for every lane
-    if (a.n_lens > 0) load(__lane_id());
+    if (a.n_lens > 0) load(0);
     for (int64_t it = 0; it < steps; ++it) {
-        const int64_t k0 = __lane_id() + 64 * U * it;
-        double X[U], Y[U], M[U];
+        double d1[U], d2[U], r2[U], M[U], rc[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            X[u] = LX[u];
-            Y[u] = LY[u];
+            d1[u] = x1 - LX[u];
+            d2[u] = x2 - LY[u];
             M[u] = LM[u];
         }
-        load(k0 + 64 * U);
+        if (it + 1 < steps) load(it + 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) r2[u] = __builtin_fma(d1[u], d1[u], d2[u] * d2[u]);
+        const double pab = r2[0] * r2[1], pcd = r2[2] * r2[3], P = pab * pcd;
+        tiny |= !(P > 1e-290);   // (and a product that overflows makes S NaN: not decided either)
+        double R = __builtin_amdgcn_rcp(P);
+        double e = __builtin_fma(-P, R, 1.0);
+        R = __builtin_fma(R, e, R);
+        e = __builtin_fma(-P, R, 1.0);
+        R = __builtin_fma(R, e, R);
+        const double qab = R * pcd, qcd = R * pab;
+        rc[0] = r2[1] * qab;
+        rc[1] = r2[0] * qab;
+        rc[2] = r2[3] * qcd;
+        rc[3] = r2[2] * qcd;
+        if (it >= full) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (64 * U * it + 64 * u + lane >= a.n_lens) rc[u] = 0.0;
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool real = k0 + 64 * u < a.n_lens;
-            const double d1 = x1 - X[u];
-            const double d2 = x2 - Y[u];
-            const double r2 = __builtin_fma(d1, d1, d2 * d2);
-            tiny |= real && !(r2 > 1e-200);
-            double rc = __builtin_amdgcn_rcp(r2);
-            double e = __builtin_fma(-r2, rc, 1.0);
-            rc = __builtin_fma(rc, e, rc);
-            e = __builtin_fma(-r2, rc, 1.0);
-            rc = __builtin_fma(rc, e, rc);
-            if (!UNIT) rc = rc * M[u];
-            rc = real ? rc : 0.0;
-            a1 = __builtin_fma(d1, rc, a1);
-            a2 = __builtin_fma(d2, rc, a2);
-            S = __builtin_fma(fabs(d1) + fabs(d2), fabs(rc), S);
+            if (!UNIT) rc[u] = rc[u] * M[u];
+            a1 = __builtin_fma(d1[u], rc[u], a1);
+            a2 = __builtin_fma(d2[u], rc[u], a2);
+            S = __builtin_fma(fabs(d1[u]) + fabs(d2[u]), fabs(rc[u]), S);
         }
         if (it % L == L - 1 || it == steps - 1) {   // a block's end: its partial sums
             Q1 += fabs(wave_sum(a1));
