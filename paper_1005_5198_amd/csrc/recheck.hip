@@ -207,31 +207,48 @@ __global__ __launch_bounds__(256) void recheck_defer_kernel(const RecheckArgs a)
     }
 }
 
-// Stage A over a map's gathered list, one wave per ray; the rays it cannot place
-// go to a list of their own, so that the exact stage deals them out one per wave
-// (marked in place, two of them could fall to one wave and its time would double).
+// Stage A over a map's gathered list, a wave per STAGE_A_RAYS rays once there are more than
+// waves: each wave reads every lens (16 MB of the 10^6-lens map), and two rays a wave halve
+// that (6626 rays: 4.7 ms; one ray a wave 6.2, three, which leaves the chip half empty, 6.3).
+// The rays it cannot place go to a list of their own, so that the exact stage deals
+// them out one per wave (marked in place, two of them could fall to one wave and its time
+// would double).
+constexpr int STAGE_A_RAYS = 2;
+template <bool UNIT, int R>
+__device__ __forceinline__ void fast_deferred(const RecheckArgs &a, uint32_t n, uint32_t wave_id, uint32_t n_waves) {
+    for (uint32_t e = wave_id * R; e < n; e += n_waves * R) {
+        int64_t i[R], j[R];
+        int code[R];
+        bool decided[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t k = e + r < n ? e + r : n - 1;   // (the last one again: not counted)
+            i[r] = a.defer[2 * k];
+            j[r] = a.defer[2 * k + 1];
+        }
+        fast_rays_wave<UNIT, R>(a, i, j, decided, code);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (__lane_id() != 0 || e + r >= n) continue;
+            if (decided[r]) {
+                emit_ray(a, i[r], j[r], code[r]);
+            } else {
+                const uint32_t u = atomicAdd(a.ucount, 1u);   // u < n <= DEFER_CAP
+                a.udefer[2 * (int64_t)u] = i[r];
+                a.udefer[2 * (int64_t)u + 1] = j[r];
+            }
+        }
+    }
+}
 template <bool UNIT>
 __global__ __launch_bounds__(256) void recheck_fast_deferred_kernel(const RecheckArgs a) {
     const uint32_t total = *a.dcount;
     const uint32_t n = total < (uint32_t)DEFER_CAP ? total : (uint32_t)DEFER_CAP;
     if (blockIdx.x == 0 && threadIdx.x == 0 && n) atomicAdd(a.counters + C_DIRECT, (unsigned long long)n);
-    const int lane = __lane_id();
-    const uint32_t wave_id = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const uint32_t wave_id = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
     const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t e = wave_id; e < n; e += n_waves) {
-        const int64_t i = a.defer[2 * (int64_t)e], j = a.defer[2 * (int64_t)e + 1];
-        int code = 0;
-        const bool decided = fast_ray_wave<UNIT>(a, i, j, code);
-        if (lane == 0) {
-            if (decided) {
-                emit_ray(a, i, j, code);
-            } else {
-                const uint32_t u = atomicAdd(a.ucount, 1u);   // u < n <= DEFER_CAP
-                a.udefer[2 * (int64_t)u] = i;
-                a.udefer[2 * (int64_t)u + 1] = j;
-            }
-        }
-    }
+    if (n <= n_waves) fast_deferred<UNIT, 1>(a, n, wave_id, n_waves);
+    else fast_deferred<UNIT, STAGE_A_RAYS>(a, n, wave_id, n_waves);
 }
 
 // The exact stage over the gathered rays stage A left, one wave per ray.

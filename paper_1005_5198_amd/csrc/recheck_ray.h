@@ -362,24 +362,33 @@ __device__ inline bool fast_ray(const RecheckArgs &a, int64_t i, int64_t j, int 
                           sequential_bound(a.n_lens, S, Q2), tiny, code);
 }
 
-// Stage A by a whole wave for one ray (i, j wave-uniform): lanes take every 64th lens, U of
-// them per step; every L steps (blocks of B = 64 U L lenses in lens order) the lanes' running
-// sums are added over the wave to give the partial sum at the block's end, whose magnitudes
-// feed block_bound; the totals meet in the same butterfly. Every lane returns the same result.
-template <bool UNIT>
-__device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j, int &code) {
-    double x1, x2;
-    ray_xy(a, i, j, x1, x2);
-    double a1 = 0.0, a2 = 0.0, S = 0.0, Q1 = 0.0, Q2 = 0.0;
-    int tiny = 0;
+// Stage A by a whole wave for R rays (ray r at (i[r], j[r]), wave-uniform): lanes take every
+// 64th lens, U of them per step; every L steps (blocks of B = 64 U L lenses in lens order) the
+// lanes' running sums are added over the wave to give the partial sum at the block's end, whose
+// magnitudes feed block_bound; the totals meet in the same butterfly. Every lane returns the
+// same result.
+template <bool UNIT, int R>
+__device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R], const int64_t (&j)[R],
+                                      bool (&decided)[R], int (&code)[R]) {
+    double x1[R], x2[R], a1[R], a2[R], S[R], Q1[R], Q2[R];
+    int tiny[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        ray_xy(a, i[r], j[r], x1[r], x2[r]);
+        a1[r] = a2[r] = S[r] = Q1[r] = Q2[r] = 0.0;
+        tiny[r] = 0;
+    }
     // Lane l takes lenses l, l + 64, ...; U of them per step, whose positions were
     // loaded during the previous step, so the memory latency is not waited for. In the
     // last, partial step loads past the last lens read the last lens and their terms are
     // dropped, so the loop has no branches per lane and the compiler can count the loads
-    // in flight. A step's four lenses share one reciprocal (v_rcp_f64 issues like four
+    // in flight. Four lenses share one reciprocal (v_rcp_f64 issues like four
     // FMAs, and its Newton steps are four more; sharing takes nine products).
-    constexpr int U = 4, L = 4;
-    constexpr double B = 64.0 * U * L;
+    constexpr int U = 8;
+    // (a block's butterfly takes as long as its 16 lenses per lane; where there are many
+    // lenses, blocks of 4096 add little to the bound)
+    const int L = a.n_lens < (1 << 18) ? 2 : 8;
+    const double B = 64.0 * U * L;
     double LX[U], LY[U], LM[U];
     const int lane = __lane_id();
     const int64_t last = a.n_lens - 1;
@@ -411,54 +420,78 @@ __device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j,
     };
     if (a.n_lens > 0) load(0);
     for (int64_t it = 0; it < steps; ++it) {
-        double d1[U], d2[U], r2[U], M[U], rc[U];
+        double X[U], Y[U], M[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            d1[u] = x1 - LX[u];
-            d2[u] = x2 - LY[u];
+            X[u] = LX[u];
+            Y[u] = LY[u];
             M[u] = LM[u];
         }
         if (it + 1 < steps) load(it + 1);
 #pragma unroll
-        for (int u = 0; u < U; ++u) r2[u] = __builtin_fma(d1[u], d1[u], d2[u] * d2[u]);
-        const double pab = r2[0] * r2[1], pcd = r2[2] * r2[3], P = pab * pcd;
-        tiny |= !(P > 1e-290);   // (and a product that overflows makes S NaN: not decided either)
-        double R = __builtin_amdgcn_rcp(P);
-        double e = __builtin_fma(-P, R, 1.0);
-        R = __builtin_fma(R, e, R);
-        e = __builtin_fma(-P, R, 1.0);
-        R = __builtin_fma(R, e, R);
-        const double qab = R * pcd, qcd = R * pab;
-        rc[0] = r2[1] * qab;
-        rc[1] = r2[0] * qab;
-        rc[2] = r2[3] * qcd;
-        rc[3] = r2[2] * qcd;
-        if (it >= full) {
+        for (int r = 0; r < R; ++r) {
+            double d1[U], d2[U], r2[U], rc[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (64 * U * it + 64 * u + lane >= a.n_lens) rc[u] = 0.0;
-        }
+            for (int u = 0; u < U; ++u) {
+                d1[u] = x1[r] - X[u];
+                d2[u] = x2[r] - Y[u];
+                r2[u] = __builtin_fma(d1[u], d1[u], d2[u] * d2[u]);
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!UNIT) rc[u] = rc[u] * M[u];
-            a1 = __builtin_fma(d1[u], rc[u], a1);
-            a2 = __builtin_fma(d2[u], rc[u], a2);
-            S = __builtin_fma(fabs(d1[u]) + fabs(d2[u]), fabs(rc[u]), S);
+            for (int q = 0; q < U; q += 4) {
+                const double pab = r2[q] * r2[q + 1], pcd = r2[q + 2] * r2[q + 3], P = pab * pcd;
+                tiny[r] |= !(P > 1e-290);   // (and a product that overflows makes S NaN: not decided either)
+                double rp = __builtin_amdgcn_rcp(P);
+                double e = __builtin_fma(-P, rp, 1.0);
+                rp = __builtin_fma(rp, e, rp);
+                e = __builtin_fma(-P, rp, 1.0);
+                rp = __builtin_fma(rp, e, rp);
+                const double qab = rp * pcd, qcd = rp * pab;
+                rc[q] = r2[q + 1] * qab;
+                rc[q + 1] = r2[q] * qab;
+                rc[q + 2] = r2[q + 3] * qcd;
+                rc[q + 3] = r2[q + 2] * qcd;
+            }
+            if (it >= full) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (64 * U * it + 64 * u + lane >= a.n_lens) rc[u] = 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!UNIT) rc[u] = rc[u] * M[u];
+                a1[r] = __builtin_fma(d1[u], rc[u], a1[r]);
+                a2[r] = __builtin_fma(d2[u], rc[u], a2[r]);
+                S[r] = __builtin_fma(fabs(d1[u]) + fabs(d2[u]), fabs(rc[u]), S[r]);
+            }
         }
-        if (it % L == L - 1 || it == steps - 1) {   // a block's end: its partial sums
-            Q1 += fabs(wave_sum(a1));
-            Q2 += fabs(wave_sum(a2));
+        if ((it & (L - 1)) == L - 1 || it == steps - 1) {   // a block's end: its partial sums
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                Q1[r] += fabs(wave_sum(a1[r]));
+                Q2[r] += fabs(wave_sum(a2[r]));
+            }
         }
     }
-    a1 = wave_sum(a1);
-    a2 = wave_sum(a2);
-    S = wave_sum(S);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) tiny |= __shfl_xor(tiny, off);
     // a partial sum's depth: a lane's running sum plus the six butterfly levels
     const double depth = (double)steps * U + 6.0;
-    return stage_a_decide(a, x1, x2, a1, a2, S, block_bound(a.n_lens, S, Q1, B, depth),
-                          block_bound(a.n_lens, S, Q2, B, depth), tiny != 0, code);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double t1 = wave_sum(a1[r]), t2 = wave_sum(a2[r]), s = wave_sum(S[r]);
+        const bool t = __ballot(tiny[r]) != 0;
+        decided[r] = stage_a_decide(a, x1[r], x2[r], t1, t2, s, block_bound(a.n_lens, s, Q1[r], B, depth),
+                                    block_bound(a.n_lens, s, Q2[r], B, depth), t, code[r]);
+    }
+}
+
+template <bool UNIT>
+__device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j, int &code) {
+    const int64_t ri[1] = {i}, rj[1] = {j};
+    bool decided[1];
+    int c[1] = {code};
+    fast_rays_wave<UNIT, 1>(a, ri, rj, decided, c);
+    code = c[0];
+    return decided[0];
 }
 
 // Bin one re-checked ray (or write its pixel) and count it in the map's counters.
