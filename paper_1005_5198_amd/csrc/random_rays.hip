@@ -22,18 +22,56 @@ __device__ __forceinline__ int64_t bin_of(const ShootArgs &a, double x1, double 
     return by * a.nbx_r + bx;
 }
 
-__global__ __launch_bounds__(256) void rand_count_kernel(const ShootArgs a) {
-    const int64_t W = a.i1 - a.i0;
-    const int64_t n = (a.jc1 - a.jc0) * W;
-    for (int64_t rel = blockIdx.x * (int64_t)256 + threadIdx.x; rel < n; rel += (int64_t)gridDim.x * 256) {
+// Counting and scattering by blocks, each over one range of the launch's rays, with the
+// bins' counts in LDS: a block adds its count of a bin to the bin at once, and reserves its
+// slots of the bin at once; bins past the LDS counts' number (more than the largest launch
+// has, but for strips) take further rounds over the block's rays. One atomic per ray on the
+// bins bound both kernels: 4.9 million rays in 2600 bins took 0.48 ms each, now 0.05 and 0.2
+// (the scatter makes the positions twice); 60000 rays a map of 0.26 ms, now 0.06; launches of
+// 64 million rays a map of 9.1 ms, now 5.8 (6.2 with 1024 blocks, 8.5 with 512).
+constexpr int RAND_THREADS = 1024;
+constexpr int RAND_BLOCKS = 2048;
+constexpr uint32_t RAND_LDS_BINS = 36864;
+constexpr int64_t RAND_BLOCK_RAYS = 1024;   // at least, so that small launches make few atomics
+
+// f(rel, x1, x2, bin) for every ray of the block's range.
+template <class F>
+__device__ __forceinline__ void block_rays(const ShootArgs &a, F f) {
+    const uint32_t W = (uint32_t)(a.i1 - a.i0);                     // at most 2^22
+    const uint32_t n = (uint32_t)((a.jc1 - a.jc0) * (a.i1 - a.i0));   // at most RAND_CHUNK_RAYS, or one row
+    const uint32_t per = (n + gridDim.x - 1) / gridDim.x;
+    const uint32_t lo = min(n, blockIdx.x * per), hi = min(n, lo + per);
+    for (uint32_t rel = lo + threadIdx.x; rel < hi; rel += RAND_THREADS) {
         const int64_t i = a.i0 + rel % W, j = a.jc0 + rel / W;
         double x1, x2;
         random_ray_xy(a.sx0, a.sy0, a.sw, a.sh, a.nx, a.seed, i, j, x1, x2);
-        atomicAdd(a.bin_count + bin_of(a, x1, x2), 1u);
+        f(rel, x1, x2, (uint32_t)bin_of(a, x1, x2));
     }
 }
 
-// Exclusive prefix sums of the bin counts (one block): offset[0..nb], cursor = offset.
+// The block's rays of bins [first, first + RAND_LDS_BINS) counted into LDS.
+__device__ __forceinline__ uint32_t block_count(const ShootArgs &a, uint32_t first, uint32_t nb, uint32_t *count) {
+    const uint32_t bins = min(RAND_LDS_BINS, nb - first);
+    for (uint32_t b = threadIdx.x; b < bins; b += RAND_THREADS) count[b] = 0u;
+    __syncthreads();
+    block_rays(a, [&](uint32_t, double, double, uint32_t bin) {
+        if (bin - first < bins) atomicAdd(&count[bin - first], 1u);
+    });
+    __syncthreads();
+    return bins;
+}
+
+__global__ __launch_bounds__(RAND_THREADS) void rand_count_kernel(const ShootArgs a) {
+    extern __shared__ uint32_t count[];   // RAND_LDS_BINS, or one per bin
+    const uint32_t nb = (uint32_t)(a.nbx_r * a.nby_r);
+    for (uint32_t first = 0; first < nb; first += RAND_LDS_BINS) {
+        const uint32_t bins = block_count(a, first, nb, count);
+        for (uint32_t b = threadIdx.x; b < bins; b += RAND_THREADS)
+            if (count[b]) atomicAdd(a.bin_count + first + b, count[b]);
+        __syncthreads();
+    }
+}
+
 __global__ __launch_bounds__(1024) void rand_scan_kernel(const uint32_t *count, int64_t nb, uint32_t *offset,
                                                          uint32_t *cursor) {
     __shared__ uint32_t wsum[16];
@@ -71,17 +109,23 @@ __global__ __launch_bounds__(1024) void rand_scan_kernel(const uint32_t *count, 
     if (threadIdx.x == 0) offset[nb] = carry;
 }
 
-__global__ __launch_bounds__(256) void rand_scatter_kernel(const ShootArgs a) {
-    const int64_t W = a.i1 - a.i0;
-    const int64_t n = (a.jc1 - a.jc0) * W;
-    for (int64_t rel = blockIdx.x * (int64_t)256 + threadIdx.x; rel < n; rel += (int64_t)gridDim.x * 256) {
-        const int64_t i = a.i0 + rel % W, j = a.jc0 + rel / W;
-        double x1, x2;
-        random_ray_xy(a.sx0, a.sy0, a.sw, a.sh, a.nx, a.seed, i, j, x1, x2);
-        const uint32_t slot = atomicAdd(a.bin_cursor + bin_of(a, x1, x2), 1u);
-        a.ray_rel[slot] = (uint32_t)rel;
-        a.ray_x[slot] = x1;
-        a.ray_y[slot] = x2;
+__global__ __launch_bounds__(RAND_THREADS) void rand_scatter_kernel(const ShootArgs a) {
+    extern __shared__ uint32_t count[];
+    uint32_t *const cursor = count;   // the block's counts, then its next slots
+    const uint32_t nb = (uint32_t)(a.nbx_r * a.nby_r);
+    for (uint32_t first = 0; first < nb; first += RAND_LDS_BINS) {
+        const uint32_t bins = block_count(a, first, nb, cursor);
+        for (uint32_t b = threadIdx.x; b < bins; b += RAND_THREADS)
+            if (cursor[b]) cursor[b] = atomicAdd(a.bin_cursor + first + b, cursor[b]);
+        __syncthreads();
+        block_rays(a, [&](uint32_t rel, double x1, double x2, uint32_t bin) {
+            if (bin - first >= bins) return;
+            const uint32_t slot = atomicAdd(&cursor[bin - first], 1u);
+            a.ray_rel[slot] = rel;
+            a.ray_x[slot] = x1;
+            a.ray_y[slot] = x2;
+        });
+        __syncthreads();
     }
 }
 
@@ -297,14 +341,15 @@ hipError_t launch_shoot_random(const ShootArgs &a, int mode, hipStream_t stream)
     if (n <= 0) return hipSuccess;
     hipError_t e = launch_zero(a.bin_count, nb, stream);
     if (e != hipSuccess) return e;
-    const int64_t want = (n + 255) / 256;
-    const int blocks = (int)(want < 8192 ? want : 8192);
-    hipLaunchKernelGGL(rand_count_kernel, dim3(blocks), dim3(256), 0, stream, a);
+    const int64_t want = (n + RAND_BLOCK_RAYS - 1) / RAND_BLOCK_RAYS;
+    const int blocks = (int)(want < RAND_BLOCKS ? want : RAND_BLOCKS);
+    const size_t lds = sizeof(uint32_t) * (size_t)(nb < RAND_LDS_BINS ? nb : RAND_LDS_BINS);
+    hipLaunchKernelGGL(rand_count_kernel, dim3(blocks), dim3(RAND_THREADS), lds, stream, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(rand_scan_kernel, dim3(1), dim3(1024), 0, stream, (const uint32_t *)a.bin_count, nb,
                        a.bin_offset, a.bin_cursor);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(rand_scatter_kernel, dim3(blocks), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(rand_scatter_kernel, dim3(blocks), dim3(RAND_THREADS), lds, stream, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const bool unit = a.lens_m == nullptr;
     const bool pix = a.pix_out != nullptr;
