@@ -997,7 +997,7 @@ __global__ __launch_bounds__(256, 4) void recheck_far_kernel(const ShootArgs a, 
                 todo &= todo - 1;
                 const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
                 int c = 0;
-                const bool decided = fast_ray_wave<UNIT>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c);
+                const bool decided = fast_ray_wave<UNIT, 4>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c);
                 if (lane == src) {
                     if (decided) {
                         code = c;

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void recheck_fast_wave_kernel(const RecheckArg
             const int64_t i = a.i0 + (int64_t)(q % (uint64_t)W);
             const int64_t j = a.jc0 + (int64_t)(q / (uint64_t)W);
             int code = 0;
-            const bool decided = fast_ray_wave<UNIT>(a, i, j, code);
+            const bool decided = fast_ray_wave<UNIT, 8>(a, i, j, code);
             if (lane == src) {
                 if (decided) {
                     tally(code, n_in, n_out, n_sing);
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void recheck_defer_kernel(const RecheckArgs a)
 // them out one per wave (marked in place, two of them could fall to one wave and its time
 // would double).
 constexpr int STAGE_A_RAYS = 2;
-template <bool UNIT, int R>
+template <bool UNIT, int R, int U>
 __device__ __forceinline__ void fast_deferred(const RecheckArgs &a, uint32_t n, uint32_t wave_id, uint32_t n_waves) {
     for (uint32_t e = wave_id * R; e < n; e += n_waves * R) {
         int64_t i[R], j[R];
@@ -226,7 +226,7 @@ __device__ __forceinline__ void fast_deferred(const RecheckArgs &a, uint32_t n, 
             i[r] = a.defer[2 * k];
             j[r] = a.defer[2 * k + 1];
         }
-        fast_rays_wave<UNIT, R>(a, i, j, decided, code);
+        fast_rays_wave<UNIT, R, U>(a, i, j, decided, code);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (__lane_id() != 0 || e + r >= n) continue;
@@ -247,8 +247,8 @@ __global__ __launch_bounds__(256) void recheck_fast_deferred_kernel(const Rechec
     if (blockIdx.x == 0 && threadIdx.x == 0 && n) atomicAdd(a.counters + C_DIRECT, (unsigned long long)n);
     const uint32_t wave_id = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
     const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
-    if (n <= n_waves) fast_deferred<UNIT, 1>(a, n, wave_id, n_waves);
-    else fast_deferred<UNIT, STAGE_A_RAYS>(a, n, wave_id, n_waves);
+    if (n <= n_waves) fast_deferred<UNIT, 1, 8>(a, n, wave_id, n_waves);
+    else fast_deferred<UNIT, STAGE_A_RAYS, 4>(a, n, wave_id, n_waves);
 }
 
 // The exact stage over the gathered rays stage A left, one wave per ray.
@@ -364,7 +364,7 @@ __device__ inline void batch_stage_a_wave(const BatchArgs &b, QueueEntry e) {
     const int64_t i = a.i0 + (int64_t)(e.ray % (uint64_t)W);
     const int64_t j = a.j0 + (int64_t)(e.ray / (uint64_t)W);
     int code = CODE_OUT;
-    const bool ok = a.lens_m == nullptr ? fast_ray_wave<true>(a, i, j, code) : fast_ray_wave<false>(a, i, j, code);
+    const bool ok = a.lens_m == nullptr ? fast_ray_wave<true, 4>(a, i, j, code) : fast_ray_wave<false, 4>(a, i, j, code);
     if (__lane_id() == 0) {
         if (ok) {
             if (code >= 0) atomicAdd(a.map + code, 1u);

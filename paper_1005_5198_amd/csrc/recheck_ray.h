@@ -367,7 +367,7 @@ __device__ inline bool fast_ray(const RecheckArgs &a, int64_t i, int64_t j, int 
 // lanes' running sums are added over the wave to give the partial sum at the block's end, whose
 // magnitudes feed block_bound; the totals meet in the same butterfly. Every lane returns the
 // same result.
-template <bool UNIT, int R>
+template <bool UNIT, int R, int U>
 __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R], const int64_t (&j)[R],
                                       bool (&decided)[R], int (&code)[R]) {
     double x1[R], x2[R], a1[R], a2[R], S[R], Q1[R], Q2[R];
@@ -384,10 +384,9 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
     // dropped, so the loop has no branches per lane and the compiler can count the loads
     // in flight. Four lenses share one reciprocal (v_rcp_f64 issues like four
     // FMAs, and its Newton steps are four more; sharing takes nine products).
-    constexpr int U = 8;
     // (a block's butterfly takes as long as its 16 lenses per lane; where there are many
     // lenses, blocks of 4096 add little to the bound)
-    const int L = a.n_lens < (1 << 18) ? 2 : 8;
+    const int L = (a.n_lens < (1 << 18) ? 16 : 64) / U;
     const double B = 64.0 * U * L;
     double LX[U], LY[U], LM[U];
     const int lane = __lane_id();
@@ -484,12 +483,13 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
     }
 }
 
-template <bool UNIT>
+// U: 8 where a kernel has the registers (a lone wave waits less for its lenses), 4 elsewhere.
+template <bool UNIT, int U>
 __device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j, int &code) {
     const int64_t ri[1] = {i}, rj[1] = {j};
     bool decided[1];
     int c[1] = {code};
-    fast_rays_wave<UNIT, 1>(a, ri, rj, decided, c);
+    fast_rays_wave<UNIT, 1, U>(a, ri, rj, decided, c);
     code = c[0];
     return decided[0];
 }
