@@ -311,6 +311,22 @@ __global__ __launch_bounds__(FAR_THREADS) void farfield_super_kernel(const Shoot
     build_super<UNIT>(a, blockIdx.x, sm);
 }
 
+// Records and the map's zeroing in one launch: the first n_super blocks build the records,
+// the others clear the map and the workspace's words.
+template <bool UNIT>
+__global__ __launch_bounds__(FAR_THREADS) void fill_records_kernel(const ShootArgs a, uint32_t n_super, uint32_t *map,
+                                                                   int64_t n_pix, uint32_t *ws_words, int64_t n_ws_words) {
+    __shared__ FarSuperSmem sm;
+    if (blockIdx.x < n_super) {
+        build_super<UNIT>(a, blockIdx.x, sm);
+        return;
+    }
+    const int64_t t0 = (int64_t)(blockIdx.x - n_super) * FAR_THREADS + threadIdx.x;
+    const int64_t stride = (int64_t)(gridDim.x - n_super) * FAR_THREADS;
+    for (int64_t t = t0; t < n_pix; t += stride) map[t] = 0u;
+    for (int64_t t = t0; t < n_ws_words; t += stride) ws_words[t] = 0u;
+}
+
 // Blocks that scan one group's lenses: one per 8192 lenses, at most FF_GROUP_PARTS.
 __host__ __device__ inline int group_parts(int64_t n_lens) {
     return n_lens / 8192 + 1 < FF_GROUP_PARTS ? (int)(n_lens / 8192 + 1) : FF_GROUP_PARTS;
@@ -963,12 +979,14 @@ constexpr uint32_t FAR_WAVE_MAX = 32768;
 
 // Re-check stage F of the mixed mode (far_recheck_ray), one thread or one wave per
 // queued ray. A ray it places is binned. STAGE_A: the others take stage A at once, one
-// wave per ray, and are marked UNRESOLVED when that cannot place them either;
+// wave per ray, and are marked UNRESOLVED when that cannot place them either (or, with
+// few lenses, take stage B at once: its kernel, which mostly finds nothing to do, costs 5 us
+// of the 108 of the 1024^2-ray, 462-lens map);
 // otherwise a ray it places is marked RESOLVED, and the others are counted in *qlive and
 // left for the stages over every lens. Queue entries of one deflection block are
 // adjacent and share a super-patch, so a wave walks one list.
 template <bool UNIT, bool STAGE_A>
-__global__ __launch_bounds__(256, 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
+__global__ __launch_bounds__(256, STAGE_A ? 3 : 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
     __shared__ uint32_t sums[3];   // rays in the map, out, left
     const uint32_t n = *a.qcount;
     if (n == 0) return;
@@ -997,10 +1015,15 @@ __global__ __launch_bounds__(256, 4) void recheck_far_kernel(const ShootArgs a, 
                 todo &= todo - 1;
                 const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
                 int c = 0;
-                const bool decided = fast_ray_wave<UNIT, 4>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c);
+                const int64_t is = a.i0 + (int64_t)(qs % W), js = a.jc0 + (int64_t)(qs / W);
+                const bool decided = fast_ray_wave<UNIT, 4>(r, is, js, c);
+                const bool exact = !decided && r.n_lens <= EXACT_INLINE_LENSES;
+                if (exact) c = exact_ray_wave<UNIT, 1>(r, is, js);
                 if (lane == src) {
                     if (decided) {
                         code = c;
+                    } else if (exact) {
+                        emit_ray(r, is, js, c);
                     } else {
                         a.queue[idx] = q | UNRESOLVED;
                         atomicAdd(r.qunres, 1u);
@@ -1031,14 +1054,34 @@ __global__ __launch_bounds__(256, 4) void recheck_far_kernel(const ShootArgs a, 
 
 }  // namespace
 
-hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t *qlive, bool stage_a, int64_t max_rays,
-                              hipStream_t stream) {
+static int64_t super_patches(const ShootArgs &a) {
+    const int64_t nby = (a.jc1 - a.jc0 + PATCH_Y - 1) / PATCH_Y;
+    return a.ff_sbx * ((nby + FF_SP_Y - 1) / FF_SP_Y);
+}
+
+hipError_t launch_fill_records(const ShootArgs &a, uint32_t *map, int64_t n_pix, void *workspace, int64_t n_qcount,
+                               hipStream_t stream) {
+    const int64_t n_super = super_patches(a);
+    const int64_t n_ws_words = (int64_t)(WS_QCOUNT / 4) + n_qcount;
+    const int64_t work = map && n_pix > n_ws_words ? n_pix : n_ws_words;
+    int64_t blocks = (work + FAR_THREADS - 1) / FAR_THREADS;
+    if (blocks > 4096) blocks = 4096;
+    const dim3 grid((unsigned)(n_super + blocks));
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(FAR_THREADS), 0, stream, a, (uint32_t)n_super, map, map ? n_pix : 0,
+                           static_cast<uint32_t *>(workspace), n_ws_words);
+    };
+    if (a.lens_m == nullptr) launch(fill_records_kernel<true>);
+    else launch(fill_records_kernel<false>);
+    return hipGetLastError();
+}
+
+hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t *qlive, bool stage_a, bool records,
+                              int64_t max_rays, hipStream_t stream) {
     if (max_rays <= 0) return hipSuccess;
     const bool unit = a.lens_m == nullptr;
-    if (!a.random) {   // grid: this launch's records (random rays: the map's, built once)
-        const int64_t rows = a.jc1 - a.jc0;
-        const int64_t nby = (rows + PATCH_Y - 1) / PATCH_Y;
-        const int64_t n_super = a.ff_sbx * ((nby + FF_SP_Y - 1) / FF_SP_Y);
+    if (records) {
+        const int64_t n_super = super_patches(a);
         if (n_super <= 0) return hipSuccess;
         if (unit) hipLaunchKernelGGL((farfield_super_kernel<true, true>), dim3((unsigned)n_super), dim3(FAR_THREADS), 0, stream, a);
         else hipLaunchKernelGGL((farfield_super_kernel<false, true>), dim3((unsigned)n_super), dim3(FAR_THREADS), 0, stream, a);

@@ -484,6 +484,7 @@ hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_onl
         if (unit) hipLaunchKernelGGL(recheck_exact_kernel<true>, grid, block, 0, stream, a);
         else hipLaunchKernelGGL(recheck_exact_kernel<false>, grid, block, 0, stream, a);
     } else if (stage_a_done) {
+        if (a.n_lens <= EXACT_INLINE_LENSES) return hipSuccess;   // stage B as well
         const dim3 few((unsigned)(blocks < 512 ? blocks : 512));   // it mostly finds nothing to do
         if (unit) hipLaunchKernelGGL(recheck_exact_wave_kernel<true>, few, block, 0, stream, a);
         else hipLaunchKernelGGL(recheck_exact_wave_kernel<false>, few, block, 0, stream, a);

@@ -214,7 +214,10 @@ __device__ __forceinline__ double add_in_order(double s, const double (&t)[J], O
 // 4.7 ms (the slowest ray, whose sum stays near zero; 2.2 ms without its starts over)
 // against 9.8 ms for the chain of dependent additions alone.
 constexpr int EXACT_J = 8;
-template <bool UNIT>
+// Maps of at most this many lenses run it in stage A's kernel, one lens per lane at a time
+// (there are no registers for more), at most 32 times.
+constexpr int64_t EXACT_INLINE_LENSES = 2048;
+template <bool UNIT, int J = EXACT_J>
 __device__ inline int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j) {
     const int lane = __lane_id();
     double x1, x2;
@@ -225,22 +228,22 @@ __device__ inline int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j)
     // terms are replaced by zero, which adds nothing: the running sums start at +0 and
     // never become -0), and the next lenses are loaded while these are summed.
     const int64_t last = a.n_lens - 1;
-    double X[EXACT_J], Y[EXACT_J], M[EXACT_J];
+    double X[J], Y[J], M[J];
     auto load = [&](int64_t k0) {
 #pragma unroll
-        for (int u = 0; u < EXACT_J; ++u) {
+        for (int u = 0; u < J; ++u) {
             const int64_t k = k0 + u < a.n_lens ? k0 + u : last;
             X[u] = lens_x(a, k);
             Y[u] = lens_y(a, k);
             M[u] = UNIT ? 1.0 : lens_mass(a, k);
         }
     };
-    if (a.n_lens > 0) load((int64_t)lane * EXACT_J);
-    for (int64_t k0 = 0; k0 < a.n_lens; k0 += 64 * EXACT_J) {
-        const int64_t mine = k0 + (int64_t)lane * EXACT_J;
-        double t1[EXACT_J], t2[EXACT_J];
+    if (a.n_lens > 0) load((int64_t)lane * J);
+    for (int64_t k0 = 0; k0 < a.n_lens; k0 += 64 * J) {
+        const int64_t mine = k0 + (int64_t)lane * J;
+        double t1[J], t2[J];
 #pragma unroll
-        for (int u = 0; u < EXACT_J; ++u) {
+        for (int u = 0; u < J; ++u) {
             const double d1 = x1 - X[u];
             const double d2 = x2 - Y[u];
             const double r2 = d1 * d1 + d2 * d2;
@@ -250,7 +253,7 @@ __device__ inline int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j)
             t1[u] = real ? f * d1 : 0.0;
             t2[u] = real ? f * d2 : 0.0;
         }
-        load(mine + 64 * EXACT_J);
+        load(mine + 64 * J);
         const OrderedRound o1 = ordered_round(a1, t1, 0), o2 = ordered_round(a2, t2, 0);
         a1 = add_in_order(a1, t1, o1);
         a2 = add_in_order(a2, t2, o2);

@@ -268,12 +268,15 @@ hipError_t launch_shoot_random(const ShootArgs &a, int mode, hipStream_t stream)
 hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_only, bool stage_a_done, hipStream_t stream);
 // The exact stage of the rays a map's launches gathered in a.defer.
 hipError_t launch_recheck_deferred(const RecheckArgs &a, hipStream_t stream);
-// Mixed mode: the super-patch expansions of the launch (regular grid), then the
+// launch_fill and the super-patch records of a map's one launch together.
+hipError_t launch_fill_records(const ShootArgs &a, uint32_t *map, int64_t n_pix, void *workspace, int64_t n_qcount,
+                               hipStream_t stream);
+// Mixed mode: with records the super-patch expansions of the launch (regular grid), then the
 // far-field re-check stage over the queue (a.queue, a.qcount). With stage_a the
 // rays it cannot place go to stage A at once and the two kernels count in r's
 // map; otherwise they are counted in *qlive and stay in the queue.
-hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t *qlive, bool stage_a, int64_t max_rays,
-                              hipStream_t stream);
+hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t *qlive, bool stage_a, bool records,
+                              int64_t max_rays, hipStream_t stream);
 // Records of n_super super-patches from origin (a.ff_i0, a.ff_j0), unconditionally
 // (random rays: the whole rectangle, once per map).
 hipError_t launch_super_records(const ShootArgs &a, int64_t n_super, hipStream_t stream);

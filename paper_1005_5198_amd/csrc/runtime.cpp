@@ -164,10 +164,6 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
     Range range(pix ? "rs_ray_pixels" : "rs_make_map");
 
     const bool accumulate = (p->flags & RS_ACCUMULATE) != 0;
-    hipError_t e =
-        launch_fill((map && !accumulate) ? map : nullptr, p->npx * p->npy, workspace, 4 * pl.n_chunks + 2, stream);
-    if (e != hipSuccess) return hip_fail(e, "fill kernel");
-
     char *ws = static_cast<char *>(workspace);
     ShootArgs a{};
     a.sx0 = p->sx0;
@@ -260,12 +256,29 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
                 a.ff_tlist = reinterpret_cast<int32_t *>(ws + pl.ff_tlist_off);
             }
         }
-        if (pl.random) {
-            a.ff_i0 = 0;
-            a.ff_j0 = 0;
-            e = launch_super_records(a, pl.super_cap, stream);
-            if (e != hipSuccess) return hip_fail(e, "super-patch records");
-        }
+    }
+    // A small map's records are built by the launch that clears it, not by one of their own
+    // (1024^2 rays, 462 lenses: 5 of 108 us). A large map's follow its deflection launch, which
+    // mostly takes as long as many such launches, and only if that left rays to re-check.
+    constexpr int64_t FILL_RECORDS_PATCHES = 4096;
+    const bool fill_records = pl.far_recheck && !pl.random && pl.n_chunks == 1 &&
+                              a.nbx * ((pl.H + PATCH_Y - 1) / PATCH_Y) <= FILL_RECORDS_PATCHES;
+    uint32_t *const clear = (map && !accumulate) ? map : nullptr;
+    hipError_t e;
+    if (fill_records) {
+        a.ff_i0 = a.i0;
+        a.ff_j0 = a.jc0 = p->j0;
+        a.jc1 = p->j1;
+        e = launch_fill_records(a, clear, p->npx * p->npy, workspace, 4 * pl.n_chunks + 2, stream);
+    } else {
+        e = launch_fill(clear, p->npx * p->npy, workspace, 4 * pl.n_chunks + 2, stream);
+    }
+    if (e != hipSuccess) return hip_fail(e, "fill kernel");
+    if (pl.far_recheck && pl.random && pl.n_chunks > 0) {
+        a.ff_i0 = 0;
+        a.ff_j0 = 0;
+        e = launch_super_records(a, pl.super_cap, stream);
+        if (e != hipSuccess) return hip_fail(e, "super-patch records");
     }
     if (shape < 0 && !pl.random && p->mode != RS_FARFIELD)
         shape = choose_shape(p->mode, lens_m == nullptr, n_lens, (pl.W + PATCH_X - 1) / PATCH_X * ((pl.H + PATCH_Y - 1) / PATCH_Y));
@@ -322,7 +335,7 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
             if (pl.far_recheck) {
                 uint32_t *qlive = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + pl.n_chunks + c;
                 r.qlive = qlive;
-                e = launch_recheck_far(a, r, qlive, !pl.defer, (a.jc1 - a.jc0) * pl.W, stream);
+                e = launch_recheck_far(a, r, qlive, !pl.defer, !pl.random && !fill_records, (a.jc1 - a.jc0) * pl.W, stream);
                 if (e != hipSuccess) return hip_fail(e, "far-field re-check kernel");
             }
             e = launch_recheck(r, (a.jc1 - a.jc0) * pl.W, (p->flags & RS_EXACT_RECHECK) != 0,
