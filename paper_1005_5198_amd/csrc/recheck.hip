@@ -55,10 +55,10 @@ __device__ inline void place(const RecheckArgs &a, int64_t i, int64_t j, int cod
 
 // ----------------------------- single map ---------------------------------
 
-// Below this many queued rays stage A runs one wave per ray (latency: a few
+// Below this many queued rays stage A runs one block per ray (latency: a few
 // rays must not each take a thread through every lens); above it, one thread
-// per ray (throughput). Each of the two kernels checks the count on the device.
-constexpr uint32_t WAVE_STAGE_MAX = 32768;
+// per ray (throughput). The kernel checks the count on the device.
+constexpr uint32_t BLOCK_STAGE_MAX = 32768;
 
 template <bool UNIT>
 __global__ __launch_bounds__(256) void recheck_exact_kernel(const RecheckArgs a) {
@@ -81,69 +81,58 @@ __global__ __launch_bounds__(256) void recheck_exact_kernel(const RecheckArgs a)
     }
 }
 
+// Stage A over a launch's queue. Few live entries: entries are dealt to the blocks 64 at a
+// time (lane l of each wave of block k reads entry k + (t + l) n_blocks), so a
+// long queue whose entries the far-field stage mostly decided costs each block
+// a few vector loads, and neighbouring live rays go to different blocks. (One wave per ray
+// took 27 us for the 14 rays of the 19200 x 3840-ray, 17240-lens far-field map, and a kernel
+// for each form 4.6 us more.)
 template <bool UNIT>
 __global__ __launch_bounds__(256) void recheck_fast_kernel(const RecheckArgs a) {
+    constexpr int WAVES = 4;
+    __shared__ FastSums part[WAVES];
     const uint32_t n = *a.qcount;
     const uint32_t live = a.qlive ? *a.qlive : n;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (n) atomicAdd(a.counters + C_RECHECK, (unsigned long long)n);
         if (live) atomicAdd(a.counters + C_DIRECT, (unsigned long long)live);
     }
-    if (live < WAVE_STAGE_MAX) return;   // recheck_fast_wave_kernel takes short queues
+    if (live == 0) return;
     const int64_t W = a.i1 - a.i0;
     unsigned long long n_in = 0, n_out = 0, n_sing = 0;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += stride) {
-        const uint32_t q = a.queue[idx];
-        if (q & RESOLVED) continue;
-        const int64_t i = a.i0 + (int64_t)(q % (uint64_t)W);
-        const int64_t j = a.jc0 + (int64_t)(q / (uint64_t)W);
-        int code;
-        if (fast_ray<UNIT>(a, i, j, code)) {
+    auto record = [&](uint32_t idx, uint32_t q, bool decided, int code) __attribute__((always_inline)) {
+        if (decided) {
             tally(code, n_in, n_out, n_sing);
-            place(a, i, j, code);
+            place(a, a.i0 + (int64_t)(q % (uint64_t)W), a.jc0 + (int64_t)(q / (uint64_t)W), code);
         } else {
             a.queue[idx] = q | UNRESOLVED;
             if (a.qunres) atomicAdd(a.qunres, 1u);
         }
-    }
-    count_wave(a.counters, n_in, n_out, n_sing);
-}
-
-// Stage A for few live entries: one wave per ray. Entries are dealt to the
-// waves 64 at a time (lane l of wave k reads entry k + (t + l) n_waves), so a
-// long queue whose entries the far-field stage mostly decided costs each wave
-// a few vector loads, and neighbouring live rays go to different waves.
-template <bool UNIT>
-__global__ __launch_bounds__(256) void recheck_fast_wave_kernel(const RecheckArgs a) {
-    const uint32_t n = *a.qcount;
-    const uint32_t live = a.qlive ? *a.qlive : n;
-    if (live >= WAVE_STAGE_MAX || live == 0) return;
-    const int64_t W = a.i1 - a.i0;
-    const int lane = __lane_id();
-    const uint32_t wave_id = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
-    unsigned long long n_in = 0, n_out = 0, n_sing = 0;
-    for (uint64_t t0 = 0; (uint64_t)wave_id + t0 * n_waves < n; t0 += 64) {
-        const uint64_t idx64 = (uint64_t)wave_id + (t0 + (uint64_t)lane) * n_waves;
-        const uint32_t q_lane = idx64 < n ? a.queue[idx64] : RESOLVED;
-        uint64_t todo = __ballot(!(q_lane & RESOLVED));
-        while (todo) {
-            const int src = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)q_lane, src);
-            const int64_t i = a.i0 + (int64_t)(q % (uint64_t)W);
-            const int64_t j = a.jc0 + (int64_t)(q / (uint64_t)W);
-            int code = 0;
-            const bool decided = fast_ray_wave<UNIT, 8>(a, i, j, code);
-            if (lane == src) {
-                if (decided) {
-                    tally(code, n_in, n_out, n_sing);
-                    place(a, i, j, code);
-                } else {
-                    a.queue[idx64] = q | UNRESOLVED;
-                    if (a.qunres) atomicAdd(a.qunres, 1u);
-                }
+    };
+    if (live >= BLOCK_STAGE_MAX) {
+        const uint32_t stride = gridDim.x * blockDim.x;
+        for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += stride) {
+            const uint32_t q = a.queue[idx];
+            if (q & RESOLVED) continue;
+            int code;
+            const bool decided = fast_ray<UNIT>(a, a.i0 + (int64_t)(q % (uint64_t)W), a.jc0 + (int64_t)(q / (uint64_t)W), code);
+            record(idx, q, decided, code);
+        }
+    } else {
+        const int lane = __lane_id();
+        for (uint64_t t0 = 0; blockIdx.x + t0 * gridDim.x < n; t0 += 64) {
+            const uint64_t idx = blockIdx.x + (t0 + (uint64_t)lane) * gridDim.x;
+            const uint32_t q_lane = idx < n ? a.queue[idx] : RESOLVED;
+            uint64_t todo = __ballot(!(q_lane & (RESOLVED | UNRESOLVED)));   // the same in every wave
+            __syncthreads();   // every wave has read the entries that thread `src` marks
+            while (todo) {
+                const int src = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)q_lane, src);
+                int code = 0;
+                const bool decided = fast_ray_block<UNIT, 4, WAVES>(a, a.i0 + (int64_t)(q % (uint64_t)W),
+                                                                    a.jc0 + (int64_t)(q / (uint64_t)W), part, code);
+                if ((int)threadIdx.x == src) record((uint32_t)idx, q, decided, code);
             }
         }
     }
@@ -496,11 +485,9 @@ hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_onl
         }
         if (unit) {
             hipLaunchKernelGGL(recheck_fast_kernel<true>, grid, block, 0, stream, b);
-            hipLaunchKernelGGL(recheck_fast_wave_kernel<true>, grid, block, 0, stream, b);
             hipLaunchKernelGGL(recheck_exact_wave_kernel<true>, grid, block, 0, stream, b);
         } else {
             hipLaunchKernelGGL(recheck_fast_kernel<false>, grid, block, 0, stream, b);
-            hipLaunchKernelGGL(recheck_fast_wave_kernel<false>, grid, block, 0, stream, b);
             hipLaunchKernelGGL(recheck_exact_wave_kernel<false>, grid, block, 0, stream, b);
         }
     }

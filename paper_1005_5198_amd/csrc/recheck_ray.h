@@ -365,19 +365,29 @@ __device__ inline bool fast_ray(const RecheckArgs &a, int64_t i, int64_t j, int 
                           sequential_bound(a.n_lens, S, Q2), tiny, code);
 }
 
-// Stage A by a whole wave for R rays (ray r at (i[r], j[r]), wave-uniform): lanes take every
-// 64th lens, U of them per step; every L steps (blocks of B = 64 U L lenses in lens order) the
-// lanes' running sums are added over the wave to give the partial sum at the block's end, whose
-// magnitudes feed block_bound; the totals meet in the same butterfly. Every lane returns the
-// same result.
+// Stage A's sums over steps [it0, it1) of 64 U lenses each by a whole wave, for R rays: lanes
+// take every 64th lens, U of them per step; every L steps (blocks of 64 U L lenses in lens
+// order) the lanes' running sums are added over the wave to give the partial sum at the block's
+// end, whose magnitudes add up to Q1, Q2 (for block_bound); the totals meet in the same
+// butterfly. Every lane returns the same result.
+struct FastSums {
+    double a1, a2, S, Q1, Q2;
+    bool tiny;
+};
+__device__ __forceinline__ int64_t fast_steps(const RecheckArgs &a, int U) {
+    return (a.n_lens + 64 * U - 1) / (64 * U);
+}
+// Steps per block. (A block's butterfly takes as long as its 16 lenses per lane; where there
+// are many lenses, blocks of 4096 add little to the bound.)
+__device__ __forceinline__ int fast_block(const RecheckArgs &a, int U) { return (a.n_lens < (1 << 18) ? 16 : 64) / U; }
+
 template <bool UNIT, int R, int U>
-__device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R], const int64_t (&j)[R],
-                                      bool (&decided)[R], int (&code)[R]) {
-    double x1[R], x2[R], a1[R], a2[R], S[R], Q1[R], Q2[R];
+__device__ inline void fast_sums(const RecheckArgs &a, const double (&x1)[R], const double (&x2)[R], int64_t it0,
+                                 int64_t it1, FastSums (&out)[R]) {
+    double a1[R], a2[R], S[R], Q1[R], Q2[R];
     int tiny[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        ray_xy(a, i[r], j[r], x1[r], x2[r]);
         a1[r] = a2[r] = S[r] = Q1[r] = Q2[r] = 0.0;
         tiny[r] = 0;
     }
@@ -387,15 +397,11 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
     // dropped, so the loop has no branches per lane and the compiler can count the loads
     // in flight. Four lenses share one reciprocal (v_rcp_f64 issues like four
     // FMAs, and its Newton steps are four more; sharing takes nine products).
-    // (a block's butterfly takes as long as its 16 lenses per lane; where there are many
-    // lenses, blocks of 4096 add little to the bound)
-    const int L = (a.n_lens < (1 << 18) ? 16 : 64) / U;
-    const double B = 64.0 * U * L;
+    const int L = fast_block(a, U);
     double LX[U], LY[U], LM[U];
     const int lane = __lane_id();
     const int64_t last = a.n_lens - 1;
     const int64_t full = a.n_lens / (64 * U);                   // steps without a remainder
-    const int64_t steps = (a.n_lens + 64 * U - 1) / (64 * U);   // (both the same for every lane)
     auto load = [&](int64_t it) {
         const int64_t k0 = 64 * U * it + lane;
         if (it < full) {
@@ -420,8 +426,8 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
         return v;
     };
-    if (a.n_lens > 0) load(0);
-    for (int64_t it = 0; it < steps; ++it) {
+    if (it0 < it1) load(it0);
+    for (int64_t it = it0; it < it1; ++it) {
         double X[U], Y[U], M[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -429,7 +435,7 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
             Y[u] = LY[u];
             M[u] = LM[u];
         }
-        if (it + 1 < steps) load(it + 1);
+        if (it + 1 < it1) load(it + 1);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             double d1[U], d2[U], r2[U], rc[U];
@@ -467,7 +473,7 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
                 S[r] = __builtin_fma(fabs(d1[u]) + fabs(d2[u]), fabs(rc[u]), S[r]);
             }
         }
-        if ((it & (L - 1)) == L - 1 || it == steps - 1) {   // a block's end: its partial sums
+        if (((it - it0) & (L - 1)) == L - 1 || it == it1 - 1) {   // a block's end: its partial sums
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 Q1[r] += fabs(wave_sum(a1[r]));
@@ -475,15 +481,61 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
             }
         }
     }
-    // a partial sum's depth: a lane's running sum plus the six butterfly levels
-    const double depth = (double)steps * U + 6.0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double t1 = wave_sum(a1[r]), t2 = wave_sum(a2[r]), s = wave_sum(S[r]);
-        const bool t = __ballot(tiny[r]) != 0;
-        decided[r] = stage_a_decide(a, x1[r], x2[r], t1, t2, s, block_bound(a.n_lens, s, Q1[r], B, depth),
-                                    block_bound(a.n_lens, s, Q2[r], B, depth), t, code[r]);
+    for (int r = 0; r < R; ++r)
+        out[r] = FastSums{wave_sum(a1[r]), wave_sum(a2[r]), wave_sum(S[r]), Q1[r], Q2[r], __ballot(tiny[r]) != 0};
+}
+
+// Stage A by a whole wave for R rays, ray r at (i[r], j[r]) (wave-uniform).
+template <bool UNIT, int R, int U>
+__device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R], const int64_t (&j)[R],
+                                      bool (&decided)[R], int (&code)[R]) {
+    double x1[R], x2[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) ray_xy(a, i[r], j[r], x1[r], x2[r]);
+    const int64_t steps = fast_steps(a, U);
+    FastSums f[R];
+    fast_sums<UNIT, R, U>(a, x1, x2, 0, steps, f);
+    // a partial sum's depth: a lane's running sum plus the six butterfly levels
+    const double depth = (double)steps * U + 6.0, B = 64.0 * U * fast_block(a, U);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        decided[r] = stage_a_decide(a, x1[r], x2[r], f[r].a1, f[r].a2, f[r].S,
+                                    block_bound(a.n_lens, f[r].S, f[r].Q1, B, depth),
+                                    block_bound(a.n_lens, f[r].S, f[r].Q2, B, depth), f[r].tiny, code[r]);
+}
+
+// Stage A by a block of WAVES waves for one ray (i, j block-uniform), each wave over one range
+// of the lenses: a partial sum is the total of the ranges before plus the range's own, and its
+// magnitude at most the sum of theirs. part: WAVES entries of shared memory, free on entry.
+template <bool UNIT, int U, int WAVES>
+__device__ inline bool fast_ray_block(const RecheckArgs &a, int64_t i, int64_t j, FastSums *part, int &code) {
+    double x1[1], x2[1];
+    ray_xy(a, i, j, x1[0], x2[0]);
+    const int wave = threadIdx.x >> 6;
+    const int64_t steps = fast_steps(a, U), per = (steps + WAVES - 1) / WAVES;
+    const int L = fast_block(a, U);
+    auto bound = [&](int w) { return w * per < steps ? w * per : steps; };
+    FastSums f[1];
+    fast_sums<UNIT, 1, U>(a, x1, x2, bound(wave), bound(wave + 1), f);
+    if (__lane_id() == 0) part[wave] = f[0];
+    __syncthreads();
+    FastSums t{0.0, 0.0, 0.0, 0.0, 0.0, false};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const FastSums p = part[w];
+        const double blocks = (double)((bound(w + 1) - bound(w) + L - 1) / L);
+        t.Q1 += blocks * fabs(t.a1) + p.Q1;
+        t.Q2 += blocks * fabs(t.a2) + p.Q2;
+        t.a1 += p.a1;
+        t.a2 += p.a2;
+        t.S += p.S;
+        t.tiny |= p.tiny;
     }
+    __syncthreads();
+    const double depth = (double)per * U + 6.0 + WAVES, B = 64.0 * U * L;
+    return stage_a_decide(a, x1[0], x2[0], t.a1, t.a2, t.S, block_bound(a.n_lens, t.S, t.Q1, B, depth),
+                          block_bound(a.n_lens, t.S, t.Q2, B, depth), t.tiny, code);
 }
 
 // U: 8 where a kernel has the registers (a lone wave waits less for its lenses), 4 elsewhere.
