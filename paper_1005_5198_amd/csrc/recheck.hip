@@ -5,19 +5,22 @@
 //   stage F (far_ray.h, farfield.hip): the ray's super-patch FP64 expansion
 //     plus the lenses listed near the super-patch, under a rigorous bound; it
 //     places all but a few queued rays;
-//   stage A (fast_ray): FP64 over every lens with fused multiply-adds and a
+//   stage A (fast_ray, fast_rays_wave, fast_ray_block): FP64 over every lens with
+//     fused multiply-adds and a
 //     bound that also covers the definition's own FP64 rounding; it decides
 //     almost every ray stage F left, identically to the definition, and marks
 //     the rest;
 //   stage B (exact_ray_wave): the marked rays, one wave per ray, with the
-//     definition's exact operation sequence.
+//     definition's operations and the roundings of its order.
 // RS_EXACT_RECHECK runs the exact sequence for every queued ray instead (one
 // thread per ray).
 //
 // Single map: the queue holds uint32 chunk-relative ray indices. Unless the
 // caller asked for the exact sequence only (or a random-ray window holds few of
-// its map's rays), the far-field stage (farfield.hip) runs first and marks the entries it decided RESOLVED; stage A skips them and
-// picks its form from the number left (*qlive).
+// its map's rays), the far-field stage (farfield.hip) runs first. In a map of one
+// launch its kernel takes its rays through stage A as well; otherwise it marks the
+// entries it decided RESOLVED, and stage A skips them and picks its form from the
+// number left (*qlive).
 // Batch: the deflection kernel sets one bit per flagged ray in each map's
 // bitmap; a persistent scan compacts the set bits per wave and the map's
 // descriptor supplies its parameters and its super-patch records (stage F).
