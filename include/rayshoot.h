@@ -230,7 +230,7 @@ typedef struct {
 
 /*
  * Time every shape on a sample of this map (a band of rows from the middle of
- * the window holding about sample_rays rays; <= 0 picks 2^22) and remember the
+ * the window holding about sample_rays rays; <= 0 picks 2^24) and remember the
  * fastest for maps with the same signature (mode, unit or general masses,
  * N* rounded down to a power of two, the window's 64 x 32-ray patches rounded
  * down to a power of two). Later rs_make_map calls with that signature use it.

@@ -161,7 +161,9 @@ int rs_tune(const rs_map_params *params, const double *lens_xy, const double *le
     p.flags &= ~RS_ACCUMULATE;
     const int64_t W = p.i1 - p.i0, H = p.j1 - p.j0;
     if (W <= 0 || H <= 0) return fail(RS_EINVAL, "empty window");
-    if (sample_rays <= 0) sample_rays = int64_t(1) << 22;
+    // (2^24 rays are eight rounds of blocks; with 2^22, under two, the last round decided: 4 x 4
+    // rays per lane over 4 x 2, which is 3% faster on the 19200 x 3840-ray, 17240-lens map)
+    if (sample_rays <= 0) sample_rays = int64_t(1) << 24;
     int64_t rows = sample_rays / W;
     rows = rows / PATCH_Y * PATCH_Y;
     if (rows < PATCH_Y) rows = PATCH_Y;
