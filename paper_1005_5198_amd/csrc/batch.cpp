@@ -141,6 +141,7 @@ static int enqueue_batch(const rs_map_request *reqs, int32_t n, void *workspace,
     b.n_maps = n;
     b.mode = mode;
     b.unit_masses = unit ? 1 : 0;
+    b.max_lenses = reqs[order[0]].n_lens;
     b.total_tiles = tiles;
     b.total_words = words;
     b.total_super = supers;

@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(256, STAGE_A ? 3 : 4) void recheck_far_kernel(const
                 const int64_t is = a.i0 + (int64_t)(qs % W), js = a.jc0 + (int64_t)(qs / W);
                 const bool decided = fast_ray_wave<UNIT, 4>(r, is, js, c);
                 const bool exact = !decided && r.n_lens <= EXACT_INLINE_LENSES;
-                if (exact) c = exact_ray_wave<UNIT, 1>(r, is, js);
+                if (exact) c = exact_ray_chain<UNIT, 2, 4>(r, is, js);
                 if (lane == src) {
                     if (decided) {
                         code = c;

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void recheck_fast_kernel(const RecheckArgs a) 
     count_wave(a.counters, n_in, n_out, n_sing);
 }
 
-template <bool UNIT>
+template <bool UNIT, bool CHAIN>
 __global__ __launch_bounds__(256) void recheck_exact_wave_kernel(const RecheckArgs a) {
     if (a.qunres && *a.qunres == 0u) return;   // stage A decided every entry
     const uint32_t n = *a.qcount;
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void recheck_exact_wave_kernel(const RecheckAr
             const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)q_lane, src) & ~UNRESOLVED;
             const int64_t i = a.i0 + (int64_t)(q % (uint64_t)W);
             const int64_t j = a.jc0 + (int64_t)(q / (uint64_t)W);
-            const int code = exact_ray_wave<UNIT>(a, i, j);
+            const int code = exact_ray_wave<UNIT, CHAIN>(a, i, j);
             if (lane == 0) emit_ray(a, i, j, code);
         }
     }
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void recheck_fast_deferred_kernel(const Rechec
 }
 
 // The exact stage over the gathered rays stage A left, one wave per ray.
-template <bool UNIT>
+template <bool UNIT, bool CHAIN>
 __global__ __launch_bounds__(256) void recheck_exact_deferred_kernel(const RecheckArgs a) {
     const uint32_t n = *a.ucount;
     const int lane = __lane_id();
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void recheck_exact_deferred_kernel(const Reche
     const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t e = wave_id; e < n; e += n_waves) {
         const int64_t i = a.udefer[2 * (int64_t)e], j = a.udefer[2 * (int64_t)e + 1];
-        const int code = exact_ray_wave<UNIT>(a, i, j);
+        const int code = exact_ray_wave<UNIT, CHAIN>(a, i, j);
         if (lane == 0) emit_ray(a, i, j, code);
     }
 }
@@ -345,7 +345,6 @@ __device__ inline bool batch_stage_f(const BatchArgs &b, QueueEntry e, bool vali
     return placed;
 }
 
-// Exact stage for up to 64 entries held one per lane: one wave per ray.
 // Stage A of one queued ray (wave-uniform entry) by the whole wave: lanes split the
 // lenses. Used for a wave's last few rays, where one ray per lane would leave the
 // GPU mostly idle while each lane walks every lens.
@@ -369,6 +368,9 @@ __device__ inline void batch_stage_a_wave(const BatchArgs &b, QueueEntry e) {
     }
 }
 
+// Exact stage for up to 64 entries held one per lane: one wave per ray. CHAIN: no map has
+// more than EXACT_CHAIN_LENSES lenses.
+template <bool ALL_UNIT, bool CHAIN>
 __device__ inline void batch_stage_b(const BatchArgs &b, QueueEntry e, int n_valid) {
     const int lane = __lane_id();
     for (int s = 0; s < n_valid; ++s) {
@@ -379,7 +381,12 @@ __device__ inline void batch_stage_b(const BatchArgs &b, QueueEntry e, int n_val
         const int64_t W = a.i1 - a.i0;
         const int64_t i = a.i0 + (int64_t)(ray % (uint64_t)W);
         const int64_t j = a.j0 + (int64_t)(ray / (uint64_t)W);
-        const int code = a.lens_m == nullptr ? exact_ray_wave<true>(a, i, j) : exact_ray_wave<false>(a, i, j);
+        const bool unit = ALL_UNIT || a.lens_m == nullptr;
+        int code;
+        if (CHAIN || a.n_lens <= EXACT_CHAIN_LENSES)
+            code = unit ? exact_ray_wave<true, true>(a, i, j) : exact_ray_wave<false, true>(a, i, j);
+        else
+            code = unit ? exact_ray_parallel<true, 4>(a, i, j) : exact_ray_parallel<false, 4>(a, i, j);
         if (lane == 0) emit_ray(a, i, j, code);
     }
 }
@@ -391,7 +398,7 @@ __device__ inline void batch_stage_b(const BatchArgs &b, QueueEntry e, int n_val
 // is spread over many waves instead of queueing in one. Each wave compacts its
 // set bits into its own ring buffer in LDS and evaluates them 64 at a time, one
 // per lane. A wave leaves when its words are done and its buffer is empty.
-template <int STAGE, bool ALL_UNIT>
+template <int STAGE, bool ALL_UNIT, bool CHAIN>
 __global__ __launch_bounds__(256) void recheck_scan_batch_kernel(const BatchArgs b) {
     if (STAGE == 1 && *b.unresolved == 0u) return;
     constexpr int RING = 128;
@@ -437,7 +444,7 @@ __global__ __launch_bounds__(256) void recheck_scan_batch_kernel(const BatchArgs
                     const bool placed = batch_stage_f<ALL_UNIT>(b, e, true);
                     batch_stage_a<ALL_UNIT>(b, e, !placed);
                 }
-                else batch_stage_b(b, e, 64);
+                else batch_stage_b<ALL_UNIT, CHAIN>(b, e, 64);
             }
         }
     }
@@ -459,12 +466,23 @@ __global__ __launch_bounds__(256) void recheck_scan_batch_kernel(const BatchArgs
                 batch_stage_a_wave(b, es);
             }
         } else {
-            batch_stage_b(b, e, left);
+            batch_stage_b<ALL_UNIT, CHAIN>(b, e, left);
         }
     }
 }
 
 }  // namespace
+
+static void launch_exact_wave(const RecheckArgs &a, dim3 grid, hipStream_t stream) {
+    const dim3 block(256);
+    auto launch = [&](auto unit) {
+        constexpr bool U = decltype(unit)::value;
+        if (a.n_lens <= EXACT_CHAIN_LENSES) hipLaunchKernelGGL((recheck_exact_wave_kernel<U, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((recheck_exact_wave_kernel<U, false>), grid, block, 0, stream, a);
+    };
+    if (a.lens_m == nullptr) launch(std::true_type{});
+    else launch(std::false_type{});
+}
 
 hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_only, bool stage_a_done, hipStream_t stream) {
     int64_t blocks = (max_rays + 255) / 256;
@@ -478,44 +496,47 @@ hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_onl
     } else if (stage_a_done) {
         if (a.n_lens <= EXACT_INLINE_LENSES) return hipSuccess;   // stage B as well
         const dim3 few((unsigned)(blocks < 512 ? blocks : 512));   // it mostly finds nothing to do
-        if (unit) hipLaunchKernelGGL(recheck_exact_wave_kernel<true>, few, block, 0, stream, a);
-        else hipLaunchKernelGGL(recheck_exact_wave_kernel<false>, few, block, 0, stream, a);
+        launch_exact_wave(a, few, stream);
     } else {
         RecheckArgs b = a;
         if (a.defer) {
             hipLaunchKernelGGL(recheck_defer_kernel, grid, block, 0, stream, a);
             b.qlive = a.qleft;   // stage A of this launch takes what was not gathered
         }
-        if (unit) {
-            hipLaunchKernelGGL(recheck_fast_kernel<true>, grid, block, 0, stream, b);
-            hipLaunchKernelGGL(recheck_exact_wave_kernel<true>, grid, block, 0, stream, b);
-        } else {
-            hipLaunchKernelGGL(recheck_fast_kernel<false>, grid, block, 0, stream, b);
-            hipLaunchKernelGGL(recheck_exact_wave_kernel<false>, grid, block, 0, stream, b);
-        }
+        if (unit) hipLaunchKernelGGL(recheck_fast_kernel<true>, grid, block, 0, stream, b);
+        else hipLaunchKernelGGL(recheck_fast_kernel<false>, grid, block, 0, stream, b);
+        launch_exact_wave(b, grid, stream);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_recheck_deferred(const RecheckArgs &a, hipStream_t stream) {
     const dim3 grid(1024), block(256);
-    if (a.lens_m == nullptr) {
-        hipLaunchKernelGGL(recheck_fast_deferred_kernel<true>, grid, block, 0, stream, a);
-        hipLaunchKernelGGL(recheck_exact_deferred_kernel<true>, grid, block, 0, stream, a);
-    } else {
-        hipLaunchKernelGGL(recheck_fast_deferred_kernel<false>, grid, block, 0, stream, a);
-        hipLaunchKernelGGL(recheck_exact_deferred_kernel<false>, grid, block, 0, stream, a);
-    }
+    auto launch = [&](auto unit) {
+        constexpr bool U = decltype(unit)::value;
+        hipLaunchKernelGGL(recheck_fast_deferred_kernel<U>, grid, block, 0, stream, a);
+        if (a.n_lens <= EXACT_CHAIN_LENSES) hipLaunchKernelGGL((recheck_exact_deferred_kernel<U, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((recheck_exact_deferred_kernel<U, false>), grid, block, 0, stream, a);
+    };
+    if (a.lens_m == nullptr) launch(std::true_type{});
+    else launch(std::false_type{});
     return hipGetLastError();
 }
 
 hipError_t launch_recheck_batch(const BatchArgs &b, hipStream_t stream) {
     if (b.total_words <= 0) return hipSuccess;
     const dim3 grid(2048), block(256);
-    // stage A in a kernel of its own for batches of unit-mass maps only (fewer registers)
-    if (b.unit_masses) hipLaunchKernelGGL((recheck_scan_batch_kernel<0, true>), grid, block, 0, stream, b);
-    else hipLaunchKernelGGL((recheck_scan_batch_kernel<0, false>), grid, block, 0, stream, b);
-    hipLaunchKernelGGL((recheck_scan_batch_kernel<1, false>), grid, block, 0, stream, b);
+    // kernels of their own for batches of unit-mass maps only, and for batches whose maps all
+    // take the exact stage's chain (fewer registers)
+    const bool chain = b.max_lenses <= EXACT_CHAIN_LENSES;
+    auto launch = [&](auto unit) {
+        constexpr bool U = decltype(unit)::value;
+        hipLaunchKernelGGL((recheck_scan_batch_kernel<0, U, true>), grid, block, 0, stream, b);
+        if (chain) hipLaunchKernelGGL((recheck_scan_batch_kernel<1, U, true>), grid, block, 0, stream, b);
+        else hipLaunchKernelGGL((recheck_scan_batch_kernel<1, U, false>), grid, block, 0, stream, b);
+    };
+    if (b.unit_masses) launch(std::true_type{});
+    else launch(std::false_type{});
     return hipGetLastError();
 }
 

@@ -82,6 +82,17 @@ __device__ __forceinline__ void ray_xy(const RecheckArgs &a, int64_t i, int64_t 
     }
 }
 
+// The pixel of the ray at (x1, x2) deflected by the definition's sums (a1, a2), or CODE_OUT.
+__device__ __forceinline__ int definition_pixel(const RecheckArgs &a, double x1, double x2, double a1, double a2) {
+    const double y1 = ((1.0 - a.gamma) - a.sigma_c) * x1 - a1;
+    const double y2 = ((1.0 + a.gamma) - a.sigma_c) * x2 - a2;
+    const double u = (y1 - a.tx0) / (a.tw / (double)a.npx);
+    const double v = (y2 - a.ty0) / (a.th / (double)a.npy);
+    if (isfinite(u) && isfinite(v) && u >= 0.0 && u < (double)a.npx && v >= 0.0 && v < (double)a.npy)
+        return (int)((int64_t)floor(v) * a.npx + (int64_t)floor(u));
+    return CODE_OUT;
+}
+
 template <bool UNIT>
 __device__ inline int exact_ray_thread(const RecheckArgs &a, int64_t i, int64_t j) {
     double x1, x2;
@@ -97,13 +108,7 @@ __device__ inline int exact_ray_thread(const RecheckArgs &a, int64_t i, int64_t 
         a1 += f * d1;
         a2 += f * d2;
     }
-    const double y1 = ((1.0 - a.gamma) - a.sigma_c) * x1 - a1;
-    const double y2 = ((1.0 + a.gamma) - a.sigma_c) * x2 - a2;
-    const double u = (y1 - a.tx0) / (a.tw / (double)a.npx);
-    const double v = (y2 - a.ty0) / (a.th / (double)a.npy);
-    if (isfinite(u) && isfinite(v) && u >= 0.0 && u < (double)a.npx && v >= 0.0 && v < (double)a.npy)
-        return (int)((int64_t)floor(v) * a.npx + (int64_t)floor(u));
-    return CODE_OUT;
+    return definition_pixel(a, x1, x2, a1, a2);
 }
 
 __device__ __forceinline__ void wave_lds_fence() {
@@ -208,17 +213,103 @@ __device__ __forceinline__ double add_in_order(double s, const double (&t)[J], O
     return s + o.total;
 }
 
-// The same definition evaluated by a whole wave for one ray (i, j wave-uniform): lanes
-// form the per-lens terms (m/r2)*d1, (m/r2)*d2 of EXACT_J consecutive lenses each, and the
-// sums add them in lens order (add_in_order). The 10^6-lens far-field map's last rays:
-// 4.7 ms (the slowest ray, whose sum stays near zero; 2.2 ms without its starts over)
-// against 9.8 ms for the chain of dependent additions alone.
-constexpr int EXACT_J = 8;
-// Maps of at most this many lenses run it in stage A's kernel, one lens per lane at a time
-// (there are no registers for more), at most 32 times.
-constexpr int64_t EXACT_INLINE_LENSES = 2048;
-template <bool UNIT, int J = EXACT_J>
-__device__ inline int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j) {
+// Stage B: the same definition evaluated by a whole wave for one ray (i, j wave-uniform),
+// in two forms; the caller picks the form by the map's lenses.
+//
+// The chain: lanes form the per-lens terms (m/r2)*d1, (m/r2)*d2 of 64 lenses at a time and
+// stage them in LDS; every lane then adds them in lens order (the same sum in every lane, so
+// no lane-to-scalar moves sit on the dependent chain). Callers are blocks of at most 256
+// threads.
+template <bool UNIT, int P = 4, int B = 8>
+__device__ inline int exact_ray_chain(const RecheckArgs &a, int64_t i, int64_t j) {
+    __shared__ double2 terms[4][2][64];   // [wave][buffer][lens of the chunk]: (m/r2 d1, m/r2 d2)
+    const int lane = __lane_id();
+    const int w = (threadIdx.x >> 6) & 3;
+    double x1, x2;
+    ray_xy(a, i, j, x1, x2);
+    double a1 = 0.0, a2 = 0.0;
+    bool zero = false;
+    if (a.n_lens > 0) {
+        // Loads and terms have no branches (indices past the last lens read the last
+        // lens, and their terms are replaced by zero, which adds nothing: the running
+        // sums start at +0 and never become -0), so the compiler can count the loads
+        // in flight and wait for the oldest only.
+        const int64_t last = a.n_lens - 1;
+        auto load = [&](int64_t k, double &X, double &Y, double &M) {
+            const int64_t kc = k < a.n_lens ? k : last;
+            X = lens_x(a, kc);
+            Y = lens_y(a, kc);
+            M = UNIT ? 1.0 : lens_mass(a, kc);
+        };
+        auto term = [&](int64_t k, double X, double Y, double M) {
+            const double d1 = x1 - X;
+            const double d2 = x2 - Y;
+            const double r2 = d1 * d1 + d2 * d2;
+            const bool real = k < a.n_lens;
+            zero |= real && (r2 == 0.0);
+            const double m = UNIT ? 1.0 : M;
+            const double f = m / r2;
+            return make_double2(real ? f * d1 : 0.0, real ? f * d2 : 0.0);
+        };
+        const int64_t n_chunks = (a.n_lens + 63) / 64;
+        {
+            double X, Y, M;
+            load(lane, X, Y, M);
+            terms[w][0][lane] = term(lane, X, Y, M);
+        }
+        // Lens positions are loaded P chunks ahead of their terms (slot s of the ring
+        // holds chunk c + 1 while chunk c is summed, c = s mod P), and a chunk's terms
+        // are formed while the previous chunk is summed, so neither the memory latency
+        // nor the division sits on the dependent chain of additions.
+        double SX[P], SY[P], SM[P];
+#pragma unroll
+        for (int s = 0; s < P; ++s) load(64 * (s + 1) + lane, SX[s], SY[s], SM[s]);
+        wave_lds_fence();
+        // Whole rounds of P chunks: the chunks past the last one hold zero terms.
+        for (int64_t c0 = 0; c0 < n_chunks; c0 += P) {
+#pragma unroll
+            for (int s = 0; s < P; ++s) {
+                const int64_t c = c0 + s;
+                const double2 tn = term(64 * (c + 1) + lane, SX[s], SY[s], SM[s]);
+                load(64 * (c + 1 + P) + lane, SX[s], SY[s], SM[s]);
+                const double2 *T = terms[w][c & 1];
+                // in lens order, B terms read ahead of their additions (LDS latency
+                // is several times one addition's)
+                double2 cur[B];
+#pragma unroll
+                for (int l = 0; l < B; ++l) cur[l] = T[l];
+#pragma unroll
+                for (int g = 0; g < 64 / B; ++g) {
+                    double2 nxt[B];
+#pragma unroll
+                    for (int l = 0; l < B; ++l) nxt[l] = T[(B * (g + 1) + l) & 63];
+#pragma unroll
+                    for (int l = 0; l < B; ++l) {
+                        a1 += cur[l].x;
+                        a2 += cur[l].y;
+                    }
+#pragma unroll
+                    for (int l = 0; l < B; ++l) cur[l] = nxt[l];
+                }
+                terms[w][(c + 1) & 1][lane] = tn;
+                wave_lds_fence();   // every lane has read chunk c, and chunk c + 1 is written
+            }
+        }
+    }
+    if (__ballot(zero)) return CODE_SINGULAR;
+    return definition_pixel(a, x1, x2, a1, a2);
+}
+
+// The sums many terms at a time: lanes form the terms of J consecutive lenses each, and
+// add_in_order adds them in lens order. A sum that starts at zero or stays near it (a ray on
+// its lenses' mirror axis) starts over again and again, so that the chain is the faster form
+// for maps of few lenses. Time per ray, four waves per CU, chain against this form: 512 lenses
+// 5.9 / 12.4 us, 2000 20.7 / 27.4, 8000 80 / 93, 16000 156 / 163, 32000 310 / 301, 64000
+// 618 / 350, 10^6 9650 / 4460; on a mirror axis 512 lenses 5.8 / 12.5, 32000 310 / 511, 128000
+// 1237 / 1147. The line lies where a ray of a random field takes as long by either.
+constexpr int64_t EXACT_CHAIN_LENSES = 32768;
+template <bool UNIT, int J = 8>
+__device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_t j) {
     const int lane = __lane_id();
     double x1, x2;
     ray_xy(a, i, j, x1, x2);
@@ -259,14 +350,17 @@ __device__ inline int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j)
         a2 = add_in_order(a2, t2, o2);
     }
     if (__ballot(zero)) return CODE_SINGULAR;
-    const double y1 = ((1.0 - a.gamma) - a.sigma_c) * x1 - a1;
-    const double y2 = ((1.0 + a.gamma) - a.sigma_c) * x2 - a2;
-    const double u = (y1 - a.tx0) / (a.tw / (double)a.npx);
-    const double v = (y2 - a.ty0) / (a.th / (double)a.npy);
-    if (isfinite(u) && isfinite(v) && u >= 0.0 && u < (double)a.npx && v >= 0.0 && v < (double)a.npy)
-        return (int)((int64_t)floor(v) * a.npx + (int64_t)floor(u));
-    return CODE_OUT;
+    return definition_pixel(a, x1, x2, a1, a2);
 }
+
+template <bool UNIT, bool CHAIN>
+__device__ __forceinline__ int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j) {
+    if constexpr (CHAIN) return exact_ray_chain<UNIT>(a, i, j);
+    else return exact_ray_parallel<UNIT>(a, i, j);
+}
+
+// Maps of at most this many lenses and of one launch run stage B in stage A's kernel.
+constexpr int64_t EXACT_INLINE_LENSES = 2048;
 
 // Stage A's pixel decision. (a1, a2) is this stage's FP64 sum, S = sum (|d1| + |d2|) |m| / r^2
 // over every lens, and t1, t2 bound |definition's a_i - this a_i| (both roundings added); the

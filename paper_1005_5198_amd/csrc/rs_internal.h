@@ -214,6 +214,7 @@ struct BatchArgs {
     int32_t pad;
     int64_t total_tiles;
     int64_t total_words;
+    int64_t max_lenses;            // of any map
     int64_t total_super;           // super-patch records of every map (mixed mode)
     unsigned long long *tile_counter;
     unsigned int *unresolved;          // set when stage A left a ray to the exact stage
