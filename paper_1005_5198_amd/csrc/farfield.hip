@@ -1,6 +1,7 @@
 // Far-field expansion (RS_FARFIELD): two levels of FP64 local expansions of the
 // distant lenses, near lenses summed directly, a rigorous per-ray bound.
 #include "far_ray.h"
+#include "rs_launch.h"
 
 namespace rs {
 namespace {
@@ -1088,9 +1089,7 @@ hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    int64_t blocks = (max_rays + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    const dim3 grid((unsigned)blocks), block(256);
+    const dim3 grid((unsigned)queue_blocks(max_rays, 4, 1024)), block(256);   // (a wave per ray of a short queue)
     if (unit) {
         if (stage_a) hipLaunchKernelGGL((recheck_far_kernel<true, true>), grid, block, 0, stream, a, r, qlive);
         else hipLaunchKernelGGL((recheck_far_kernel<true, false>), grid, block, 0, stream, a, r, qlive);

@@ -25,6 +25,7 @@
 // bitmap; a persistent scan compacts the set bits per wave and the map's
 // descriptor supplies its parameters and its super-patch records (stage F).
 #include "far_ray.h"
+#include "rs_launch.h"
 
 namespace rs {
 namespace {
@@ -485,27 +486,25 @@ static void launch_exact_wave(const RecheckArgs &a, dim3 grid, hipStream_t strea
 }
 
 hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_only, bool stage_a_done, hipStream_t stream) {
-    int64_t blocks = (max_rays + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    if (blocks < 1) blocks = 1;
-    const dim3 grid((unsigned)blocks), block(256);
+    const dim3 block(256);
+    const dim3 threads((unsigned)queue_blocks(max_rays, 256, 2048));   // a ray per thread
     const bool unit = a.lens_m == nullptr;
     if (exact_only) {
-        if (unit) hipLaunchKernelGGL(recheck_exact_kernel<true>, grid, block, 0, stream, a);
-        else hipLaunchKernelGGL(recheck_exact_kernel<false>, grid, block, 0, stream, a);
+        if (unit) hipLaunchKernelGGL(recheck_exact_kernel<true>, threads, block, 0, stream, a);
+        else hipLaunchKernelGGL(recheck_exact_kernel<false>, threads, block, 0, stream, a);
     } else if (stage_a_done) {
         if (a.n_lens <= EXACT_INLINE_LENSES) return hipSuccess;   // stage B as well
-        const dim3 few((unsigned)(blocks < 512 ? blocks : 512));   // it mostly finds nothing to do
-        launch_exact_wave(a, few, stream);
+        launch_exact_wave(a, dim3((unsigned)queue_blocks(max_rays, 4, 512)), stream);   // it mostly finds nothing to do
     } else {
         RecheckArgs b = a;
         if (a.defer) {
-            hipLaunchKernelGGL(recheck_defer_kernel, grid, block, 0, stream, a);
+            hipLaunchKernelGGL(recheck_defer_kernel, threads, block, 0, stream, a);
             b.qlive = a.qleft;   // stage A of this launch takes what was not gathered
         }
+        const dim3 grid((unsigned)queue_blocks(max_rays, 1, 2048));   // (a block per ray of a short queue)
         if (unit) hipLaunchKernelGGL(recheck_fast_kernel<true>, grid, block, 0, stream, b);
         else hipLaunchKernelGGL(recheck_fast_kernel<false>, grid, block, 0, stream, b);
-        launch_exact_wave(b, grid, stream);
+        launch_exact_wave(b, dim3((unsigned)queue_blocks(max_rays, 4, 2048)), stream);
     }
     return hipGetLastError();
 }

@@ -1,0 +1,49 @@
+"""The rules that size launches, on the CPU (no device): tests/launch_driver.cpp links only
+paper_1005_5198_amd/csrc/rs_launch.h (pure host logic)."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1005_5198_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("launch") / "launch_driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=all", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "launch_driver.cpp"), "-o", exe], check=True)
+
+    def run(what, *args):
+        line = " ".join([what, *map(str, args)])
+        out = subprocess.run([exe], input=line + "\n", check=True, capture_output=True, text=True).stdout
+        return [float(v) if "." in v or "n" in v else int(v) for v in out.split()]
+    return run
+
+
+@pytest.mark.parametrize("per_block,cap", [(1, 2048), (4, 1024), (4, 512), (256, 2048)])
+def test_a_queue_fills_the_chip_before_rays_wait(ask, per_block, cap):
+    """Every ray of a queue has its place (a wave, a block or a thread) until the grid is full:
+    none waits for another while blocks could still be added."""
+    for entries in (0, 1, per_block, per_block + 1, 64, 2048, 33 * 64, per_block * cap - 1, per_block * cap,
+                    per_block * cap + 1, 1 << 27):
+        blocks, = ask("queue_blocks", entries, per_block, cap)
+        assert 1 <= blocks <= cap
+        assert blocks == cap or blocks * per_block >= entries
+        assert (blocks - 1) * per_block < max(entries, 1)   # and no block without one
+
+
+def _function(source, name):
+    text = open(os.path.join(CSRC, source)).read()
+    body = text[text.index("hipError_t " + name + "("):]
+    return body[:body.index("\n}\n")]
+
+
+@pytest.mark.parametrize("source,name,per_block", [("farfield.hip", "launch_recheck_far", 4),
+                                                   ("recheck.hip", "launch_recheck", 1)])
+def test_short_queue_forms_are_launched_by_that_rule(source, name, per_block):
+    """The kernels with a wave or a block per ray get their grid from it."""
+    body = _function(source, name)
+    assert f"queue_blocks(max_rays, {per_block}," in body and "/ 256" not in body
