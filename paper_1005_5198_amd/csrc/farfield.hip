@@ -977,17 +977,24 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
 // most of the chip idle otherwise: the 1219 rays of the 1024^2-ray, 462-lens map, whose
 // super-patches list almost every lens, took 84 us one thread per ray).
 constexpr uint32_t FAR_WAVE_MAX = 32768;
+// From this many of a wave's 64 rays left by stage F on, stage A takes them one per lane (a
+// pass over the lenses for all of them); below it one after another, each by the whole wave.
+constexpr int LANE_STAGE_MIN = 32;
 
 // Re-check stage F of the mixed mode (far_recheck_ray), one thread or one wave per
-// queued ray. A ray it places is binned. STAGE_A: the others take stage A at once, one
-// wave per ray, and are marked UNRESOLVED when that cannot place them either (or, with
+// queued ray. A ray it places is binned. STAGE_A (recheck_in_one): the others take stage A at
+// once, and are marked UNRESOLVED when that cannot place them either (or, with
 // few lenses, take stage B at once: its kernel, which mostly finds nothing to do, costs 5 us
-// of the 108 of the 1024^2-ray, 462-lens map);
-// otherwise a ray it places is marked RESOLVED, and the others are counted in *qlive and
-// left for the stages over every lens. Queue entries of one deflection block are
-// adjacent and share a super-patch, so a wave walks one list.
+// of the 108 of the 1024^2-ray, 462-lens map); otherwise a ray it places is marked RESOLVED,
+// and the others are counted in *qlive and left for the stages over every lens. Queue entries
+// of one deflection block are adjacent and share a super-patch, so a wave that takes adjacent
+// entries walks one list (dealt one by one to the waves, which spreads the rays stage F
+// leaves more evenly, 5000-lens maps with every ray queued took 1.7 times as long).
+// With stage A it takes the registers of two waves per SIMD (held to three it spills, and a small
+// map's call takes up to 5% longer).
+constexpr int64_t STAGE_A_BLOCKS = 512;   // two waves per SIMD
 template <bool UNIT, bool STAGE_A>
-__global__ __launch_bounds__(256, STAGE_A ? 3 : 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
+__global__ __launch_bounds__(256, STAGE_A ? 2 : 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
     __shared__ uint32_t sums[3];   // rays in the map, out, left
     const uint32_t n = *a.qcount;
     if (n == 0) return;
@@ -1000,35 +1007,49 @@ __global__ __launch_bounds__(256, STAGE_A ? 3 : 4) void recheck_far_kernel(const
     uint32_t n_in = 0, n_out = 0, left = 0;   // this lane's
     const bool wave_form = n <= FAR_WAVE_MAX;
     if (STAGE_A && wave_id == 0 && lane == 0) atomicAdd(a.counters + C_RECHECK, (unsigned long long)n);
-    // wave form: entry wave_id, wave_id + n_waves, ...; thread form: 64 entries at a time
-    for (uint64_t e0 = wave_form ? wave_id : 64ull * wave_id; e0 < n; e0 += wave_form ? n_waves : 64ull * n_waves) {
-        const uint64_t idx = wave_form ? e0 : e0 + (uint32_t)lane;
-        const bool mine = wave_form ? lane == 0 : idx < n;   // this lane records the entry's result
-        const uint32_t q = a.queue[idx < n ? idx : n - 1];
+    const uint32_t run = wave_form ? 1u : entry_run(n, n_waves);   // entries a wave takes at a time
+    for (uint64_t first = (uint64_t)run * wave_id; first < n; first += (uint64_t)run * n_waves) {
+        const uint64_t idx = wave_form ? first : first + (uint32_t)lane;
+        const bool mine = wave_form ? lane == 0 : (uint32_t)lane < run && idx < n;   // this lane records the entry's result
+        const uint32_t q = a.queue[mine ? idx : first];   // (an entry of this wave's: others mark theirs)
         const int64_t i = a.i0 + (int64_t)(q % W);
         const int64_t j = a.jc0 + (int64_t)(q / W);
         int code = wave_form ? far_recheck_ray<UNIT, true>(a, i, j) : far_recheck_ray<UNIT, false>(a, i, j);
         uint64_t todo = __ballot(mine && code == FLAGGED);
         if (mine && code == FLAGGED) ++left;
-        if (STAGE_A) {
-            while (todo) {
-                const int src = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
-                int c = 0;
-                const int64_t is = a.i0 + (int64_t)(qs % W), js = a.jc0 + (int64_t)(qs / W);
-                const bool decided = fast_ray_wave<UNIT, 4>(r, is, js, c);
-                const bool exact = !decided && r.n_lens <= EXACT_INLINE_LENSES;
-                if (exact) c = exact_ray_chain<UNIT, 2, 4>(r, is, js);
-                if (lane == src) {
-                    if (decided) {
-                        code = c;
-                    } else if (exact) {
-                        emit_ray(r, is, js, c);
-                    } else {
-                        a.queue[idx] = q | UNRESOLVED;
-                        atomicAdd(r.qunres, 1u);
-                    }
+        if (STAGE_A && todo) {
+            uint64_t undecided = 0;
+            if (__builtin_popcountll(todo) >= LANE_STAGE_MIN) {
+                bool decided = true;
+                if ((todo >> lane) & 1ull) {
+                    int c = 0;
+                    decided = fast_ray<UNIT>(r, i, j, c);
+                    if (decided) code = c;
+                }
+                undecided = __ballot(!decided);
+            } else {
+                while (todo) {
+                    const int src = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
+                    int c = 0;
+                    if (!fast_ray_wave<UNIT, 4>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c)) undecided |= 1ull << src;
+                    else if (lane == src) code = c;
+                }
+            }
+            if (r.n_lens > EXACT_INLINE_LENSES) {
+                if ((undecided >> lane) & 1ull) {
+                    a.queue[idx] = q | UNRESOLVED;
+                    atomicAdd(r.qunres, 1u);
+                }
+            } else {
+                while (undecided) {
+                    const int src = __builtin_ctzll(undecided);
+                    undecided &= undecided - 1;
+                    const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
+                    const int64_t is = a.i0 + (int64_t)(qs % W), js = a.jc0 + (int64_t)(qs / W);
+                    const int c = exact_ray_chain<UNIT, 2, 4>(r, is, js);
+                    if (lane == 0) emit_ray(r, is, js, c);
                 }
             }
         }
@@ -1089,7 +1110,7 @@ hipError_t launch_recheck_far(const ShootArgs &a, const RecheckArgs &r, uint32_t
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const dim3 grid((unsigned)queue_blocks(max_rays, 4, 1024)), block(256);   // (a wave per ray of a short queue)
+    const dim3 grid((unsigned)queue_blocks(max_rays, 4, stage_a ? STAGE_A_BLOCKS : 1024)), block(256);   // (a wave per ray of a short queue)
     if (unit) {
         if (stage_a) hipLaunchKernelGGL((recheck_far_kernel<true, true>), grid, block, 0, stream, a, r, qlive);
         else hipLaunchKernelGGL((recheck_far_kernel<true, false>), grid, block, 0, stream, a, r, qlive);

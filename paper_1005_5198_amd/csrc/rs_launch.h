@@ -1,8 +1,14 @@
-// How launches are sized: plain host rules (no device calls), shared by the launch
-// code and its CPU tests.
+// How launches are sized and queues dealt out: plain rules (no device calls), shared by the
+// launch code, the kernels and their CPU tests.
 #pragma once
 
 #include <cstdint>
+
+#ifdef __HIPCC__
+#define RS_HOST_DEVICE __host__ __device__
+#else
+#define RS_HOST_DEVICE
+#endif
 
 namespace rs {
 
@@ -14,6 +20,24 @@ namespace rs {
 inline int64_t queue_blocks(int64_t max_entries, int64_t per_block, int64_t cap) {
     const int64_t blocks = (max_entries + per_block - 1) / per_block;
     return blocks < 1 ? 1 : (blocks > cap ? cap : blocks);
+}
+
+// Adjacent entries of a long queue that a wave takes at a time: as many as give every wave some,
+// at most one per lane.
+RS_HOST_DEVICE inline uint32_t entry_run(uint32_t entries, uint32_t n_waves) {
+    const uint32_t share = (uint32_t)(((uint64_t)entries + n_waves - 1) / n_waves);
+    return share < 64u ? share : 64u;
+}
+
+// Mixed maps of one launch and at most this many ray-lens pairs take the re-check's stages F and A
+// in one kernel: a launch or two less, 4 us each, in a call of up to about 150 us. In larger maps
+// stage A follows in kernels of its own, in the form that suits the number of rays stage F left
+// and with those rays dealt out (in one kernel they stay with the waves that had them, and stage
+// F has fewer registers: 1024 x 512 rays, 5000 lenses 2.04 ms in kernels of their own, 2.40 in
+// one; where stage F leaves next to nothing, 2048 x 2048 rays and 300 lenses, 203 against 199 us).
+constexpr double RECHECK_ONE_PAIRS = 1.0e9;
+inline bool recheck_in_one(int64_t rays, int64_t n_lens, bool several_launches) {
+    return !several_launches && (double)rays * (double)n_lens <= RECHECK_ONE_PAIRS;
 }
 
 }  // namespace rs

@@ -2,6 +2,7 @@
 // validation, planning of ray chunks and workspace, and the launch sequence
 // (zero map and counters -> per chunk: deflection kernel, FP64 re-check).
 #include "rs_internal.h"
+#include "rs_launch.h"
 #include "rayshoot.h"
 #include "rs_debug.h"
 #include "rs_plan.h"
@@ -332,14 +333,15 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
             r.qlive = nullptr;
             r.qunres = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + 2 * pl.n_chunks + c;
             if (pl.defer) r.qleft = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + 3 * pl.n_chunks + c;
+            const int64_t rays = (a.jc1 - a.jc0) * pl.W;
+            const bool stage_a_done = pl.far_recheck && recheck_in_one(rays, n_lens, pl.defer);
             if (pl.far_recheck) {
                 uint32_t *qlive = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + pl.n_chunks + c;
                 r.qlive = qlive;
-                e = launch_recheck_far(a, r, qlive, !pl.defer, !pl.random && !fill_records, (a.jc1 - a.jc0) * pl.W, stream);
+                e = launch_recheck_far(a, r, qlive, stage_a_done, !pl.random && !fill_records, rays, stream);
                 if (e != hipSuccess) return hip_fail(e, "far-field re-check kernel");
             }
-            e = launch_recheck(r, (a.jc1 - a.jc0) * pl.W, (p->flags & RS_EXACT_RECHECK) != 0,
-                               pl.far_recheck && !pl.defer, stream);
+            e = launch_recheck(r, rays, (p->flags & RS_EXACT_RECHECK) != 0, stage_a_done, stream);
             if (e != hipSuccess) return hip_fail(e, "re-check kernel");
         }
     }

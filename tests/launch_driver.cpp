@@ -16,6 +16,15 @@ int main() {
             int64_t entries, per_block, cap;
             if (scanf("%" SCNd64 " %" SCNd64 " %" SCNd64, &entries, &per_block, &cap) != 3) return 1;
             printf("%" PRId64 "\n", queue_blocks(entries, per_block, cap));
+        } else if (!strcmp(what, "recheck_in_one")) {
+            int64_t rays, n_lens;
+            int several;
+            if (scanf("%" SCNd64 " %" SCNd64 " %d", &rays, &n_lens, &several) != 3) return 1;
+            printf("%d\n", recheck_in_one(rays, n_lens, several != 0) ? 1 : 0);
+        } else if (!strcmp(what, "entry_run")) {
+            uint32_t entries, n_waves;
+            if (scanf("%" SCNu32 " %" SCNu32, &entries, &n_waves) != 2) return 1;
+            printf("%" PRIu32 "\n", entry_run(entries, n_waves));
         } else {
             return 1;
         }

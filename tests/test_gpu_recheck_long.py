@@ -1,0 +1,82 @@
+"""Mixed maps of one launch whose queue of rays to re-check is long and that stage F mostly cannot
+place, on both sides of the limits where the stages' kernels change: rays exactly on pixel edges
+(every stage leaves them to the exact one), and crowded super-patches (stage A places them). The
+bars are the oracle's maps."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _edges(nx, ny, k, n):
+    """x = i / 64 and pixels k / 64 wide: every k-th column lies on an edge; n massless lenses."""
+    import paper_1005_5198_amd as rs
+    p = rs.map_params(0.0, 0.0, 0.0, (-nx / 128 - 0.5 / 64, -ny / 128, nx / 64, ny / 64, nx, ny),
+                      (-nx / 128, -ny / 128, (nx // k + 2) * k / 64, ny / 64 + 0.25, nx // k + 2, ny // 2 + 8))
+    xy = np.random.default_rng(3).uniform(900.0, 1100.0, (n, 2))
+    return p, xy, np.zeros(n)
+
+
+# one kernel with runs of 16 and 64 entries and the exact stage inside, the same with the exact
+# stage after it, a kernel for each stage
+@pytest.mark.parametrize("nx,ny,k,n", [(2048, 1024, 33, 462), (2048, 1024, 5, 462), (1024, 512, 5, 1900),
+                                       (480, 512, 5, 2050), (1024, 512, 5, 2050), (8192, 1024, 33, 462)])
+def test_rays_on_edges(nx, ny, k, n):
+    import paper_1005_5198_amd as rs
+    p, xy, m = _edges(nx, ny, k, n)
+    out, st = rs.make_map(p, xy, m, mode="mixed", return_stats=True)
+    ref, st_o = oracle.make_map(p, xy, m)
+    on_edge = len(range(0, nx, k)) * ny
+    assert st["rays_rechecked"] >= st["rays_rechecked_direct"] >= on_edge > 32768
+    assert np.array_equal(out.cpu().numpy(), ref)
+    for key in ("rays_in_map", "rays_out", "rays_singular"):
+        assert st[key] == st_o[key], key
+
+
+@pytest.mark.parametrize("n", [5000, 9000])   # one kernel; a kernel for each stage
+@pytest.mark.parametrize("masses", [False, True])
+def test_crowded_super_patches(n, masses):
+    """n lenses within reach of every super-patch: no list holds them, stage A takes every ray."""
+    import paper_1005_5198_amd as rs
+    rng = np.random.default_rng(22)
+    nx, ny = 420, 280
+    r = 5.0 if masses else 150.0
+    half = 3.0 if masses else 90.0
+    xy = np.sqrt(rng.random((n, 1))) * r * np.exp(2j * np.pi * rng.random((n, 1))).view(np.float64).reshape(-1, 2)
+    m = rng.uniform(0.0005, 0.0015, n) if masses else None
+    p = rs.map_params(0.064, 0.1, 0.2, (-half, -half / 1.5, 2 * half, 2 * half / 1.5, nx, ny),
+                      (-half, -half / 1.5, 2 * half, 2 * half / 1.5, 120, 80))
+    out, st = rs.make_map(p, xy, m, mode="mixed", return_stats=True)
+    ref, st_o = oracle.make_map(p, xy, m)
+    assert st["rays_rechecked_direct"] == st["rays_rechecked"] > 32768
+    assert np.array_equal(out.cpu().numpy(), ref)
+    for key in ("rays_in_map", "rays_out", "rays_singular"):
+        assert st[key] == st_o[key], key
+
+
+def test_the_stages_keep_their_pace_on_a_long_queue():
+    """104960 rays on edges among 2000 lenses, against one thread per ray for the exact sequence
+    alone: 3.1 times its time (the counters' atomics). With the rays that stage F leaves taken
+    one after another by the wave that had them, and sums at zero started over, 28 times."""
+    import paper_1005_5198_amd as rs
+    p, xy, m = _edges(1024, 512, 5, 2000)
+    lens = rs.lens_tensors(xy, m)
+    out = torch.empty((p["npy"], p["npx"]), dtype=torch.uint32, device="cuda")
+    ws = rs.new_workspace(p, 2000, "mixed")
+
+    def best(**kw):
+        t = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            rs.make_map(p, *lens, mode="mixed", out=out, workspace=ws, **kw)
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+    assert best() < 9.0 * best(exact_recheck=True)

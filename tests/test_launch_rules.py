@@ -47,3 +47,24 @@ def test_short_queue_forms_are_launched_by_that_rule(source, name, per_block):
     """The kernels with a wave or a block per ray get their grid from it."""
     body = _function(source, name)
     assert f"queue_blocks(max_rays, {per_block}," in body and "/ 256" not in body
+
+
+@pytest.mark.parametrize("n_waves", [1, 4, 2048, 4096])
+def test_a_long_queue_gives_every_wave_some_entries(ask, n_waves):
+    """The runs of adjacent entries that waves take in turn cover the queue with at most a
+    lane's worth each, and while waves are left without any, no run is longer than its share."""
+    for entries in (1, 63, 64, 65, 32769, 65536, 64 * n_waves - 1, 64 * n_waves, 64 * n_waves + 1, 1 << 27):
+        run, = ask("entry_run", entries, n_waves)
+        assert 1 <= run <= 64
+        assert run == 64 or run * n_waves >= entries
+        assert (run - 1) * n_waves < entries
+
+
+def test_one_kernel_for_the_stages_of_small_maps_only(ask):
+    """Stage A shares stage F's kernel only where a call is short; what stage F leaves of a
+    larger map is dealt out again by a kernel of its own."""
+    assert ask("recheck_in_one", 1 << 20, 462, 0) == [1]
+    assert ask("recheck_in_one", 1 << 20, 462, 1) == [0]
+    assert ask("recheck_in_one", 1 << 19, 5000, 0) == [0]
+    assert ask("recheck_in_one", 19200 * 3840, 17240, 0) == [0]
+    assert ask("recheck_in_one", 1 << 27, 1 << 40, 0) == [0]   # (no overflow)
