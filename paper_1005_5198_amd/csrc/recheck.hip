@@ -63,6 +63,7 @@ __device__ inline void place(const RecheckArgs &a, int64_t i, int64_t j, int cod
 // rays must not each take a thread through every lens); above it, one thread
 // per ray (throughput). The kernel checks the count on the device.
 constexpr uint32_t BLOCK_STAGE_MAX = 32768;
+enum StageAForm { FORM_EITHER, FORM_THREADS, FORM_BLOCKS };
 
 template <bool UNIT>
 __global__ __launch_bounds__(256) void recheck_exact_kernel(const RecheckArgs a) {
@@ -90,36 +91,40 @@ __global__ __launch_bounds__(256) void recheck_exact_kernel(const RecheckArgs a)
 // long queue whose entries the far-field stage mostly decided costs each block
 // a few vector loads, and neighbouring live rays go to different blocks. (One wave per ray
 // took 27 us for the 14 rays of the 19200 x 3840-ray, 17240-lens far-field map, and a kernel
-// for each form 4.6 us more.)
-template <bool UNIT>
+// for each form 4.6 us more. But both forms in one kernel hold three waves per SIMD instead of
+// the thread form's four: crowded maps, whose rays mostly come here, have a kernel for each.
+// 3000^2 rays and 300000 lenses, far field: 1.72 s in one kernel, 1.62 in one for each.)
+template <bool UNIT, StageAForm FORM>
 __global__ __launch_bounds__(256) void recheck_fast_kernel(const RecheckArgs a) {
     constexpr int WAVES = 4;
     __shared__ FastSums part[WAVES];
     const uint32_t n = *a.qcount;
     const uint32_t live = a.qlive ? *a.qlive : n;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (FORM != FORM_BLOCKS && blockIdx.x == 0 && threadIdx.x == 0) {
         if (n) atomicAdd(a.counters + C_RECHECK, (unsigned long long)n);
         if (live) atomicAdd(a.counters + C_DIRECT, (unsigned long long)live);
     }
-    if (live == 0) return;
-    const int64_t W = a.i1 - a.i0;
-    unsigned long long n_in = 0, n_out = 0, n_sing = 0;
+    const bool by_thread = live >= BLOCK_STAGE_MAX;
+    if (live == 0 || (FORM == FORM_THREADS && !by_thread) || (FORM == FORM_BLOCKS && by_thread)) return;
+    const uint32_t W = (uint32_t)(a.i1 - a.i0);   // at most 2^22
+    uint32_t n_in = 0, n_out = 0;   // (stage A never yields a singular ray)
     auto record = [&](uint32_t idx, uint32_t q, bool decided, int code) __attribute__((always_inline)) {
         if (decided) {
-            tally(code, n_in, n_out, n_sing);
-            place(a, a.i0 + (int64_t)(q % (uint64_t)W), a.jc0 + (int64_t)(q / (uint64_t)W), code);
+            if (code >= 0) ++n_in;
+            else ++n_out;
+            place(a, a.i0 + (int64_t)(q % W), a.jc0 + (int64_t)(q / W), code);
         } else {
             a.queue[idx] = q | UNRESOLVED;
             if (a.qunres) atomicAdd(a.qunres, 1u);
         }
     };
-    if (live >= BLOCK_STAGE_MAX) {
+    if (FORM == FORM_THREADS || (FORM == FORM_EITHER && by_thread)) {
         const uint32_t stride = gridDim.x * blockDim.x;
         for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += stride) {
             const uint32_t q = a.queue[idx];
             if (q & RESOLVED) continue;
             int code;
-            const bool decided = fast_ray<UNIT>(a, a.i0 + (int64_t)(q % (uint64_t)W), a.jc0 + (int64_t)(q / (uint64_t)W), code);
+            const bool decided = fast_ray<UNIT>(a, a.i0 + (int64_t)(q % W), a.jc0 + (int64_t)(q / W), code);
             record(idx, q, decided, code);
         }
     } else {
@@ -134,13 +139,13 @@ __global__ __launch_bounds__(256) void recheck_fast_kernel(const RecheckArgs a) 
                 todo &= todo - 1;
                 const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)q_lane, src);
                 int code = 0;
-                const bool decided = fast_ray_block<UNIT, 4, WAVES>(a, a.i0 + (int64_t)(q % (uint64_t)W),
-                                                                    a.jc0 + (int64_t)(q / (uint64_t)W), part, code);
+                const bool decided = fast_ray_block<UNIT, 4, WAVES>(a, a.i0 + (int64_t)(q % W),
+                                                                    a.jc0 + (int64_t)(q / W), part, code);
                 if ((int)threadIdx.x == src) record((uint32_t)idx, q, decided, code);
             }
         }
     }
-    count_wave(a.counters, n_in, n_out, n_sing);
+    count_wave(a.counters, n_in, n_out, 0ull);
 }
 
 template <bool UNIT, bool CHAIN>
@@ -502,8 +507,17 @@ hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_onl
             b.qlive = a.qleft;   // stage A of this launch takes what was not gathered
         }
         const dim3 grid((unsigned)queue_blocks(max_rays, 1, 2048));   // (a block per ray of a short queue)
-        if (unit) hipLaunchKernelGGL(recheck_fast_kernel<true>, grid, block, 0, stream, b);
-        else hipLaunchKernelGGL(recheck_fast_kernel<false>, grid, block, 0, stream, b);
+        auto launch = [&](auto u) {
+            constexpr bool U = decltype(u)::value;
+            if (crowded(max_rays, a.n_lens)) {
+                hipLaunchKernelGGL((recheck_fast_kernel<U, FORM_THREADS>), threads, block, 0, stream, b);
+                hipLaunchKernelGGL((recheck_fast_kernel<U, FORM_BLOCKS>), grid, block, 0, stream, b);
+            } else {
+                hipLaunchKernelGGL((recheck_fast_kernel<U, FORM_EITHER>), grid, block, 0, stream, b);
+            }
+        };
+        if (unit) launch(std::true_type{});
+        else launch(std::false_type{});
         launch_exact_wave(b, dim3((unsigned)queue_blocks(max_rays, 4, 2048)), stream);
     }
     return hipGetLastError();

@@ -21,6 +21,10 @@ int main() {
             int several;
             if (scanf("%" SCNd64 " %" SCNd64 " %d", &rays, &n_lens, &several) != 3) return 1;
             printf("%d\n", recheck_in_one(rays, n_lens, several != 0) ? 1 : 0);
+        } else if (!strcmp(what, "crowded")) {
+            int64_t rays, n_lens;
+            if (scanf("%" SCNd64 " %" SCNd64, &rays, &n_lens) != 2) return 1;
+            printf("%d\n", crowded(rays, n_lens) ? 1 : 0);
         } else if (!strcmp(what, "entry_run")) {
             uint32_t entries, n_waves;
             if (scanf("%" SCNu32 " %" SCNu32, &entries, &n_waves) != 2) return 1;

@@ -60,6 +60,24 @@ def test_crowded_super_patches(n, masses):
         assert st[key] == st_o[key], key
 
 
+@pytest.mark.parametrize("nx,ny", [(160, 120), (420, 280)])   # a block per ray, a thread per ray
+@pytest.mark.parametrize("masses", [False, True])
+def test_crowded_far_field(nx, ny, masses):
+    """Fewer than 256 rays per lens, far-field mode: stage A in a kernel for each of its forms."""
+    import paper_1005_5198_amd as rs
+    rng = np.random.default_rng(nx)
+    xy = rng.uniform(-150.0, 150.0, (9000, 2))
+    m = rng.uniform(0.2, 1.8, 9000) if masses else None
+    p = rs.map_params(0.3, 0.0, 0.1, (-90.0, -60.0, 180.0, 120.0, nx, ny), (-60.0, -50.0, 120.0, 100.0, 120, 100))
+    out, st = rs.make_map(p, xy, m, mode="farfield", return_stats=True)
+    ref, st_o = oracle.make_map(p, xy, m)
+    assert st["rays_rechecked_direct"] > 0
+    assert (st["rays_rechecked_direct"] >= 32768) == (nx > 160)
+    assert np.array_equal(out.cpu().numpy(), ref)
+    for key in ("rays_in_map", "rays_out", "rays_singular"):
+        assert st[key] == st_o[key], key
+
+
 def test_the_stages_keep_their_pace_on_a_long_queue():
     """104960 rays on edges among 2000 lenses, against one thread per ray for the exact sequence
     alone: 3.1 times its time (the counters' atomics). With the rays that stage F leaves taken

@@ -45,3 +45,9 @@ def _kernels(source, pattern):
 def test_exact_stage_keeps_its_waves(pattern, waves, scratch):
     for name, u in _kernels("recheck.hip", pattern).items():
         assert u["waves"] >= waves and u["scratch"] <= scratch, (name, u)
+
+
+def test_stage_a_by_thread_keeps_its_waves():
+    """Stage A with a thread per ray, in a kernel without the form for short queues (1: FORM_THREADS)."""
+    for name, u in _kernels("recheck.hip", r"recheck_fast_kernel<\w+, .*StageAForm\)1>").items():
+        assert u["waves"] >= 4 and u["scratch"] == 0, (name, u)

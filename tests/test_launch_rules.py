@@ -68,3 +68,12 @@ def test_one_kernel_for_the_stages_of_small_maps_only(ask):
     assert ask("recheck_in_one", 1 << 19, 5000, 0) == [0]
     assert ask("recheck_in_one", 19200 * 3840, 17240, 0) == [0]
     assert ask("recheck_in_one", 1 << 27, 1 << 40, 0) == [0]   # (no overflow)
+
+
+def test_crowded_maps(ask):
+    """Maps whose lists cannot hold the lenses nearby, most of whose rays come to stage A."""
+    assert ask("crowded", 3000 * 3000, 300000) == [1]
+    assert ask("crowded", 19200 * 3840, 17240) == [0]
+    assert ask("crowded", 256 * 1000, 1000) == [0] and ask("crowded", 256 * 1000 - 1, 1000) == [1]
+    assert ask("crowded", 1 << 27, (1 << 62)) == [1]   # (no overflow)
+    assert ask("crowded", 0, 0) == [0]
