@@ -776,7 +776,8 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     if (!PIX) table_clear<FAR_THREADS>(sm.table, tid);
-    // thread 0's share of the counter: patches share .. share + left - 1 are this block's
+    // Every block has its first two patches by its index. thread 0's share of the counter for
+    // the others: tickets share .. share + left - 1 are this block's.
     uint32_t share = 0;
     int left = 0;
     auto fetch = [&]() {
@@ -785,15 +786,9 @@ __global__ __launch_bounds__(FAR_THREADS, 3) void farfield_kernel(const ShootArg
             left = take;
         }
         --left;
-        return (int)share++;
+        return (int)ticket_patch(share++, gridDim.x);
     };
-    if (tid == 0) {
-        sm.near_count = fetch();
-        sm.next = fetch();
-    }
-    __syncthreads();
-    int64_t patch = sm.near_count, next = sm.next;
-    __syncthreads();
+    int64_t patch = first_patch(blockIdx.x, gridDim.x, 0), next = first_patch(blockIdx.x, gridDim.x, 1);
     if (tid == 0) sm.near_count = 0;
     auto hold = [&](int par, double v) {   // a record's double tid into its place
         if (tid < 2 * FAR_P) reinterpret_cast<double *>(sm.series[par])[tid] = v;

@@ -29,6 +29,13 @@ RS_HOST_DEVICE inline uint32_t entry_run(uint32_t entries, uint32_t n_waves) {
     return share < 64u ? share : 64u;
 }
 
+// Patches of the far-field ray kernel's persistent blocks, which load a patch's record while they
+// evaluate the one before: the first two of each block by its index, the others by tickets from a
+// counter. (With tickets for the first two as well, a block took two before others had any: 32
+// patches of a map with a block for each took 69 us in most calls and 39 in the rest.)
+RS_HOST_DEVICE inline int64_t first_patch(uint32_t block, uint32_t n_blocks, int turn) { return block + (int64_t)turn * n_blocks; }
+RS_HOST_DEVICE inline int64_t ticket_patch(uint32_t ticket, uint32_t n_blocks) { return 2ll * n_blocks + ticket; }
+
 // Mixed maps of one launch and at most this many ray-lens pairs take the re-check's stages F and A
 // in one kernel: a launch or two less, 4 us each, in a call of up to about 150 us. In larger maps
 // stage A follows in kernels of its own, in the form that suits the number of rays stage F left

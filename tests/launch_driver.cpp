@@ -21,6 +21,15 @@ int main() {
             int several;
             if (scanf("%" SCNd64 " %" SCNd64 " %d", &rays, &n_lens, &several) != 3) return 1;
             printf("%d\n", recheck_in_one(rays, n_lens, several != 0) ? 1 : 0);
+        } else if (!strcmp(what, "first_patch")) {
+            uint32_t block, n_blocks;
+            int turn;
+            if (scanf("%" SCNu32 " %" SCNu32 " %d", &block, &n_blocks, &turn) != 3) return 1;
+            printf("%" PRId64 "\n", first_patch(block, n_blocks, turn));
+        } else if (!strcmp(what, "ticket_patch")) {
+            uint32_t ticket, n_blocks;
+            if (scanf("%" SCNu32 " %" SCNu32, &ticket, &n_blocks) != 2) return 1;
+            printf("%" PRId64 "\n", ticket_patch(ticket, n_blocks));
         } else if (!strcmp(what, "crowded")) {
             int64_t rays, n_lens;
             if (scanf("%" SCNd64 " %" SCNd64, &rays, &n_lens) != 2) return 1;

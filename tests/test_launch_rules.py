@@ -17,9 +17,13 @@ def ask(tmp_path_factory):
                     os.path.join(ROOT, "tests", "launch_driver.cpp"), "-o", exe], check=True)
 
     def run(what, *args):
-        line = " ".join([what, *map(str, args)])
-        out = subprocess.run([exe], input=line + "\n", check=True, capture_output=True, text=True).stdout
-        return [float(v) if "." in v or "n" in v else int(v) for v in out.split()]
+        return run.many([(what, *args)])
+
+    def many(queries):
+        lines = "".join(" ".join(map(str, q)) + "\n" for q in queries)
+        out = subprocess.run([exe], input=lines, check=True, capture_output=True, text=True).stdout
+        return [int(v) for v in out.split()]
+    run.many = many
     return run
 
 
@@ -77,3 +81,20 @@ def test_crowded_maps(ask):
     assert ask("crowded", 256 * 1000, 1000) == [0] and ask("crowded", 256 * 1000 - 1, 1000) == [1]
     assert ask("crowded", 1 << 27, (1 << 62)) == [1]   # (no overflow)
     assert ask("crowded", 0, 0) == [0]
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 32, 768])
+def test_no_block_takes_two_patches_before_every_block_has_one(ask, blocks):
+    """The far-field ray kernel's blocks hold two patches at a time. Whatever the order in which
+    they start, each patch is taken once, and up to two patches per block are shared evenly."""
+    first = ask.many([("first_patch", b, blocks, turn) for turn in (0, 1) for b in range(blocks)])
+    tickets = ask.many([("ticket_patch", t, blocks) for t in range(5)])
+    assert sorted(first) + tickets == list(range(2 * blocks + 5))   # each once, tickets after them
+    assert first[:blocks] == list(range(blocks))                    # the first round gives each block one
+
+
+def test_the_far_field_ray_kernel_starts_by_that_rule():
+    text = open(os.path.join(CSRC, "farfield.hip")).read()
+    body = text[text.index("void farfield_kernel("):text.index("void recheck_far_kernel(")]
+    assert "patch = first_patch(blockIdx.x, gridDim.x, 0), next = first_patch(blockIdx.x, gridDim.x, 1)" in body
+    assert "ticket_patch(share++, gridDim.x)" in body
