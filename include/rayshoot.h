@@ -234,6 +234,9 @@ typedef struct {
  * fastest for maps with the same signature (mode, unit or general masses,
  * N* rounded down to a power of two, the window's 64 x 32-ray patches rounded
  * down to a power of two). Later rs_make_map calls with that signature use it.
+ * Shape 0 is the built-in choice: 4 x 2 rays per lane and 256 threads, or 2 x 2 and
+ * 512 in maps of few patches (at most two per CU, RS_FP32: one); it is timed and
+ * reported as the one that this map runs.
  * scratch_map (device, uint32 [npy][npx]) is overwritten. Synchronises the
  * stream. When the environment variable RAYSHOOT_TUNE_CACHE names a file, the
  * cache is loaded from it on first use and written to it after every tuning run.
@@ -244,7 +247,7 @@ int rs_tune(const rs_map_params *params, const double *lens_xy, const double *le
             void *stream, rs_tune_result *result_host);
 
 /*
- * Force a shape for every later launch (0 .. n_shapes-1), or -1 to use the
+ * Force a shape for every later launch (0 .. n_shapes-1; 0: 4 x 2 rays per lane), or -1 to use the
  * tuner's cache and the built-in default. The previous setting is stored in
  * *previous when it is not NULL. Errors: RS_EINVAL (shape out of range).
  */

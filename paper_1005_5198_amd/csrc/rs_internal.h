@@ -242,14 +242,20 @@ inline int64_t bitmap_words_of(const rs_map_params &p) {
     return (words + BITMAP_WORD_ALIGN - 1) / BITMAP_WORD_ALIGN * BITMAP_WORD_ALIGN;
 }
 
-// Blocks of a persistent kernel on the current device: every CU times
-// min(blocks_per_cu, the blocks that fit on it); blocks_per_cu <= 0 takes all that fit.
-template <class K>
-inline int persistent_blocks(K kernel, int threads, int blocks_per_cu) {
+// CUs of the current device.
+inline int compute_units() {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
         n_cu = 256;
+    return n_cu;
+}
+
+// Blocks of a persistent kernel on the current device: every CU times
+// min(blocks_per_cu, the blocks that fit on it); blocks_per_cu <= 0 takes all that fit.
+template <class K>
+inline int persistent_blocks(K kernel, int threads, int blocks_per_cu) {
+    const int n_cu = compute_units();
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu <= 0)
         per_cu = 2;

@@ -4,6 +4,8 @@
 
 #include <cstdint>
 
+#include "rs_layout.h"
+
 #ifdef __HIPCC__
 #define RS_HOST_DEVICE __host__ __device__
 #else
@@ -11,6 +13,20 @@
 #endif
 
 namespace rs {
+
+// Thread shapes of the deflection kernel beside the N_SHAPES that can be forced and tuned:
+// SHAPE_AUTO stands for the built-in choice, which is shape 0 (4 x 2 rays per lane, four waves) or,
+// in launches of few patches, SHAPE_WIDE (2 x 2 rays per lane, eight waves).
+constexpr int SHAPE_AUTO = -1;
+constexpr int SHAPE_WIDE = N_SHAPES;
+
+// At most two patches per CU (in FP32 mode one) are deflected by the wide shape: shape 0 would
+// leave SIMDs with one or two waves. us a call, wide against shape 0, 2000 lenses: 256 patches 224
+// / 347 (mixed), 150 / 222 (FP32); 512 patches 338 / 344 (mixed; with masses 379 / 371), 279 / 260
+// (FP32). 300 lenses: 58 / 81, 33 / 46; 79 / 87 (with masses 90 / 94), 54 / 54.
+inline int default_shape(bool mixed, int64_t patches, int64_t compute_units) {
+    return patches <= (mixed ? 2 : 1) * compute_units ? SHAPE_WIDE : 0;
+}
 
 // Blocks for a queue of at most max_entries rays, per_block of which a block takes at once in
 // the kernel's form for short queues (one per wave, one per block or one per thread): one for

@@ -108,7 +108,7 @@ struct EventPair {
 int choose_shape(int mode, bool unit, int64_t n_lens, int64_t patches);
 
 // Enqueue the whole map (or pixel) computation. map may be null when pix is set.
-// shape < 0 picks the tuned or default thread shape. When kernel_ms is given,
+// shape: SHAPE_AUTO picks the forced, tuned or built-in thread shape. When kernel_ms is given,
 // the deflection launches are timed with events and the call synchronises.
 static int check_inputs(const rs_map_params *p, const double *lens_xy, const double *lens_m, int64_t n_lens,
                         const uint32_t *map, const int32_t *pix) {
@@ -155,7 +155,7 @@ int enqueue_map_fixed(const rs_map_params *p, const double *lens_xy, const doubl
     rc = scratch_of_device(&scratch);
     if (rc) return rc;
     *scratch_used = scratch;
-    return enqueue_planned(p, lens_xy, lens_m, n_lens, map, nullptr, scratch, stream, -1, nullptr, pl, false);
+    return enqueue_planned(p, lens_xy, lens_m, n_lens, map, nullptr, scratch, stream, SHAPE_AUTO, nullptr, pl, false);
 }
 
 static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const double *lens_m, int64_t n_lens,
@@ -281,12 +281,18 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
         e = launch_super_records(a, pl.super_cap, stream);
         if (e != hipSuccess) return hip_fail(e, "super-patch records");
     }
-    if (shape < 0 && !pl.random && p->mode != RS_FARFIELD)
+    const bool direct = !pl.random && p->mode != RS_FARFIELD;
+    if (direct && shape == SHAPE_AUTO)
         shape = choose_shape(p->mode, lens_m == nullptr, n_lens, (pl.W + PATCH_X - 1) / PATCH_X * ((pl.H + PATCH_Y - 1) / PATCH_Y));
+    const int64_t launch_bands = ((pl.H < pl.rows_per_chunk ? pl.H : pl.rows_per_chunk) + PATCH_Y - 1) / PATCH_Y;
+    const int n_cu = direct && shape == SHAPE_AUTO ? compute_units() : 0;
+    auto shape_of = [&](int64_t bands) {   // of a launch of that many rows of patches
+        return shape != SHAPE_AUTO || !direct ? shape : default_shape(p->mode == RS_MIXED, a.nbx * bands, n_cu);
+    };
     debug_print(1, "map %lldx%lld rays, %lld lenses%s, mode %d%s: %lld launch(es) of %lld rows, workspace %zu B, shape %d",
                 (long long)pl.W, (long long)pl.H, (long long)n_lens, lens_m ? " with masses" : "", p->mode,
                 pl.random ? ", random rays" : "", (long long)pl.n_chunks, (long long)pl.rows_per_chunk, pl.bytes,
-                shape);
+                shape_of(launch_bands));
     EventPair ev;
     if (kernel_ms) {
         *kernel_ms = 0.0f;
@@ -315,7 +321,7 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
         } else if (p->mode == RS_FARFIELD) {
             e = launch_farfield(a, stream);
         } else {
-            e = launch_shoot(a, p->mode, shape, stream);
+            e = launch_shoot(a, p->mode, shape_of((a.jc1 - a.jc0 + PATCH_Y - 1) / PATCH_Y), stream);
         }
         if (e != hipSuccess) return hip_fail(e, "deflection kernel");
         if (kernel_ms) {
@@ -375,14 +381,14 @@ int rs_make_map(const rs_map_params *params, const double *lens_xy, const double
                 uint32_t *map, void *workspace, size_t workspace_bytes, void *stream) {
     if (!map) return fail(RS_EINVAL, "map is NULL");
     return enqueue_map(params, lens_xy, lens_m, n_lens, map, nullptr, workspace, workspace_bytes,
-                       static_cast<hipStream_t>(stream), -1, nullptr);
+                       static_cast<hipStream_t>(stream), SHAPE_AUTO, nullptr);
 }
 
 int rs_ray_pixels(const rs_map_params *params, const double *lens_xy, const double *lens_m, int64_t n_lens,
                   int32_t *pix, void *workspace, size_t workspace_bytes, void *stream) {
     if (!pix) return fail(RS_EINVAL, "pix is NULL");
     return enqueue_map(params, lens_xy, lens_m, n_lens, nullptr, pix, workspace, workspace_bytes,
-                       static_cast<hipStream_t>(stream), -1, nullptr);
+                       static_cast<hipStream_t>(stream), SHAPE_AUTO, nullptr);
 }
 
 int rs_read_stats(const void *workspace, rs_map_stats *stats_host, void *stream) {

@@ -28,6 +28,7 @@
 //    pixels, so aggregating within a wave alone took up to 64 rounds per ray of a lane:
 //    half of the time of the 1024^2-ray, 462-lens map).
 #include "shoot_common.h"
+#include "rs_launch.h"
 
 namespace rs {
 namespace {
@@ -446,10 +447,10 @@ static void launch_shape(const ShootArgs &a, int mode, dim3 grid, hipStream_t st
 #undef RS_LAUNCH
 }
 const ShapeInfo &shape_info(int shape) {
-    static const ShapeInfo table[N_SHAPES] = {
-        {4, 2, 2, 2}, {4, 4, 2, 1}, {8, 2, 1, 2}, {8, 4, 1, 1},
+    static const ShapeInfo table[SHAPE_WIDE + 1] = {
+        {4, 2, 2, 2}, {4, 4, 2, 1}, {8, 2, 1, 2}, {8, 4, 1, 1}, {2, 2, 4, 2},
     };
-    return table[(shape >= 0 && shape < N_SHAPES) ? shape : 0];
+    return table[(shape >= 0 && shape <= SHAPE_WIDE) ? shape : 0];
 }
 
 template <int RX, int RY, int WX, int WY, bool UNIT, int MODE>
@@ -491,13 +492,6 @@ hipError_t launch_batch_fill(const BatchArgs &b, void *workspace, int32_t n_maps
     return hipGetLastError();
 }
 
-// At most this many patches (two per CU; in FP32 mode one) are deflected by blocks of
-// twice the waves with half the rays per lane: the default shape would leave SIMDs with
-// one or two waves. 1848 lenses, patches of 64 x 32 rays, default against wide: 256
-// patches 244 against 148 us (mixed) and 210 against 137 us (FP32); 512 patches 270
-// against 267 us and 235 against 249 us.
-constexpr int64_t WIDE_MAX_BLOCKS = 512;
-
 hipError_t launch_shoot(const ShootArgs &a, int mode, int shape, hipStream_t stream) {
     const int64_t nby = (a.jc1 - a.jc0 + PATCH_Y - 1) / PATCH_Y;
     const int64_t blocks = a.nbx * nby;
@@ -507,10 +501,8 @@ hipError_t launch_shoot(const ShootArgs &a, int mode, int shape, hipStream_t str
         case 1: launch_shape<4, 4, 2, 1>(a, mode, grid, stream); break;
         case 2: launch_shape<8, 2, 1, 2>(a, mode, grid, stream); break;
         case 3: launch_shape<8, 4, 1, 1>(a, mode, grid, stream); break;
-        default:
-            if (blocks <= (mode == 0 ? WIDE_MAX_BLOCKS / 2 : WIDE_MAX_BLOCKS)) launch_shape<2, 2, 4, 2>(a, mode, grid, stream);
-            else launch_shape<4, 2, 2, 2>(a, mode, grid, stream);
-            break;
+        case SHAPE_WIDE: launch_shape<2, 2, 4, 2>(a, mode, grid, stream); break;
+        default: launch_shape<4, 2, 2, 2>(a, mode, grid, stream); break;
     }
     return hipGetLastError();
 }

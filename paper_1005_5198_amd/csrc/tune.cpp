@@ -13,6 +13,8 @@
 // the batch's patch count for batches. RAYSHOOT_TUNE_CACHE names a file that is
 // loaded on first use and rewritten after every tuning run.
 #include "rs_internal.h"
+#include "rs_launch.h"
+#include "rs_plan.h"
 #include "rayshoot.h"
 #include "rs_debug.h"
 
@@ -38,7 +40,7 @@ std::mutex g_mu;
 std::map<Key, int> g_cache;   // single maps: shape; batches: shape + 16 * blocks per CU
 int g_forced = -1;
 bool g_env_loaded = false;
-// Built-in choice when nothing was tuned (measured on MI355X: 4 x 2 rays per lane, 2 x 2 waves).
+// A batch's choice when nothing was tuned (measured on MI355X: 4 x 2 rays per lane, 2 x 2 waves).
 constexpr int DEFAULT_SHAPE = 0;
 
 int log2_bucket(int64_t v) {
@@ -108,12 +110,14 @@ int load_locked(const char *path, bool quiet) {
 }
 }  // namespace
 
+// A single map's choice: a forced shape as it is; else the tuned one, whose shape 0 stands for
+// the built-in choice, or the built-in choice (SHAPE_AUTO).
 int choose_shape(int mode, bool unit, int64_t n_lens, int64_t patches) {
     std::lock_guard<std::mutex> lk(g_mu);
     if (g_forced >= 0) return g_forced;
     load_env_locked();
     auto it = g_cache.find(key_of(0, mode, unit, n_lens, patches));
-    return it == g_cache.end() ? DEFAULT_SHAPE : it->second;
+    return it == g_cache.end() || it->second == 0 ? SHAPE_AUTO : it->second;
 }
 
 // A batch's choice (shape + 16 * blocks per CU; 0 blocks = as many as fit).
@@ -175,15 +179,23 @@ int rs_tune(const rs_map_params *params, const double *lens_xy, const double *le
     r.n_shapes = N_SHAPES;
     r.sample_interactions = (double)W * (double)rows * (double)n_lens;
     int best = -1;
+    // shape 0 is timed as what the map itself would run with it
+    int rc = validate(params, n_lens);
+    if (rc) return rc;
+    const Plan plan = make_plan(params, n_lens);
+    const int64_t launch_rows = H < plan.rows_per_chunk ? H : plan.rows_per_chunk;
+    const int built_in = default_shape(params->mode == RS_MIXED, (W + PATCH_X - 1) / PATCH_X * ((launch_rows + PATCH_Y - 1) / PATCH_Y),
+                                       compute_units());
     for (int shape = 0; shape < N_SHAPES; ++shape) {
-        const ShapeInfo &si = shape_info(shape);
+        const int runs = shape == 0 ? built_in : shape;
+        const ShapeInfo &si = shape_info(runs);
         r.rays_per_lane[shape][0] = si.rx;
         r.rays_per_lane[shape][1] = si.ry;
         r.threads[shape] = 64 * si.wx * si.wy;
         float ms = 0.0f, best_ms = 1e30f;
         for (int rep = 0; rep < 3; ++rep) {  // first run warms up; keep the fastest of the rest
-            int rc = enqueue_map(&p, lens_xy, lens_m, n_lens, scratch_map, nullptr, workspace, workspace_bytes, s,
-                                 shape, &ms);
+            rc = enqueue_map(&p, lens_xy, lens_m, n_lens, scratch_map, nullptr, workspace, workspace_bytes, s,
+                                 runs, &ms);
             if (rc) return rc;
             if (rep > 0 && ms < best_ms) best_ms = ms;
         }

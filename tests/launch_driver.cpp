@@ -21,6 +21,11 @@ int main() {
             int several;
             if (scanf("%" SCNd64 " %" SCNd64 " %d", &rays, &n_lens, &several) != 3) return 1;
             printf("%d\n", recheck_in_one(rays, n_lens, several != 0) ? 1 : 0);
+        } else if (!strcmp(what, "default_shape")) {
+            int mixed;
+            int64_t patches, cus;
+            if (scanf("%d %" SCNd64 " %" SCNd64, &mixed, &patches, &cus) != 3) return 1;
+            printf("%d\n", default_shape(mixed != 0, patches, cus));
         } else if (!strcmp(what, "first_patch")) {
             uint32_t block, n_blocks;
             int turn;

@@ -98,3 +98,12 @@ def test_the_far_field_ray_kernel_starts_by_that_rule():
     body = text[text.index("void farfield_kernel("):text.index("void recheck_far_kernel(")]
     assert "patch = first_patch(blockIdx.x, gridDim.x, 0), next = first_patch(blockIdx.x, gridDim.x, 1)" in body
     assert "ticket_patch(share++, gridDim.x)" in body
+
+
+@pytest.mark.parametrize("cus", [64, 256, 304])
+def test_built_in_shape(ask, cus):
+    """Eight-wave blocks while there are no more patches than two per CU (FP32 mode: one), else
+    shape 0; by the device's number of CUs."""
+    for mixed, per_cu in ((1, 2), (0, 1)):
+        wide, at, past = ask.many([("default_shape", mixed, p, cus) for p in (1, per_cu * cus, per_cu * cus + 1)])
+        assert wide == at == 4 and past == 0
