@@ -220,7 +220,7 @@ int rs_profile_read(double *kernel_ms, int64_t *launches, double *interactions);
 #define RS_MAX_SHAPES 8
 
 typedef struct {
-    int32_t shape;               /* fastest shape id on the sample */
+    int32_t shape;               /* fastest shape id on the sample (0 unless another is 3% faster) */
     int32_t n_shapes;            /* shapes available */
     int32_t rays_per_lane[RS_MAX_SHAPES][2];  /* (x, y) rays per lane of each shape */
     int32_t threads[RS_MAX_SHAPES];           /* threads per block of each shape */
@@ -230,7 +230,8 @@ typedef struct {
 
 /*
  * Time every shape on a sample of this map (a band of rows from the middle of
- * the window holding about sample_rays rays; <= 0 picks 2^24) and remember the
+ * the window with the work of about sample_rays rays; <= 0 picks 2^22; of maps of
+ * 2048 lenses or more, up to four times the rays with a part of the lenses) and remember the
  * fastest for maps with the same signature (mode, unit or general masses,
  * N* rounded down to a power of two, the window's 64 x 32-ray patches rounded
  * down to a power of two). Later rs_make_map calls with that signature use it.

@@ -202,7 +202,7 @@ def version() -> str:
     return L.lib().rs_version().decode()
 
 
-def tune(params: dict, lens_xy, lens_m=None, mode: str = "mixed", sample_rays: int = 1 << 24, stream=None) -> dict:
+def tune(params: dict, lens_xy, lens_m=None, mode: str = "mixed", sample_rays: int = 1 << 22, stream=None) -> dict:
     """Time every thread shape of the deflection kernel on a sample of this map; cache the fastest."""
     dev = _device()
     xy, m = lens_tensors(lens_xy, lens_m, dev)

@@ -28,6 +28,27 @@ inline int default_shape(bool mixed, int64_t patches, int64_t compute_units) {
     return patches <= (mixed ? 2 : 1) * compute_units ? SHAPE_WIDE : 0;
 }
 
+// The tuner's sample of a W x H window: whole bands of 32 rows and some of the lenses, with as
+// many ray-lens pairs as about sample_rays rays with every lens have. Of 2048 lenses or more it
+// takes up to a quarter, 1024 at least, and as many more rays: a launch's last blocks, which leave
+// SIMDs with few waves, weigh on the shapes differently, and 4 million rays are under two rounds of
+// blocks. (19200 x 3840 rays, 17240 lenses, 4 x 2 rays per lane 132 ms, 4 x 4 137: 4 million rays
+// with every lens put 4 x 4 6% ahead, in 116 ms of tuning; 16 million 2% behind, in 442; 16 million
+// with a quarter of the lenses 2% behind, in 115.)
+struct TuneSample {
+    int64_t rows, lenses;
+};
+inline TuneSample tune_sample(int64_t W, int64_t H, int64_t n_lens, int64_t sample_rays) {
+    if (sample_rays / W >= H) return TuneSample{H, n_lens};   // the whole window
+    const int64_t spread = n_lens < 2048 ? 1 : (n_lens < 4096 ? n_lens / 1024 : 4);
+    TuneSample s{sample_rays / W * spread / PATCH_Y * PATCH_Y, n_lens};
+    if (s.rows < PATCH_Y) s.rows = PATCH_Y;
+    if (s.rows > H) s.rows = H;
+    const double share = (double)sample_rays / ((double)s.rows * (double)W);   // of the lenses
+    if (share < 1.0) s.lenses = (int64_t)((double)n_lens * (share * spread > 1.0 ? share : 1.0 / spread));
+    return s;
+}
+
 // Blocks for a queue of at most max_entries rays, per_block of which a block takes at once in
 // the kernel's form for short queues (one per wave, one per block or one per thread): one for
 // each until the chip is full, at least one, at most cap. (Sized for the form for long queues, a

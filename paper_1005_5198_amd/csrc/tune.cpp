@@ -165,23 +165,18 @@ int rs_tune(const rs_map_params *params, const double *lens_xy, const double *le
     p.flags &= ~RS_ACCUMULATE;
     const int64_t W = p.i1 - p.i0, H = p.j1 - p.j0;
     if (W <= 0 || H <= 0) return fail(RS_EINVAL, "empty window");
-    // (2^24 rays are eight rounds of blocks; with 2^22, under two, the last round decided: 4 x 4
-    // rays per lane over 4 x 2, which is 3% faster on the 19200 x 3840-ray, 17240-lens map)
-    if (sample_rays <= 0) sample_rays = int64_t(1) << 24;
-    int64_t rows = sample_rays / W;
-    rows = rows / PATCH_Y * PATCH_Y;
-    if (rows < PATCH_Y) rows = PATCH_Y;
-    if (rows > H) rows = H;
-    p.j0 = params->j0 + (H - rows) / 2;
-    p.j1 = p.j0 + rows;
+    int rc = validate(params, n_lens);
+    if (rc) return rc;
+    if (sample_rays <= 0) sample_rays = int64_t(1) << 22;
+    const TuneSample sample = tune_sample(W, H, n_lens, sample_rays);
+    p.j0 = params->j0 + (H - sample.rows) / 2;
+    p.j1 = p.j0 + sample.rows;
     hipStream_t s = static_cast<hipStream_t>(stream);
     rs_tune_result r{};
     r.n_shapes = N_SHAPES;
-    r.sample_interactions = (double)W * (double)rows * (double)n_lens;
+    r.sample_interactions = (double)W * (double)sample.rows * (double)sample.lenses;
     int best = -1;
     // shape 0 is timed as what the map itself would run with it
-    int rc = validate(params, n_lens);
-    if (rc) return rc;
     const Plan plan = make_plan(params, n_lens);
     const int64_t launch_rows = H < plan.rows_per_chunk ? H : plan.rows_per_chunk;
     const int built_in = default_shape(params->mode == RS_MIXED, (W + PATCH_X - 1) / PATCH_X * ((launch_rows + PATCH_Y - 1) / PATCH_Y),
@@ -194,7 +189,7 @@ int rs_tune(const rs_map_params *params, const double *lens_xy, const double *le
         r.threads[shape] = 64 * si.wx * si.wy;
         float ms = 0.0f, best_ms = 1e30f;
         for (int rep = 0; rep < 3; ++rep) {  // first run warms up; keep the fastest of the rest
-            rc = enqueue_map(&p, lens_xy, lens_m, n_lens, scratch_map, nullptr, workspace, workspace_bytes, s,
+            rc = enqueue_map(&p, lens_xy, lens_m, sample.lenses, scratch_map, nullptr, workspace, workspace_bytes, s,
                                  runs, &ms);
             if (rc) return rc;
             if (rep > 0 && ms < best_ms) best_ms = ms;
@@ -202,6 +197,8 @@ int rs_tune(const rs_map_params *params, const double *lens_xy, const double *le
         r.ms[shape] = best_ms;
         if (best < 0 || best_ms < r.ms[best]) best = shape;
     }
+    // (samples and maps differ by some 2%)
+    if (r.ms[0] <= 1.03 * r.ms[best]) best = 0;
     r.shape = best;
     const int64_t patches = ((W + PATCH_X - 1) / PATCH_X) * ((H + PATCH_Y - 1) / PATCH_Y);
     {

@@ -26,6 +26,11 @@ int main() {
             int64_t patches, cus;
             if (scanf("%d %" SCNd64 " %" SCNd64, &mixed, &patches, &cus) != 3) return 1;
             printf("%d\n", default_shape(mixed != 0, patches, cus));
+        } else if (!strcmp(what, "tune_sample")) {
+            int64_t W, H, n_lens, rays;
+            if (scanf("%" SCNd64 " %" SCNd64 " %" SCNd64 " %" SCNd64, &W, &H, &n_lens, &rays) != 4) return 1;
+            const TuneSample s = tune_sample(W, H, n_lens, rays);
+            printf("%" PRId64 " %" PRId64 "\n", s.rows, s.lenses);
         } else if (!strcmp(what, "first_patch")) {
             uint32_t block, n_blocks;
             int turn;

@@ -69,3 +69,11 @@ def test_forced_and_built_in_shapes_give_the_oracle_map(nbx, nby, masses):
     finally:
         rs.set_shape(-1)
     assert all(torch.equal(fp32[0], f) for f in fp32[1:])
+
+
+def test_default_tuning_is_the_work_of_four_million_rays():
+    import paper_1005_5198_amd as rs
+    from paper_1005_5198_amd import workloads as w
+    s = w.config2()
+    r = rs.tune(s.params, s.lens_xy)
+    assert 0.9 * (1 << 22) * s.n_lens < r["sample_interactions"] <= (1 << 22) * s.n_lens

@@ -107,3 +107,31 @@ def test_built_in_shape(ask, cus):
     for mixed, per_cu in ((1, 2), (0, 1)):
         wide, at, past = ask.many([("default_shape", mixed, p, cus) for p in (1, per_cu * cus, per_cu * cus + 1)])
         assert wide == at == 4 and past == 0
+
+
+def test_tuner_sample(ask):
+    """The work asked for and no more (but for the least of 32 rows), in bands that stay in the
+    window; more rays with fewer lenses where there are lenses enough."""
+    cases = [(W, H, n, rays) for W in (1, 64, 5003, 19200, 1 << 22) for H in (1, 31, 32, 3001, 3840, 1 << 52)
+             for n in (0, 1, 462, 2047, 2048, 3331, 17240, 10 ** 6) for rays in (1, 1 << 20, 1 << 22, 1 << 24, (1 << 63) - 1)]
+    got = ask.many([("tune_sample", *c) for c in cases])
+    for (W, H, n, rays), rows, lenses in zip(cases, got[::2], got[1::2]):
+        assert 1 <= rows <= H and (rows % 32 == 0 or rows == H)
+        assert (n < 2048 and lenses == n) or n // 4 <= lenses <= n
+        if rows > 32:
+            assert rows * W * lenses <= rays * n
+    # the 19200 x 3840-ray, 17240-lens map: four times the rays, a quarter of the lenses
+    rows, lenses = ask("tune_sample", 19200, 3840, 17240, 1 << 22)
+    assert rows == 864 and 0.95 * (1 << 22) * 17240 <= 19200 * rows * lenses <= (1 << 22) * 17240
+    assert ask("tune_sample", 32768, 32768, 462, 1 << 22) == [128, 462]
+    assert ask("tune_sample", 1024, 1024, 462, 1 << 22) == [1024, 462]      # the whole window
+    assert ask("tune_sample", 1 << 22, 1 << 52, 17240, 1 << 22) == [32, 4310]
+    assert ask("tune_sample", 1, 1 << 52, 17240, (1 << 63) - 1) == [1 << 52, 17240]   # (no overflow)
+
+
+def test_the_tuner_asks_for_four_million_rays():
+    import inspect
+
+    from paper_1005_5198_amd import api
+    assert inspect.signature(api.tune).parameters["sample_rays"].default == 1 << 22
+    assert "if (sample_rays <= 0) sample_rays = int64_t(1) << 22;" in open(os.path.join(CSRC, "tune.cpp")).read()
