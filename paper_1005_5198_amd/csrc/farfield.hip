@@ -1,6 +1,7 @@
 // Far-field expansion (RS_FARFIELD): two levels of FP64 local expansions of the
 // distant lenses, near lenses summed directly, a rigorous per-ray bound.
 #include "far_ray.h"
+#include "rs_decide.h"
 #include "rs_launch.h"
 
 namespace rs {
@@ -712,15 +713,10 @@ __device__ __forceinline__ PatchBound patch_bound(const ShootArgs &a, const Patc
 __device__ __forceinline__ int patch_decide(const ShootArgs &a, const PatchBound &b, double u, double v, double snear) {
     const double Mu = __builtin_fma(b.su, snear, b.eu);
     const double Mv = __builtin_fma(b.sv, snear, b.ev);
-    const double fu = floor(u), fv = floor(v);
-    const double ru = u - fu, rv = v - fv;   // exact
-    const int iu = (int)fu, iv = (int)fv;    // (out of int's range: its end, outside the map)
-    const bool in = (uint32_t)iu < (uint32_t)a.npx && (uint32_t)iv < (uint32_t)a.npy && ru > Mu && ru + Mu < 1.0 &&
-                    rv > Mv && rv + Mv < 1.0;
-    int code = (int)((uint32_t)iv * (uint32_t)a.npx + (uint32_t)iu);
-    if (__ballot(!in)) {
+    int code = pixel_inside(u, v, Mu, Mv, a.npx, a.npy);
+    if (__ballot(code < 0)) {
         const bool out = u < -Mu || u - (double)a.npx > Mu || v < -Mv || v - (double)a.npy > Mv;
-        code = in ? code : (out ? OUT : FLAGGED);
+        code = code >= 0 ? code : (out ? OUT : FLAGGED);
     }
     return code;
 }

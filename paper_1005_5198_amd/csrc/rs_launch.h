@@ -6,12 +6,6 @@
 
 #include "rs_layout.h"
 
-#ifdef __HIPCC__
-#define RS_HOST_DEVICE __host__ __device__
-#else
-#define RS_HOST_DEVICE
-#endif
-
 namespace rs {
 
 // Thread shapes of the deflection kernel beside the N_SHAPES that can be forced and tuned:

@@ -5,6 +5,13 @@
 #include <cstddef>
 #include <cstdint>
 
+// For plain functions that kernels and host-only code (with its CPU tests) share.
+#ifdef __HIPCC__
+#define RS_HOST_DEVICE __host__ __device__
+#else
+#define RS_HOST_DEVICE
+#endif
+
 namespace rs {
 
 // Ray patch of one block of the deflection kernel: PATCH_X x PATCH_Y rays,
