@@ -375,7 +375,7 @@ __device__ inline void batch_stage_a_wave(const BatchArgs &b, QueueEntry e) {
 }
 
 // Exact stage for up to 64 entries held one per lane: one wave per ray. CHAIN: no map has
-// more than EXACT_CHAIN_LENSES lenses.
+// more than BATCH_CHAIN_LENSES lenses.
 template <bool ALL_UNIT, bool CHAIN>
 __device__ inline void batch_stage_b(const BatchArgs &b, QueueEntry e, int n_valid) {
     const int lane = __lane_id();
@@ -389,7 +389,7 @@ __device__ inline void batch_stage_b(const BatchArgs &b, QueueEntry e, int n_val
         const int64_t j = a.j0 + (int64_t)(ray / (uint64_t)W);
         const bool unit = ALL_UNIT || a.lens_m == nullptr;
         int code;
-        if (CHAIN || a.n_lens <= EXACT_CHAIN_LENSES)
+        if (CHAIN || a.n_lens <= BATCH_CHAIN_LENSES)
             code = unit ? exact_ray_wave<true, true>(a, i, j) : exact_ray_wave<false, true>(a, i, j);
         else
             code = unit ? exact_ray_parallel<true, 4>(a, i, j) : exact_ray_parallel<false, 4>(a, i, j);
@@ -541,7 +541,7 @@ hipError_t launch_recheck_batch(const BatchArgs &b, hipStream_t stream) {
     const dim3 grid(2048), block(256);
     // kernels of their own for batches of unit-mass maps only, and for batches whose maps all
     // take the exact stage's chain (fewer registers)
-    const bool chain = b.max_lenses <= EXACT_CHAIN_LENSES;
+    const bool chain = b.max_lenses <= BATCH_CHAIN_LENSES;
     auto launch = [&](auto unit) {
         constexpr bool U = decltype(unit)::value;
         hipLaunchKernelGGL((recheck_scan_batch_kernel<0, U, true>), grid, block, 0, stream, b);

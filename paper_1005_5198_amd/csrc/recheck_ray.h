@@ -195,9 +195,10 @@ __device__ __forceinline__ OrderedRound ordered_round(double s, const double (&t
     return o;
 }
 
+// starts: counts the starts over.
 template <int J>
-__device__ __forceinline__ double add_in_order(double s, const double (&t)[J], OrderedRound o) {
-    for (int run = 1; o.where; run *= 2) {   // (the same in every lane)
+__device__ __forceinline__ double add_in_order(double s, const double (&t)[J], OrderedRound o, int &starts) {
+    for (int run = 1; o.where; run *= 2, ++starts) {   // (the same in every lane)
         int next = __builtin_ctzll(o.where);
         s = read_lane(o.before, next);   // (exact: every lane before it is good)
         const int end = next + run < 64 ? next + run : 64;
@@ -301,13 +302,19 @@ __device__ inline int exact_ray_chain(const RecheckArgs &a, int64_t i, int64_t j
 }
 
 // The sums many terms at a time: lanes form the terms of J consecutive lenses each, and
-// add_in_order adds them in lens order. A sum that starts at zero or stays near it (a ray on
-// its lenses' mirror axis) starts over again and again, so that the chain is the faster form
-// for maps of few lenses. Time per ray, four waves per CU, chain against this form: 512 lenses
-// 5.9 / 12.4 us, 2000 20.7 / 27.4, 8000 80 / 93, 16000 156 / 163, 32000 310 / 301, 64000
-// 618 / 350, 10^6 9650 / 4460; on a mirror axis 512 lenses 5.8 / 12.5, 32000 310 / 511, 128000
-// 1237 / 1147. The line lies where a ray of a random field takes as long by either.
-constexpr int64_t EXACT_CHAIN_LENSES = 32768;
+// add_in_order adds a chunk of 64 J of them in lens order. Where a sum starts at zero, or stays
+// small beside its terms (near the field's centre, on the lenses' mirror axis), it starts over
+// again and again and takes up to twice the chain's time, so the first 4096 lenses, and after a
+// chunk of more than STARTS_MAX starts over the next chunks too (more of them each time it
+// happens again), are added one by one, both sums at once. One ray among n lenses, chain / this
+// form / this form without that pause, at 0.05, 0.3 and 0.7 of the field's radius and on a mirror
+// axis, in us: 8000 lenses 81 / 101, 92, 67, 97 / 135, 106, 62, 153; 16000 158 / 168, 176, 104, 184 /
+// 184, 184, 106, 273; 64000 619 / 564, 587, 239, 699 / 590, 603, 220, 988; 10^6 9.68 ms / 5.48, 4.37,
+// 2.72, 7.03 / 5.46, 4.37, 2.72, 6.65. The line between the forms lies where they come out even.
+constexpr int64_t EXACT_CHAIN_LENSES = 8192;
+// In batches the chain alone up to this many lenses: both forms in the scan's kernel leave it no
+// registers for more than the two waves per SIMD it has, and its rays are spread over many waves.
+constexpr int64_t BATCH_CHAIN_LENSES = 32768;
 template <bool UNIT, int J = 8>
 __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_t j) {
     const int lane = __lane_id();
@@ -320,6 +327,8 @@ __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_
     // never become -0), and the next lenses are loaded while these are summed.
     const int64_t last = a.n_lens - 1;
     double X[J], Y[J], M[J];
+    constexpr int FIRST = 64 / J, STARTS_MAX = 6, PAUSE_MIN = 4, PAUSE_MAX = 32;
+    int one_by_one = FIRST, pause = PAUSE_MIN;   // chunks
     auto load = [&](int64_t k0) {
 #pragma unroll
         for (int u = 0; u < J; ++u) {
@@ -345,9 +354,31 @@ __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_
             t2[u] = real ? f * d2 : 0.0;
         }
         load(mine + 64 * J);
-        const OrderedRound o1 = ordered_round(a1, t1, 0), o2 = ordered_round(a2, t2, 0);
-        a1 = add_in_order(a1, t1, o1);
-        a2 = add_in_order(a2, t2, o2);
+        if (one_by_one > 0) {
+            --one_by_one;
+            const int64_t lanes = (a.n_lens - k0 + J - 1) / J;
+#pragma unroll 1
+            for (int l = 0; l < (lanes < 64 ? (int)lanes : 64); ++l) {   // every lane adds its own terms; lane l's sums count
+#pragma unroll
+                for (int u = 0; u < J; ++u) {
+                    a1 += t1[u];
+                    a2 += t2[u];
+                }
+                a1 = read_lane(a1, l);
+                a2 = read_lane(a2, l);
+            }
+        } else {
+            int starts = 0;
+            const OrderedRound o1 = ordered_round(a1, t1, 0), o2 = ordered_round(a2, t2, 0);
+            a1 = add_in_order(a1, t1, o1, starts);
+            a2 = add_in_order(a2, t2, o2, starts);
+            if (starts > STARTS_MAX) {
+                one_by_one = pause;
+                pause = pause < PAUSE_MAX ? 2 * pause : PAUSE_MAX;
+            } else {
+                pause = PAUSE_MIN;
+            }
+        }
     }
     if (__ballot(zero)) return CODE_SINGULAR;
     return definition_pixel(a, x1, x2, a1, a2);

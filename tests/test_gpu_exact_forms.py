@@ -1,6 +1,6 @@
 """Stage B of the re-check in each of its forms (the chain of additions, the sums many terms at
 a time) and places (the far-field re-check's kernel, a kernel of its own, the gathered list, the
-batch), at the lens counts where one takes over from another: 2048 and 32768. Every ray of
+batch), at the lens counts where one takes over from another: 2048, 8192 and 32768. Every ray of
 the middle column sits on the mirror axis of its lenses, its deflection is rounding noise, and
 the map's left edge lies on the axis, so that its pixel is the last bit of the sum."""
 import numpy as np
@@ -10,7 +10,7 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-COUNTS = [1, 2046, 2048, 2050, 32766, 32768, 32770]
+COUNTS = [1, 2046, 2048, 2050, 8190, 8192, 8194, 32766, 32768, 32770]
 
 
 def _mirrored(n, masses):
@@ -27,7 +27,7 @@ def _params(rs):
     return rs.map_params(0.4, 0.0, 0.1, (-2.0625, -2.0, 4.125, 4.0, 33, 64), (0.0, -4.0, 8.0, 8.0, 64, 64))
 
 
-@pytest.mark.parametrize("n", COUNTS)
+@pytest.mark.parametrize("n", COUNTS + [12290, 40002, 131074])
 @pytest.mark.parametrize("masses", [False, True])
 @pytest.mark.parametrize("mode", ["mixed", "farfield"])
 def test_single_maps(n, masses, mode):
