@@ -509,7 +509,7 @@ hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_onl
         const dim3 grid((unsigned)queue_blocks(max_rays, 1, 2048));   // (a block per ray of a short queue)
         auto launch = [&](auto u) {
             constexpr bool U = decltype(u)::value;
-            if (crowded(max_rays, a.n_lens)) {
+            if (crowded(a.nx, a.ny, a.n_lens)) {
                 hipLaunchKernelGGL((recheck_fast_kernel<U, FORM_THREADS>), threads, block, 0, stream, b);
                 hipLaunchKernelGGL((recheck_fast_kernel<U, FORM_BLOCKS>), grid, block, 0, stream, b);
             } else {

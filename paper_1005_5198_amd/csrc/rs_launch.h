@@ -78,10 +78,11 @@ inline bool recheck_in_one(int64_t rays, int64_t n_lens, bool several_launches) 
     return !several_launches && (double)rays * (double)n_lens <= RECHECK_ONE_PAIRS;
 }
 
-// Launches with fewer rays than this per lens have more lenses near a patch (a super-patch) than the
-// deflection's near-lens list (the lens lists of stage F and of the far-field mode) holds, if the
-// lenses are spread evenly: a patch has 2048 rays and lists at most 64 lenses of 16000 rays'
-// area about it, a super-patch at most 4096 of 10^6 rays'. Most of their rays come to stage A.
-inline bool crowded(int64_t rays, int64_t n_lens) { return (double)rays < 256.0 * (double)n_lens; }
+// Ray grids (whole, whatever the window and launch) with fewer rays than this per lens have more
+// lenses near a patch (a super-patch) than the deflection's near-lens list (the lens lists of
+// stage F and of the far-field mode) holds, if the lenses are spread evenly over the grid: a patch
+// has 2048 rays and lists at most 64 lenses of 16000 rays' area about it, a super-patch at most
+// 4096 of 10^6 rays'. Most of their rays come to stage A.
+inline bool crowded(int64_t nx, int64_t ny, int64_t n_lens) { return (double)nx * (double)ny < 256.0 * (double)n_lens; }
 
 }  // namespace rs

@@ -41,9 +41,9 @@ int main() {
             if (scanf("%" SCNu32 " %" SCNu32, &ticket, &n_blocks) != 2) return 1;
             printf("%" PRId64 "\n", ticket_patch(ticket, n_blocks));
         } else if (!strcmp(what, "crowded")) {
-            int64_t rays, n_lens;
-            if (scanf("%" SCNd64 " %" SCNd64, &rays, &n_lens) != 2) return 1;
-            printf("%d\n", crowded(rays, n_lens) ? 1 : 0);
+            int64_t nx, ny, n_lens;
+            if (scanf("%" SCNd64 " %" SCNd64 " %" SCNd64, &nx, &ny, &n_lens) != 3) return 1;
+            printf("%d\n", crowded(nx, ny, n_lens) ? 1 : 0);
         } else if (!strcmp(what, "entry_run")) {
             uint32_t entries, n_waves;
             if (scanf("%" SCNu32 " %" SCNu32, &entries, &n_waves) != 2) return 1;

@@ -75,12 +75,18 @@ def test_one_kernel_for_the_stages_of_small_maps_only(ask):
 
 
 def test_crowded_maps(ask):
-    """Maps whose lists cannot hold the lenses nearby, most of whose rays come to stage A."""
-    assert ask("crowded", 3000 * 3000, 300000) == [1]
-    assert ask("crowded", 19200 * 3840, 17240) == [0]
-    assert ask("crowded", 256 * 1000, 1000) == [0] and ask("crowded", 256 * 1000 - 1, 1000) == [1]
-    assert ask("crowded", 1 << 27, (1 << 62)) == [1]   # (no overflow)
-    assert ask("crowded", 0, 0) == [0]
+    """Maps whose lists cannot hold the lenses nearby, most of whose rays come to stage A; by the
+    whole ray grid, not a window or launch of it."""
+    assert ask("crowded", 3000, 3000, 300000) == [1]
+    assert ask("crowded", 19200, 3840, 17240) == [0]
+    assert ask("crowded", 55902, 55902, 10 ** 6) == [0]   # (a launch of it has 130 rays per lens)
+    assert ask("crowded", 256, 1000, 1000) == [0] and ask("crowded", 255, 1000, 1000) == [1]
+    assert ask("crowded", 1 << 27, 1, 1 << 62) == [1] and ask("crowded", 1 << 51, 1 << 51, 1) == [0]   # (no overflow)
+    assert ask("crowded", 0, 0, 0) == [0]
+
+
+def test_crowded_is_asked_of_the_whole_grid():
+    assert "crowded(a.nx, a.ny, a.n_lens)" in _function("recheck.hip", "launch_recheck")
 
 
 @pytest.mark.parametrize("blocks", [1, 2, 32, 768])
