@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void recheck_fast_kernel(const RecheckArgs a) 
     count_wave(a.counters, n_in, n_out, 0ull);
 }
 
-template <bool UNIT, bool CHAIN>
+template <bool UNIT, ExactForm FORM>
 __global__ __launch_bounds__(256) void recheck_exact_wave_kernel(const RecheckArgs a) {
     if (a.qunres && *a.qunres == 0u) return;   // stage A decided every entry
     const uint32_t n = *a.qcount;
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void recheck_exact_wave_kernel(const RecheckAr
             const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)q_lane, src) & ~UNRESOLVED;
             const int64_t i = a.i0 + (int64_t)(q % (uint64_t)W);
             const int64_t j = a.jc0 + (int64_t)(q / (uint64_t)W);
-            const int code = exact_ray_wave<UNIT, CHAIN>(a, i, j);
+            const int code = exact_ray_wave<UNIT, FORM>(a, i, j);
             if (lane == 0) emit_ray(a, i, j, code);
         }
     }
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void recheck_fast_deferred_kernel(const Rechec
 }
 
 // The exact stage over the gathered rays stage A left, one wave per ray.
-template <bool UNIT, bool CHAIN>
+template <bool UNIT, ExactForm FORM>
 __global__ __launch_bounds__(256) void recheck_exact_deferred_kernel(const RecheckArgs a) {
     const uint32_t n = *a.ucount;
     const int lane = __lane_id();
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void recheck_exact_deferred_kernel(const Reche
     const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t e = wave_id; e < n; e += n_waves) {
         const int64_t i = a.udefer[2 * (int64_t)e], j = a.udefer[2 * (int64_t)e + 1];
-        const int code = exact_ray_wave<UNIT, CHAIN>(a, i, j);
+        const int code = exact_ray_wave<UNIT, FORM>(a, i, j);
         if (lane == 0) emit_ray(a, i, j, code);
     }
 }
@@ -390,9 +390,9 @@ __device__ inline void batch_stage_b(const BatchArgs &b, QueueEntry e, int n_val
         const bool unit = ALL_UNIT || a.lens_m == nullptr;
         int code;
         if (CHAIN || a.n_lens <= BATCH_CHAIN_LENSES)
-            code = unit ? exact_ray_wave<true, true>(a, i, j) : exact_ray_wave<false, true>(a, i, j);
+            code = unit ? exact_ray_chain<true>(a, i, j) : exact_ray_chain<false>(a, i, j);
         else
-            code = unit ? exact_ray_parallel<true, 4>(a, i, j) : exact_ray_parallel<false, 4>(a, i, j);
+            code = unit ? exact_ray_parallel<true, 4, false>(a, i, j) : exact_ray_parallel<false, 4, false>(a, i, j);
         if (lane == 0) emit_ray(a, i, j, code);
     }
 }
@@ -479,15 +479,20 @@ __global__ __launch_bounds__(256) void recheck_scan_batch_kernel(const BatchArgs
 
 }  // namespace
 
+// f with the exact stage's form for a map of n_lens lenses.
+template <class F>
+static void with_exact_form(int64_t n_lens, F f) {
+    if (n_lens <= EXACT_CHAIN_LENSES) f(std::integral_constant<ExactForm, EXACT_CHAIN>{});
+    else if (n_lens < EXACT_PAUSE_LENSES) f(std::integral_constant<ExactForm, EXACT_PAUSE>{});
+    else f(std::integral_constant<ExactForm, EXACT_PARALLEL>{});
+}
+
 static void launch_exact_wave(const RecheckArgs &a, dim3 grid, hipStream_t stream) {
-    const dim3 block(256);
-    auto launch = [&](auto unit) {
-        constexpr bool U = decltype(unit)::value;
-        if (a.n_lens <= EXACT_CHAIN_LENSES) hipLaunchKernelGGL((recheck_exact_wave_kernel<U, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((recheck_exact_wave_kernel<U, false>), grid, block, 0, stream, a);
-    };
-    if (a.lens_m == nullptr) launch(std::true_type{});
-    else launch(std::false_type{});
+    with_exact_form(a.n_lens, [&](auto form) {
+        constexpr ExactForm FORM = decltype(form)::value;
+        if (a.lens_m == nullptr) hipLaunchKernelGGL((recheck_exact_wave_kernel<true, FORM>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((recheck_exact_wave_kernel<false, FORM>), grid, dim3(256), 0, stream, a);
+    });
 }
 
 hipError_t launch_recheck(const RecheckArgs &a, int64_t max_rays, bool exact_only, bool stage_a_done, hipStream_t stream) {
@@ -528,8 +533,9 @@ hipError_t launch_recheck_deferred(const RecheckArgs &a, hipStream_t stream) {
     auto launch = [&](auto unit) {
         constexpr bool U = decltype(unit)::value;
         hipLaunchKernelGGL(recheck_fast_deferred_kernel<U>, grid, block, 0, stream, a);
-        if (a.n_lens <= EXACT_CHAIN_LENSES) hipLaunchKernelGGL((recheck_exact_deferred_kernel<U, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((recheck_exact_deferred_kernel<U, false>), grid, block, 0, stream, a);
+        with_exact_form(a.n_lens, [&](auto form) {
+            hipLaunchKernelGGL((recheck_exact_deferred_kernel<U, decltype(form)::value>), grid, block, 0, stream, a);
+        });
     };
     if (a.lens_m == nullptr) launch(std::true_type{});
     else launch(std::false_type{});

@@ -305,17 +305,19 @@ __device__ inline int exact_ray_chain(const RecheckArgs &a, int64_t i, int64_t j
 // add_in_order adds a chunk of 64 J of them in lens order. Where a sum starts at zero, or stays
 // small beside its terms (near the field's centre, on the lenses' mirror axis), it starts over
 // again and again and takes up to twice the chain's time, so the first 4096 lenses, and after a
-// chunk of more than STARTS_MAX starts over the next chunks too (more of them each time it
-// happens again), are added one by one, both sums at once. One ray among n lenses, chain / this
+// chunk of more than six starts over the next chunks too (more of them each time it happens
+// again), are added one by one, both sums at once (PAUSE; not in maps of 131072 lenses or more,
+// where that saves nothing). One ray among n lenses, chain / this
 // form / this form without that pause, at 0.05, 0.3 and 0.7 of the field's radius and on a mirror
-// axis, in us: 8000 lenses 81 / 101, 92, 67, 97 / 135, 106, 62, 153; 16000 158 / 168, 176, 104, 184 /
-// 184, 184, 106, 273; 64000 619 / 564, 587, 239, 699 / 590, 603, 220, 988; 10^6 9.68 ms / 5.48, 4.37,
-// 2.72, 7.03 / 5.46, 4.37, 2.72, 6.65. The line between the forms lies where they come out even.
+// axis, in us: 8000 lenses 81 / 104, 93, 67, 99 / 135, 106, 62, 153; 16000 158 / 165, 172, 104, 189 /
+// 184, 184, 106, 273; 64000 619 / 553, 589, 229, 699 / 590, 603, 220, 988; 10^6 9.68 ms / 5.45, 4.37,
+// 2.71, 7.01 / 5.46, 4.37, 2.72, 6.65. The line between the forms lies where they come out even.
 constexpr int64_t EXACT_CHAIN_LENSES = 8192;
+constexpr int64_t EXACT_PAUSE_LENSES = 131072;
 // In batches the chain alone up to this many lenses: both forms in the scan's kernel leave it no
 // registers for more than the two waves per SIMD it has, and its rays are spread over many waves.
 constexpr int64_t BATCH_CHAIN_LENSES = 32768;
-template <bool UNIT, int J = 8>
+template <bool UNIT, int J, bool PAUSE>
 __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_t j) {
     const int lane = __lane_id();
     double x1, x2;
@@ -327,7 +329,7 @@ __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_
     // never become -0), and the next lenses are loaded while these are summed.
     const int64_t last = a.n_lens - 1;
     double X[J], Y[J], M[J];
-    constexpr int FIRST = 64 / J, STARTS_MAX = 6, PAUSE_MIN = 4, PAUSE_MAX = 32;
+    constexpr int FIRST = 64 / J, STARTS_MAX = 6, PAUSE_MIN = 1, PAUSE_MAX = 64;
     int one_by_one = FIRST, pause = PAUSE_MIN;   // chunks
     auto load = [&](int64_t k0) {
 #pragma unroll
@@ -354,7 +356,7 @@ __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_
             t2[u] = real ? f * d2 : 0.0;
         }
         load(mine + 64 * J);
-        if (one_by_one > 0) {
+        if (PAUSE && one_by_one > 0) {
             --one_by_one;
             const int64_t lanes = (a.n_lens - k0 + J - 1) / J;
 #pragma unroll 1
@@ -374,7 +376,7 @@ __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_
             a2 = add_in_order(a2, t2, o2, starts);
             if (starts > STARTS_MAX) {
                 one_by_one = pause;
-                pause = pause < PAUSE_MAX ? 2 * pause : PAUSE_MAX;
+                pause = pause < PAUSE_MAX ? 4 * pause : PAUSE_MAX;
             } else {
                 pause = PAUSE_MIN;
             }
@@ -384,10 +386,11 @@ __device__ inline int exact_ray_parallel(const RecheckArgs &a, int64_t i, int64_
     return definition_pixel(a, x1, x2, a1, a2);
 }
 
-template <bool UNIT, bool CHAIN>
+enum ExactForm { EXACT_CHAIN, EXACT_PAUSE, EXACT_PARALLEL };
+template <bool UNIT, ExactForm FORM>
 __device__ __forceinline__ int exact_ray_wave(const RecheckArgs &a, int64_t i, int64_t j) {
-    if constexpr (CHAIN) return exact_ray_chain<UNIT>(a, i, j);
-    else return exact_ray_parallel<UNIT>(a, i, j);
+    if constexpr (FORM == EXACT_CHAIN) return exact_ray_chain<UNIT>(a, i, j);
+    else return exact_ray_parallel<UNIT, 8, FORM == EXACT_PAUSE>(a, i, j);
 }
 
 // Maps of at most this many lenses and of one launch run stage B in stage A's kernel.

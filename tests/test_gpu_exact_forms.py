@@ -27,7 +27,7 @@ def _params(rs):
     return rs.map_params(0.4, 0.0, 0.1, (-2.0625, -2.0, 4.125, 4.0, 33, 64), (0.0, -4.0, 8.0, 8.0, 64, 64))
 
 
-@pytest.mark.parametrize("n", COUNTS + [12290, 40002, 131074])
+@pytest.mark.parametrize("n", COUNTS + [12290, 40002, 131070, 131074])
 @pytest.mark.parametrize("masses", [False, True])
 @pytest.mark.parametrize("mode", ["mixed", "farfield"])
 def test_single_maps(n, masses, mode):

@@ -40,7 +40,7 @@ def _kernels(source, pattern):
 # (the figures are the kernels' own before they took a second form in)
 @pytest.mark.parametrize("pattern,waves,scratch", [
     (r"recheck_scan_batch_kernel<1,", 2, 16),        # the batch's exact stage
-    (r"recheck_exact_wave_kernel<\w+, true>", 3, 0),   # a map's, chain
+    (r"recheck_exact_wave_kernel<\w+, .*ExactForm\)0>", 3, 0),   # a map's, chain
 ])
 def test_exact_stage_keeps_its_waves(pattern, waves, scratch):
     for name, u in _kernels("recheck.hip", pattern).items():
