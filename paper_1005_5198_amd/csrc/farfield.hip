@@ -981,11 +981,13 @@ constexpr int LANE_STAGE_MIN = 32;
 // of one deflection block are adjacent and share a super-patch, so a wave that takes adjacent
 // entries walks one list (dealt one by one to the waves, which spreads the rays stage F
 // leaves more evenly, 5000-lens maps with every ray queued took 1.7 times as long).
-// With stage A it takes the registers of two waves per SIMD (held to three it spills, and a small
-// map's call takes up to 5% longer).
-constexpr int64_t STAGE_A_BLOCKS = 512;   // two waves per SIMD
+// With stage A it takes the registers of three waves per SIMD, which leaves none for loading its
+// wave form's lenses a step ahead (two waves that do: 700^2 rays, 900 lenses in clusters, 338 us
+// a call; three that don't: 319).
+constexpr int64_t STAGE_A_BLOCKS = 768;   // three waves per SIMD
+constexpr uint32_t RUN_WAVES = 1024;      // one per SIMD
 template <bool UNIT, bool STAGE_A>
-__global__ __launch_bounds__(256, STAGE_A ? 2 : 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
+__global__ __launch_bounds__(256, STAGE_A ? 3 : 4) void recheck_far_kernel(const ShootArgs a, const RecheckArgs r, uint32_t *qlive) {
     __shared__ uint32_t sums[3];   // rays in the map, out, left
     const uint32_t n = *a.qcount;
     if (n == 0) return;
@@ -998,7 +1000,7 @@ __global__ __launch_bounds__(256, STAGE_A ? 2 : 4) void recheck_far_kernel(const
     uint32_t n_in = 0, n_out = 0, left = 0;   // this lane's
     const bool wave_form = n <= FAR_WAVE_MAX;
     if (STAGE_A && wave_id == 0 && lane == 0) atomicAdd(a.counters + C_RECHECK, (unsigned long long)n);
-    const uint32_t run = wave_form ? 1u : entry_run(n, n_waves);   // entries a wave takes at a time
+    const uint32_t run = wave_form ? 1u : entry_run(n, RUN_WAVES);   // entries a wave takes at a time
     for (uint64_t first = (uint64_t)run * wave_id; first < n; first += (uint64_t)run * n_waves) {
         const uint64_t idx = wave_form ? first : first + (uint32_t)lane;
         const bool mine = wave_form ? lane == 0 : (uint32_t)lane < run && idx < n;   // this lane records the entry's result
@@ -1024,7 +1026,7 @@ __global__ __launch_bounds__(256, STAGE_A ? 2 : 4) void recheck_far_kernel(const
                     todo &= todo - 1;
                     const uint32_t qs = (uint32_t)__builtin_amdgcn_readlane((int)q, src);
                     int c = 0;
-                    if (!fast_ray_wave<UNIT, 4>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c)) undecided |= 1ull << src;
+                    if (!fast_ray_wave<UNIT, 4, false>(r, a.i0 + (int64_t)(qs % W), a.jc0 + (int64_t)(qs / W), c)) undecided |= 1ull << src;
                     else if (lane == src) code = c;
                 }
             }

@@ -509,7 +509,9 @@ __device__ __forceinline__ int64_t fast_steps(const RecheckArgs &a, int U) {
 // are many lenses, blocks of 4096 add little to the bound.)
 __device__ __forceinline__ int fast_block(const RecheckArgs &a, int U) { return (a.n_lens < (1 << 18) ? 16 : 64) / U; }
 
-template <bool UNIT, int R, int U>
+// AHEAD: as written above; without it a step's lenses are loaded at its start, for kernels short
+// of registers.
+template <bool UNIT, int R, int U, bool AHEAD = true>
 __device__ inline void fast_sums(const RecheckArgs &a, const double (&x1)[R], const double (&x2)[R], int64_t it0,
                                  int64_t it1, FastSums (&out)[R]) {
     double a1[R], a2[R], S[R], Q1[R], Q2[R];
@@ -554,8 +556,9 @@ __device__ inline void fast_sums(const RecheckArgs &a, const double (&x1)[R], co
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
         return v;
     };
-    if (it0 < it1) load(it0);
+    if (AHEAD && it0 < it1) load(it0);
     for (int64_t it = it0; it < it1; ++it) {
+        if (!AHEAD) load(it);
         double X[U], Y[U], M[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -563,7 +566,7 @@ __device__ inline void fast_sums(const RecheckArgs &a, const double (&x1)[R], co
             Y[u] = LY[u];
             M[u] = LM[u];
         }
-        if (it + 1 < it1) load(it + 1);
+        if (AHEAD && it + 1 < it1) load(it + 1);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             double d1[U], d2[U], r2[U], rc[U];
@@ -615,7 +618,7 @@ __device__ inline void fast_sums(const RecheckArgs &a, const double (&x1)[R], co
 }
 
 // Stage A by a whole wave for R rays, ray r at (i[r], j[r]) (wave-uniform).
-template <bool UNIT, int R, int U>
+template <bool UNIT, int R, int U, bool AHEAD = true>
 __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R], const int64_t (&j)[R],
                                       bool (&decided)[R], int (&code)[R]) {
     double x1[R], x2[R];
@@ -623,7 +626,7 @@ __device__ inline void fast_rays_wave(const RecheckArgs &a, const int64_t (&i)[R
     for (int r = 0; r < R; ++r) ray_xy(a, i[r], j[r], x1[r], x2[r]);
     const int64_t steps = fast_steps(a, U);
     FastSums f[R];
-    fast_sums<UNIT, R, U>(a, x1, x2, 0, steps, f);
+    fast_sums<UNIT, R, U, AHEAD>(a, x1, x2, 0, steps, f);
     // a partial sum's depth: a lane's running sum plus the six butterfly levels
     const double depth = (double)steps * U + 6.0, B = 64.0 * U * fast_block(a, U);
 #pragma unroll
@@ -667,12 +670,12 @@ __device__ inline bool fast_ray_block(const RecheckArgs &a, int64_t i, int64_t j
 }
 
 // U: 8 where a kernel has the registers (a lone wave waits less for its lenses), 4 elsewhere.
-template <bool UNIT, int U>
+template <bool UNIT, int U, bool AHEAD = true>
 __device__ inline bool fast_ray_wave(const RecheckArgs &a, int64_t i, int64_t j, int &code) {
     const int64_t ri[1] = {i}, rj[1] = {j};
     bool decided[1];
     int c[1] = {code};
-    fast_rays_wave<UNIT, 1, U>(a, ri, rj, decided, c);
+    fast_rays_wave<UNIT, 1, U, AHEAD>(a, ri, rj, decided, c);
     code = c[0];
     return decided[0];
 }

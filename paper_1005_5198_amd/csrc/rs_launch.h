@@ -53,8 +53,9 @@ inline int64_t queue_blocks(int64_t max_entries, int64_t per_block, int64_t cap)
     return blocks < 1 ? 1 : (blocks > cap ? cap : blocks);
 }
 
-// Adjacent entries of a long queue that a wave takes at a time: as many as give every wave some,
-// at most one per lane.
+// Adjacent entries of a long queue that a wave takes at a time: as many as give n_waves waves some,
+// at most one per lane. (Shorter runs for more waves leave lanes idle that would walk the same
+// list: 1024^2 rays, 900 lenses in clusters, 301 us with runs for a wave per SIMD, 340 for three.)
 RS_HOST_DEVICE inline uint32_t entry_run(uint32_t entries, uint32_t n_waves) {
     const uint32_t share = (uint32_t)(((uint64_t)entries + n_waves - 1) / n_waves);
     return share < 64u ? share : 64u;

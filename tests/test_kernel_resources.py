@@ -51,3 +51,10 @@ def test_stage_a_by_thread_keeps_its_waves():
     """Stage A with a thread per ray, in a kernel without the form for short queues (1: FORM_THREADS)."""
     for name, u in _kernels("recheck.hip", r"recheck_fast_kernel<\w+, .*StageAForm\)1>").items():
         assert u["waves"] >= 4 and u["scratch"] == 0, (name, u)
+
+
+def test_the_stages_in_one_kernel_keep_three_waves():
+    """Stage F with stages A and B in its kernel (small maps): a small map's queue is a wave or
+    two per SIMD of loads and reductions, which a third hides."""
+    for name, u in _kernels("farfield.hip", r"recheck_far_kernel<\w+, true>").items():
+        assert u["waves"] >= 3 and u["scratch"] == 0, (name, u)
