@@ -535,16 +535,28 @@ __global__ __launch_bounds__(MAX_THREADS) void max_kernel(const uint32_t *map, i
 // Four pixels per thread and step where both arrays are aligned for it. TABLE: dm of the
 // counts below LDS_BINS from an LDS table of the same values (each block makes its own, so
 // only where a block has many more pixels than that): a logarithm takes some 100 FP64
-// instructions, which bound the plain form on large maps.
+// instructions, which bound the plain form on large maps. One count beyond the table costs its
+// wave a logarithm, so that a block makes a table only if at least half of DM_THREADS / 64 runs of
+// 64 pixels, spread over the map, hold none (16.8 million pixels of 5000 and
+// more: 61 us; 76 with tables for nothing, 59 by the plain form; below 700: 36).
 template <bool TABLE>
-__global__ __launch_bounds__(256) void delta_m_kernel(const uint32_t *map, int64_t npix, double n_rays, double *dm, int vec4) {
+constexpr int DM_THREADS = TABLE ? 512 : 256;
+template <bool TABLE>
+__global__ __launch_bounds__(DM_THREADS<TABLE>) void delta_m_kernel(const uint32_t *map, int64_t npix, double n_rays, double *dm, int vec4) {
+    constexpr int THREADS = DM_THREADS<TABLE>;
     __shared__ double tbl[TABLE ? LDS_BINS : 1];
+    const int64_t gid = blockIdx.x * (int64_t)THREADS + threadIdx.x, stride = (int64_t)gridDim.x * THREADS;
+    uint32_t bins = 0;   // counts whose dm is in the table
     if (TABLE) {
-        for (int k = threadIdx.x; k < LDS_BINS; k += 256) tbl[k] = delta_m_of((uint32_t)k, n_rays);
-        __syncthreads();
+        const int64_t wave = gid / 64, n_waves = stride / 64;
+        const uint32_t sample = map[wave * (npix / n_waves) + (gid & 63)];   // (npix >= DM_TABLE_MIN: 64 n_waves at least)
+        if (2 * __syncthreads_count(__all(sample < (uint32_t)LDS_BINS)) >= THREADS) {
+            bins = LDS_BINS;
+            for (int k = threadIdx.x; k < LDS_BINS; k += THREADS) tbl[k] = delta_m_of((uint32_t)k, n_rays);
+            __syncthreads();
+        }
     }
-    auto value = [&](uint32_t c) { return TABLE && c < (uint32_t)LDS_BINS ? tbl[c] : delta_m_of(c, n_rays); };
-    const int64_t gid = blockIdx.x * (int64_t)256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+    auto value = [&](uint32_t c) { return TABLE && c < bins ? tbl[c] : delta_m_of(c, n_rays); };
     int64_t tail = 0;
     if (vec4) {
         const int64_t n4 = npix / 4;
@@ -650,7 +662,7 @@ int rs_delta_m(const uint32_t *map, int64_t npix, double n_rays, double *dm, voi
     const int vec4 = aligned(map, 16) && aligned(dm, 16) ? 1 : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (npix >= DM_TABLE_MIN)
-        hipLaunchKernelGGL(delta_m_kernel<true>, dim3(1024), dim3(256), 0, s, map, npix, n_rays, dm, vec4);
+        hipLaunchKernelGGL(delta_m_kernel<true>, dim3(1024), dim3(DM_THREADS<true>), 0, s, map, npix, n_rays, dm, vec4);
     else
         hipLaunchKernelGGL(delta_m_kernel<false>, dim3(stream_blocks(npix, 256 * 4, 4096)), dim3(256), 0, s, map, npix,
                            n_rays, dm, vec4);
