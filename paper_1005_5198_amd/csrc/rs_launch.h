@@ -68,22 +68,24 @@ RS_HOST_DEVICE inline uint32_t entry_run(uint32_t entries, uint32_t n_waves) {
 RS_HOST_DEVICE inline int64_t first_patch(uint32_t block, uint32_t n_blocks, int turn) { return block + (int64_t)turn * n_blocks; }
 RS_HOST_DEVICE inline int64_t ticket_patch(uint32_t ticket, uint32_t n_blocks) { return 2ll * n_blocks + ticket; }
 
-// Mixed maps of one launch and at most this many ray-lens pairs take the re-check's stages F and A
-// in one kernel: a launch or two less, 4 us each, in a call of up to about 150 us. In larger maps
-// stage A follows in kernels of its own, in the form that suits the number of rays stage F left
-// and with those rays dealt out (in one kernel they stay with the waves that had them, and stage
-// F has fewer registers: 1024 x 512 rays, 5000 lenses 2.04 ms in kernels of their own, 2.40 in
-// one; where stage F leaves next to nothing, 2048 x 2048 rays and 300 lenses, 203 against 199 us).
-constexpr double RECHECK_ONE_PAIRS = 1.0e9;
-inline bool recheck_in_one(int64_t rays, int64_t n_lens, bool several_launches) {
-    return !several_launches && (double)rays * (double)n_lens <= RECHECK_ONE_PAIRS;
-}
-
 // Ray grids (whole, whatever the window and launch) with fewer rays than this per lens have more
 // lenses near a patch (a super-patch) than the deflection's near-lens list (the lens lists of
 // stage F and of the far-field mode) holds, if the lenses are spread evenly over the grid: a patch
 // has 2048 rays and lists at most 64 lenses of 16000 rays' area about it, a super-patch at most
 // 4096 of 10^6 rays'. Most of their rays come to stage A.
 inline bool crowded(int64_t nx, int64_t ny, int64_t n_lens) { return (double)nx * (double)ny < 256.0 * (double)n_lens; }
+
+// Mixed maps of one launch and at most this many ray-lens pairs take the re-check's stages F and A
+// in one kernel: a launch or two less, 4 us each, in a call of up to about 150 us. In larger maps
+// stage A follows in kernels of its own, in the form that suits the number of rays stage F left
+// and with those rays dealt out (in one kernel they stay with the waves that had them, and stage
+// F has fewer registers: 1024 x 512 rays, 20000 lenses 7.43 ms in kernels of their own, 7.73 in
+// one; 5000 lenses 755 and 750 us). Of crowded maps stage A takes
+// most rays, so that they are large at fewer pairs (512^2 rays, 1500 lenses 506 us in kernels of
+// their own, 574 in one; 256^2 and 3000 lenses 667 and 664).
+constexpr double RECHECK_ONE_PAIRS = 1.0e9, RECHECK_ONE_CROWDED = 2.0e8;
+inline bool recheck_in_one(int64_t rays, int64_t n_lens, bool several_launches, bool is_crowded) {
+    return !several_launches && (double)rays * (double)n_lens <= (is_crowded ? RECHECK_ONE_CROWDED : RECHECK_ONE_PAIRS);
+}
 
 }  // namespace rs

@@ -340,7 +340,7 @@ static int enqueue_planned(const rs_map_params *p, const double *lens_xy, const 
             r.qunres = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + 2 * pl.n_chunks + c;
             if (pl.defer) r.qleft = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + 3 * pl.n_chunks + c;
             const int64_t rays = (a.jc1 - a.jc0) * pl.W;
-            const bool stage_a_done = pl.far_recheck && recheck_in_one(rays, n_lens, pl.defer);
+            const bool stage_a_done = pl.far_recheck && recheck_in_one(rays, n_lens, pl.defer, crowded(p->nx, p->ny, n_lens));
             if (pl.far_recheck) {
                 uint32_t *qlive = reinterpret_cast<uint32_t *>(ws + WS_QCOUNT) + pl.n_chunks + c;
                 r.qlive = qlive;

@@ -18,9 +18,9 @@ int main() {
             printf("%" PRId64 "\n", queue_blocks(entries, per_block, cap));
         } else if (!strcmp(what, "recheck_in_one")) {
             int64_t rays, n_lens;
-            int several;
-            if (scanf("%" SCNd64 " %" SCNd64 " %d", &rays, &n_lens, &several) != 3) return 1;
-            printf("%d\n", recheck_in_one(rays, n_lens, several != 0) ? 1 : 0);
+            int several, is_crowded;
+            if (scanf("%" SCNd64 " %" SCNd64 " %d %d", &rays, &n_lens, &several, &is_crowded) != 4) return 1;
+            printf("%d\n", recheck_in_one(rays, n_lens, several != 0, is_crowded != 0) ? 1 : 0);
         } else if (!strcmp(what, "default_shape")) {
             int mixed;
             int64_t patches, cus;

@@ -67,11 +67,15 @@ def test_a_long_queue_gives_every_wave_some_entries(ask, n_waves):
 def test_one_kernel_for_the_stages_of_small_maps_only(ask):
     """Stage A shares stage F's kernel only where a call is short; what stage F leaves of a
     larger map is dealt out again by a kernel of its own."""
-    assert ask("recheck_in_one", 1 << 20, 462, 0) == [1]
-    assert ask("recheck_in_one", 1 << 20, 462, 1) == [0]
-    assert ask("recheck_in_one", 1 << 19, 5000, 0) == [0]
-    assert ask("recheck_in_one", 19200 * 3840, 17240, 0) == [0]
-    assert ask("recheck_in_one", 1 << 27, 1 << 40, 0) == [0]   # (no overflow)
+    assert ask("recheck_in_one", 1 << 20, 462, 0, 0) == [1]
+    assert ask("recheck_in_one", 1 << 20, 462, 1, 0) == [0]
+    assert ask("recheck_in_one", 1 << 19, 5000, 0, 0) == [0]
+    assert ask("recheck_in_one", 19200 * 3840, 17240, 0, 0) == [0]
+    assert ask("recheck_in_one", 1 << 27, 1 << 40, 0, 0) == [0]   # (no overflow)
+    # crowded maps, most of whose rays come to stage A: fewer pairs
+    assert ask("recheck_in_one", 256 * 256, 3000, 0, 1) == [1]
+    assert ask("recheck_in_one", 512 * 512, 1500, 0, 1) == [0]
+    assert ask("recheck_in_one", 512 * 512, 1500, 0, 0) == [1]
 
 
 def test_crowded_maps(ask):
