@@ -4,7 +4,7 @@
 // its probability, and the histogram of ray counts.
 //
 // Plan for a pair of maps (one stream, six launches):
-//   zero      clear the globals and both histograms (no hipMemsetAsync, so the
+//   zero      clear the globals and both histograms (by a kernel, so that the
 //             sequence stays valid under stream capture);
 //   pass      one streaming read of both maps (16-byte loads): per-block LDS
 //             histograms of the counts (counts >= LDS_BINS go straight to the
@@ -18,10 +18,12 @@
 //             of mu (dm is a decreasing function of mu, so the statistic is the
 //             same); the other map's CDF is read at the bin of the same value;
 //   final     one block: fixed-order sum of the partials, P(KS), the result.
-// The histograms hold 32-bit counts (a map has fewer than 2^31 pixels). A map's caustic
-// pixels reach 10^6 rays and more, so that the histograms are as long as a map, and
-// every kernel but the last is bound by memory; atomics on one address (12 ns each) are
-// kept to one per block or fewer. A call for two 4096^2 maps with counts up to 1.5e6 and
+// The histograms hold 32-bit counts (a map has fewer than 2^31 pixels) at the start of a
+// workspace of 8 bytes per bin, whose size is part of the interface. A map's caustic
+// pixels reach 10^6 rays and more, so that the histograms are as long as a map: zero, scan
+// and ks are bound by memory. The pass is bound by LDS (two atomics and two reads of the dm
+// tables per pair of pixels; it reads the maps at 1.9 TB/s). Atomics on one address
+// (12 ns each) are kept to one per block or fewer. A call for two 4096^2 maps with counts up to 1.5e6 and
 // 3e6 takes 145 us; it took 323 with 64-bit histograms, 8 waves per CU in the pass, a
 // binary search per bin and an atomic maximum per wave in ks, and a third scan launch.
 #include "rs_internal.h"
@@ -573,7 +575,7 @@ __global__ __launch_bounds__(DM_THREADS<TABLE>) void delta_m_kernel(const uint32
 }
 
 // Pixels from which delta_m's tables pay: 1024 blocks make one of LDS_BINS values each
-// (16.8 million pixels: 65 us a call with them, 69 without).
+// (6.3 million pixels of counts below 700: 22 us a call with them, 27 without).
 constexpr int64_t DM_TABLE_MIN = int64_t(3) * 1024 * LDS_BINS / 2;
 
 // Four pixels per thread until every CU has a block (16 per thread: 252 us instead of 230

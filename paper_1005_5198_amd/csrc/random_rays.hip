@@ -24,8 +24,9 @@ __device__ __forceinline__ int64_t bin_of(const ShootArgs &a, double x1, double 
 
 // Counting and scattering by blocks, each over one range of the launch's rays, with the
 // bins' counts in LDS: a block adds its count of a bin to the bin at once, and reserves its
-// slots of the bin at once; bins past the LDS counts' number (more than the largest launch
-// has, but for strips) take further rounds over the block's rays. One atomic per ray on the
+// slots of the bin at once; bins past the LDS counts' number (a launch of RAND_CHUNK_RAYS has
+// fewer, but a launch is at least 32 rows: 2^27 rays and 70600 bins of a window 2^22 wide) take
+// further rounds over the block's rays. One atomic per ray on the
 // bins bound both kernels: 4.9 million rays in 2600 bins took 0.48 ms each, now 0.05 and 0.2
 // (the scatter makes the positions twice); 60000 rays a map of 0.26 ms, now 0.06; launches of
 // 64 million rays a map of 9.1 ms, now 5.8 (6.2 with 1024 blocks, 8.5 with 512).
@@ -38,7 +39,7 @@ constexpr int64_t RAND_BLOCK_RAYS = 1024;   // at least, so that small launches 
 template <class F>
 __device__ __forceinline__ void block_rays(const ShootArgs &a, F f) {
     const uint32_t W = (uint32_t)(a.i1 - a.i0);                     // at most 2^22
-    const uint32_t n = (uint32_t)((a.jc1 - a.jc0) * (a.i1 - a.i0));   // at most RAND_CHUNK_RAYS, or one row
+    const uint32_t n = (uint32_t)((a.jc1 - a.jc0) * (a.i1 - a.i0));   // at most 2 RAND_CHUNK_RAYS (32 rows)
     const uint32_t per = (n + gridDim.x - 1) / gridDim.x;
     const uint32_t lo = min(n, blockIdx.x * per), hi = min(n, lo + per);
     for (uint32_t rel = lo + threadIdx.x; rel < hi; rel += RAND_THREADS) {
@@ -316,7 +317,10 @@ constexpr int FREE_RR = 8;
 constexpr int FREE_WAVES = 4;
 constexpr int FREE_CAP = 64 * FREE_WAVES * FREE_RR;
 
-// One block per bin; a bin with more rays than one chunk holds takes several passes.
+// One block per bin; a bin with more rays than one chunk holds takes several passes. Four waves
+// per SIMD: the mixed forms hold 128 registers by spilling 22 to 26 (92 to 108 bytes a lane; with
+// masses FP32 spills 2). 4950 x 990 rays, 17240 lenses, mixed: 14.97 ms; 15.14 with three waves,
+// which spill nothing.
 template <bool UNIT, int MODE, bool PIX>
 __global__ __launch_bounds__(64 * FREE_WAVES, 4) void shoot_free_kernel(const ShootArgs a) {
     __shared__ ShootSmem sm;

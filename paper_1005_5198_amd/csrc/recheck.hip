@@ -11,15 +11,16 @@
 //     almost every ray stage F left, identically to the definition, and marks
 //     the rest;
 //   stage B (exact_ray_wave): the marked rays, one wave per ray, with the
-//     definition's operations and the roundings of its order.
+//     definition's operations and the roundings of its order, in the form that suits the
+//     number of lenses (ExactForm).
 // RS_EXACT_RECHECK runs the exact sequence for every queued ray instead (one
 // thread per ray).
 //
 // Single map: the queue holds uint32 chunk-relative ray indices. Unless the
 // caller asked for the exact sequence only (or a random-ray window holds few of
-// its map's rays), the far-field stage (farfield.hip) runs first. In a map of one
-// launch its kernel takes its rays through stage A as well; otherwise it marks the
-// entries it decided RESOLVED, and stage A skips them and picks its form from the
+// its map's rays), the far-field stage (farfield.hip) runs first. In a small map of
+// one launch (recheck_in_one) its kernel takes its rays through stage A as well; otherwise it
+// marks the entries it decided RESOLVED, and stage A skips them and picks its form from the
 // number left (*qlive).
 // Batch: the deflection kernel sets one bit per flagged ray in each map's
 // bitmap; a persistent scan compacts the set bits per wave and the map's

@@ -1,6 +1,5 @@
-// Per-ray FP64 re-evaluation, shared by the re-check kernels (single map and
-// batch) and by the deflection kernel's in-place fallback when a batch queue
-// is full.
+// Per-ray FP64 re-evaluation, shared by the re-check kernels of single maps
+// (recheck.hip, farfield.hip) and of batches.
 //
 // exact_ray_*: the plain definition, operation for operation —
 //   ray position (Section 3.1 regular grid, cell-centred, or the ray's random point):
@@ -688,17 +687,6 @@ __device__ inline void emit_ray(const RecheckArgs &a, int64_t i, int64_t j, int 
         atomicAdd(a.map + code, 1u);
     }
     atomicAdd(a.counters + (code >= 0 ? C_IN : (code == CODE_OUT ? C_OUT : C_SING)), 1ull);
-}
-
-// Full re-check of one ray by one thread: stage A, then the exact sequence.
-__device__ inline int recheck_ray_thread(const RecheckArgs &a, int64_t i, int64_t j) {
-    int code = 0;
-    if (a.lens_m == nullptr) {
-        if (!fast_ray<true>(a, i, j, code)) code = exact_ray_thread<true>(a, i, j);
-    } else {
-        if (!fast_ray<false>(a, i, j, code)) code = exact_ray_thread<false>(a, i, j);
-    }
-    return code;
 }
 
 }  // namespace rs

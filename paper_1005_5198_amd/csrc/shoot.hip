@@ -10,8 +10,8 @@
 //    of LENS_TILE, converted once per block from FP64 to FP32 offsets relative
 //    to the patch centre, so FP32 carries small numbers and the per-block
 //    conversion is paid once per lens per 2048 rays.
-//  * Each lane owns RX x RY rays (4x2, 4x4, 8x2 or 8x4: a tuned choice), its
-//    rows in adjacent pairs; per lens it computes dx for RX columns and dy,
+//  * Each lane owns RX x RY rays (4x2, 4x4, 8x2 or 8x4, a tuned choice, or 2x2 with
+//    eight waves a patch in launches of few patches), its rows in adjacent pairs; per lens it computes dx for RX columns and dy,
 //    dy^2 for RY rows, then r^2 = fma(dx, dx, dy^2) per ray, one v_rcp_f32 per
 //    four rays (two adjacent rows of two columns 16 apart, of the product of
 //    their r^2) and nine multiplies, and two FMAs per ray. Every LDS read is a
@@ -23,10 +23,11 @@
 //    the FP32 error of every ray in the patch (lenses close to the patch are
 //    bounded per ray instead). A ray whose bound reaches a pixel edge goes to a
 //    queue that the FP64 re-check stages decide exactly as the definition does.
-//  * Binning: a block counts its rays per pixel in an LDS table and then adds each
-//    distinct pixel's count to the map with one atomic (one wave's rays fall on up to 64
-//    pixels, so aggregating within a wave alone took up to 64 rounds per ray of a lane:
-//    half of the time of the 1024^2-ray, 462-lens map).
+//  * Binning: a block counts its rays per pixel in an LDS table of lines of 16 adjacent
+//    pixels and then adds each used line's counts to the map, 16 lanes a line, so that a line
+//    costs one transaction (one wave's rays fall on up to 64 pixels, so aggregating within a
+//    wave alone took up to 64 rounds per ray of a lane: half of the time of the 1024^2-ray,
+//    462-lens map).
 #include "shoot_common.h"
 #include "rs_launch.h"
 

@@ -1,5 +1,5 @@
 // Device helpers shared by the deflection kernels (regular grid, random rays,
-// far field): error-bound constants, ray positions, wave-aggregated binning,
+// far field): error-bound constants, ray positions, binning by way of LDS,
 // re-check sinks, lens staging with the per-lens FP32 bound, and the per-ray
 // classification against a pixel edge.
 #pragma once
