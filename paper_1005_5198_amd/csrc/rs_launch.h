@@ -27,8 +27,8 @@ inline int default_shape(bool mixed, int64_t patches, int64_t compute_units) {
 // takes up to a quarter, 1024 at least, and as many more rays: a launch's last blocks, which leave
 // SIMDs with few waves, weigh on the shapes differently, and 4 million rays are under two rounds of
 // blocks. (19200 x 3840 rays, 17240 lenses, 4 x 2 rays per lane 132 ms, 4 x 4 137: 4 million rays
-// with every lens put 4 x 4 6% ahead, in 116 ms of tuning; 16 million 2% behind, in 442; 16 million
-// with a quarter of the lenses 2% behind, in 115.)
+// with every lens put 4 x 4 6% ahead, in 141 ms of tuning; 16 million 2% behind, in 533; 16 million
+// with a quarter of the lenses 2% behind, in 141.)
 struct TuneSample {
     int64_t rows, lenses;
 };
