@@ -1,4 +1,4 @@
-// Far-field expansion (RS_FARFIELD): two levels of FP64 local expansions of the
+// Far-field expansion (RS_FARFIELD): levels of FP64 local expansions of the
 // distant lenses, near lenses summed directly, a rigorous per-ray bound.
 #include "far_ray.h"
 #include "rs_decide.h"
@@ -11,7 +11,8 @@ namespace {
 // Far-field expansion (RS_FARFIELD). The paper's tree codes group distant
 // lenses into pseudo-lenses with higher multipoles (Section 2, Eq.
 // (hierarchical)); here distant lenses enter local expansions of the
-// deflection, to order FAR_P, on two levels:
+// deflection, to order FAR_P, on three levels, four from FF_TOP_MIN_LENSES lenses
+// on. The last two (tops of groups and groups of super-patches are alike):
 //   * super-patch (FF_SP_X x FF_SP_Y patches, centre zS, half-diagonal H):
 //     lenses farther than FAR_RATIO H give C_n = sum_k m_k tS_k^(n+1),
 //     tS_k = 1 / (zS - z_k); nearer lenses go to the super-patch's list;
@@ -21,7 +22,7 @@ namespace {
 //     t_k = 1 / (z0 - z_k); the rest are summed directly.
 // With z = x1 + i x2 and w = z - z0, sum_k m_k / (z - z_k) = sum_n (-w)^n T_n,
 // and the deflection (a1, a2) is (Re, -Im) of that sum. All of it is FP64; each
-// ray carries a rigorous bound (series truncation on both levels, rounding of
+// ray carries a rigorous bound (series truncation on every level, rounding of
 // the coefficients, the translation and the evaluation, the near sum) plus the
 // definition's own rounding, and rays within it of a pixel edge go to the FP64
 // re-check, so the map equals the definition's.
